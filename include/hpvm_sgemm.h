@@ -89,9 +89,14 @@ typedef enum hpvm_precision {
  *                   tiling against (Sec. 3.4, 5.1): one lane per element of
  *                   C reading A and B from global memory, tile_m x tile_n
  *                   lanes per launch group; 1 = one buffer
- *                   (literal lowering); 2 = two stages filled through
- *                   registers, conversion to bfloat16 (if any) fused into
- *                   that copy; 3 = staged BF16 / bf16x3 lowering: operands
+ *                   (literal lowering); 2 = FP32 tiles with other leaves
+ *                   than 128 wide: a ring of two to four LDS stages filled
+ *                   straight from HBM, for any sizes and alignment (but for
+ *                   products with n < 4 or rows 2^22 floats or more apart,
+ *                   which run a 64 x 64 x 16 tile filled through
+ *                   registers); BF16 and bf16x3: two stages filled through
+ *                   registers, conversion to bfloat16 fused into that copy;
+ *                   3 = staged BF16 / bf16x3 lowering: operands
  *                   converted into a workspace by a separate pass, then
  *                   moved into LDS stages: straight from HBM for every BF16
  *                   tile and for bf16x3's 256 x 256 tile and 128 x 128 x 64
@@ -107,8 +112,8 @@ typedef enum hpvm_precision {
  *                   16-byte aligned with leading dimensions that are
  *                   multiples of 4 (edge tiles computed from a corner moved
  *                   inward, storing only the outputs they own); any other
- *                   problem given such a tile runs FP32's 128 x 128 x 16
- *                   tile, or the register-staged BF16 / bf16x3 tile of the
+ *                   problem given such a tile runs a 64 x 128 x 32 FP32
+ *                   tile for any size, or the register-staged BF16 / bf16x3 tile of the
  *                   same size with tile_k = 32.
  * hpvm_tile_menu lists the combinations compiled into this library.       */
 typedef struct hpvm_tile {
@@ -201,9 +206,8 @@ typedef struct hpvm_edge {
  *                  in hpvm_tile_menu for prec and not need a workspace
  *                  (stages != 3).
  *   stream       : hipStream_t or NULL.
- * Returns HPVM_OK once the work is enqueued.  The MFMA lowerings use 16-byte
- * vector loads where A, B, C and their leading dimensions allow and scalar
- * loads elsewhere; any alignment is accepted.                              */
+ * Returns HPVM_OK once the work is enqueued.  Any alignment is accepted (of
+ * floats: 4 bytes).                                                        */
 int hpvm_sgemm(int64_t m, int64_t n, int64_t k, float alpha, const float* A,
                int64_t lda, const float* B, int64_t ldb, float beta, float* C,
                int64_t ldc, int32_t prec, const hpvm_tile* tile, void* stream);

@@ -9,6 +9,7 @@
 
 #include "device_common.hpp"
 #include "internal.hpp"
+#include "mfma_f32_any.hpp"
 #include "mfma_f32_dma.hpp"
 #include "mfma_bf16.hpp"
 #include "mfma_bf16_dma.hpp"
@@ -16,18 +17,12 @@
 
 namespace hpvm {
 
-// Waves per SIMD the register allocation must leave room for.  The
-// 128 x 128 x 16 tile fits four resident workgroups per CU without spills
-// (with its 38 KB of LDS each), so 4096^3 runs its 1024 tiles in one wave
-// of workgroups instead of 768 and then 256; the other tiles keep the
-// compiler's choice (forcing them spills).
-template <int TM, int TN, int TK>
-constexpr int kF32MinWaves = (TM == 128 && TN == 128 && TK == 16) ? 4 : 1;
-
-// FP32 kernel: v_mfma_f32_32x32x2f32, FP32 operands and accumulation.
+// FP32 kernel: v_mfma_f32_32x32x2f32, FP32 operands and accumulation.  The
+// register-staged loop remains for the products the DMA-fed one does not
+// take (f32_any_fits): an operand of 1 to 3 columns, or rows 2^22 floats or
+// more apart.
 template <int TM, int TN, int TK, int WM, int WN, bool AT, bool BT>
-__global__ void __launch_bounds__((TM / WM) * (TN / WN) * kWave)
-    __attribute__((amdgpu_waves_per_eu(kF32MinWaves<TM, TN, TK>))) sgemm_mfma_f32(GemmArgs p) {
+__global__ void __launch_bounds__((TM / WM) * (TN / WN) * kWave) sgemm_mfma_f32(GemmArgs p) {
   extern __shared__ __align__(16) float lds[];
   int tm, tn;
   tile_coords(p.tiles_m, p.tiles_n, blockIdx.x, tm, tn);
@@ -87,6 +82,40 @@ struct F32Config {
   }
 };
 
+// The DMA-fed loop for any size and alignment (mfma_f32_any.hpp): TK deep
+// sub-slabs, KW of them per slab, NST stages.  It replaced register-staged
+// loops of the same tiles, which loaded one slab ahead (and element by
+// element where an operand was not 16-byte aligned) and waited a memory
+// round trip for nearly every slab: 1000 x 1003 x 777, 64 x 64 tiles, 21.6 us
+// against 56; 512 x 4096 x 1024 38.5 against 47 (54 under a profiler).
+template <int TM, int TN, int TK, int WM, int WN, int NST, int KW>
+struct F32AnyConfig {
+  template <bool AT, bool BT>
+  using Shape = AnyShape<TM, TN, TK, WM, WN, AT, BT, NST, KW>;
+  static constexpr int kThreads = Shape<false, false>::kThreads;
+  static constexpr int64_t kLdsBytes = Shape<false, false>::kLdsBytes;
+  template <bool AT, bool BT, int MODE>
+  static hipError_t run(const GemmArgs& args, int splits, hipStream_t s) {
+    GemmArgs a = args;
+    a.tiles_m = (a.m + TM - 1) / TM;
+    a.tiles_n = (a.n + TN - 1) / TN;
+    F32DmaOut o{};
+    o.splits = splits;
+    void* kargs[] = {&a, &o};
+    auto* fn = &sgemm_f32_any<TM, TN, TK, WM, WN, AT, BT, NST, KW, MODE>;
+    hipError_t e = allow_lds(fn, (size_t)kLdsBytes);
+    if (e != hipSuccess) return e;
+    return hipLaunchKernel(reinterpret_cast<const void*>(fn), dim3((unsigned)(a.tiles_m * a.tiles_n * splits)),
+                           dim3(kThreads), kargs, (size_t)kLdsBytes, s);
+  }
+  static hipError_t launch(const GemmArgs& a, bool at, bool bt, hipStream_t s) {
+    if (at && bt) return hipErrorInvalidValue;
+    if (!f32_any_fits(a, at, bt)) return F32Config<64, 64, 16, 32, 32>::launch(a, at, bt, s);
+    return at   ? run<true, false, kDmaUpdate>(a, 1, s)
+           : bt ? run<false, true, kDmaUpdate>(a, 1, s)
+                : run<false, false, kDmaUpdate>(a, 1, s);
+  }
+};
 
 template <int TM, int TN, int TK, int WM, int WN, bool X3>
 struct Bf16Config {
@@ -110,15 +139,10 @@ struct Bf16Config {
   }
 };
 
-#define HPVM_F32_ENTRY(TM, TN, TK, WM, WN)                                               \
-  {{TM, TN, TK, WM, WN, 2}, HPVM_PREC_FP32, F32Config<TM, TN, TK, WM, WN>::kThreads,     \
-   F32Config<TM, TN, TK, WM, WN>::lds(false, false), &F32Config<TM, TN, TK, WM, WN>::launch}
+#define HPVM_F32_ENTRY(TM, TN, TK, WM, WN, SUB, NST, KW)                                                \
+  {{TM, TN, TK, WM, WN, 2}, HPVM_PREC_FP32, F32AnyConfig<TM, TN, SUB, WM, WN, NST, KW>::kThreads,       \
+   F32AnyConfig<TM, TN, SUB, WM, WN, NST, KW>::kLdsBytes, &F32AnyConfig<TM, TN, SUB, WM, WN, NST, KW>::launch}
 
-// FP32 problems of at least one tile each way with k a multiple of the
-// slab, n a multiple of 4, every row 16-byte aligned and no transposed
-// operand take the DMA-fed loop (mfma_f32_dma.hpp; edge tiles moved inward)
-// with 128-wide wave tiles; any other problem the general 128 x 128 x 16
-// tile.
 // C <- alpha * (slice 0 + ... + slice splits-1) + beta * C, the slices
 // summed in order, from partial sums [splits][m][n]; beta == 0 never reads
 // C.  Four adjacent outputs per lane (n, ldc multiples of 4, C 16-byte
@@ -154,13 +178,20 @@ hipError_t launch_split_finish(const float* part, int32_t splits, int64_t m, int
                          fargs, 0, s);
 }
 
+// FP32 problems of at least one tile each way with k a multiple of the
+// slab, n a multiple of 4, every row 16-byte aligned and no transposed
+// operand take the DMA-fed loop of mfma_f32_dma.hpp (edge tiles moved
+// inward) with 128-wide wave tiles; any other problem the loop for any size
+// with 64 x 128 tiles, the fastest there (4097 x 4099 x 2001: 535 us against
+// 545 for 64 x 64 tiles and 609 for the best larger one, 3001 x 2999 x 1001:
+// 159 against 155 and 169).
 template <int TM, int TN, int TK, int WM, int NST>
 struct F32DmaConfig {
   using S = F32DmaShape<TM, TN, TK, WM, 128, false, false, NST>;
   static constexpr int kThreads = S::NW * kWave;
   static hipError_t launch(const GemmArgs& args, bool at, bool bt, hipStream_t s) {
     if (at || bt || !f32_dma_fits_edges<TM, TN, TK>(args, args.C, args.ldc))
-      return F32Config<128, 128, 16, 64, 64>::launch(args, at, bt, s);
+      return F32AnyConfig<64, 128, 32, 32, 64, 2, 1>::launch(args, at, bt, s);
     GemmArgs a = args;
     a.tiles_m = (a.m + TM - 1) / TM;
     a.tiles_n = (a.n + TN - 1) / TN;
@@ -230,16 +261,17 @@ struct F32DmaConfig {
    &F32DmaConfig<TM, TN, TK, WM, NST>::split_bytes,                                               \
    &F32DmaConfig<TM, TN, TK, WM, NST>::launch_split}
 
-// Entry 0 is the default: DMA-fed for whole-tile problems, otherwise the
-// 128 x 128 x 16 tile.
+// Entry 0 is the default for large problems.  The stages of the entries on
+// the loop for any size: two of 32-deep slabs, or four of 16-deep ones
+// (alike in time: 64 x 64 tiles, 1000 x 1003 x 777, 21.9 and 22.4 us).
 static const MfmaEntry kF32Menu[] = {
     HPVM_F32_DMA_ENTRY(256, 256, 32, 64, 2),
-    HPVM_F32_ENTRY(128, 128, 16, 64, 64),
-    HPVM_F32_ENTRY(256, 128, 16, 128, 64),
-    HPVM_F32_ENTRY(128, 128, 32, 64, 64),
-    HPVM_F32_ENTRY(64, 64, 16, 32, 32),
-    HPVM_F32_ENTRY(128, 64, 16, 64, 32),
-    HPVM_F32_ENTRY(64, 128, 16, 32, 64),
+    HPVM_F32_ENTRY(128, 128, 16, 64, 64, 16, 4, 1),
+    HPVM_F32_ENTRY(256, 128, 16, 128, 64, 16, 3, 1),
+    HPVM_F32_ENTRY(128, 128, 32, 64, 64, 32, 2, 1),
+    HPVM_F32_ENTRY(64, 64, 16, 32, 32, 16, 4, 1),
+    HPVM_F32_ENTRY(128, 64, 16, 64, 32, 16, 4, 1),
+    HPVM_F32_ENTRY(64, 128, 16, 32, 64, 16, 4, 1),
     HPVM_F32_DMA_ENTRY(256, 256, 16, 64, 4),
     HPVM_F32_DMA_ENTRY(128, 256, 32, 32, 2),
     HPVM_F32_DMA_ENTRY(128, 128, 32, 32, 2),

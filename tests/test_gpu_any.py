@@ -1,0 +1,40 @@
+"""The DMA-fed FP32 loop for any size and alignment, at the sizes where it can
+go wrong: integer inputs, so every sum is exact in any order and the result
+must equal the oracle's bit for bit; rows are padded with NaN, which a value
+taken from outside a matrix would spread."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_util import to_dev, to_host
+from paper_1611_00860_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+# Columns: one 16-byte unit, a partial one, a tile and one more or less of
+# it; depths: inside a slab, whole slabs, one over, one short.
+SIZES = [(1, 4, 1), (3, 5, 31), (4, 3, 33), (33, 31, 96), (63, 66, 100), (65, 127, 64), (127, 65, 257), (130, 129, 95),
+         (257, 259, 130), (5, 300, 511)]
+
+
+def run(hp, A, B, C, alpha, beta, tile, pad, misalign):
+    import torch
+
+    dA, dB, dC = (to_dev(x, pad, misalign) for x in (A, B, C))
+    hp.sgemm(dA, dB, dC, alpha, beta, tile=tile)
+    torch.cuda.synchronize()
+    return to_host(dC)
+
+
+@pytest.mark.parametrize("m,n,k", SIZES)
+@pytest.mark.parametrize("pad,misalign", [(0, False), (3, True)])
+def test_any_size_integers(gpu, m, n, k, pad, misalign):
+    A, B, C = inputs.sgemm_operands(m, n, k, seed=m + n + k, dist="int")
+    ref = oracle.sgemm(A, B, C, 1.0, -2.0)
+    for tile in [None] + [t for t in gpu.tile_menu("fp32") if t[4] != 128]:
+        print(f"case: {m}x{n}x{k} pad {pad} misalign {misalign} tile {tile}", flush=True)
+        got = run(gpu, A, B, C, 1.0, -2.0, tile, pad, misalign)
+        assert np.array_equal(got, ref), tile
+    nan_c = np.full_like(C, np.nan)
+    got = run(gpu, A, B, nan_c, 1.0, 0.0, None, pad, misalign)
+    assert np.array_equal(got, oracle.sgemm(A, B, None, 1.0, 0.0))
