@@ -199,10 +199,11 @@ typedef struct hpvm_edge {
  *   prec         : hpvm_precision.
  *   tile         : hierarchy shape, or NULL to take the autotuned choice for
  *                  this shape class (until hpvm_autotune has run, the
- *                  built-in default: the menu's entry 0 when it gives at
- *                  least 256 tiles; else the DMA-fed 128 x 128 x 32 tile
- *                  if that does, else FP32 64 x 64 x 16, BF16 and bf16x3
- *                  64 x 64 x 32).  Must be
+ *                  built-in default: FP32 the tile with the least
+ *                  estimated time; BF16 and bf16x3 the menu's entry 0 when
+ *                  it gives at least 256 tiles, else the DMA-fed
+ *                  128 x 128 x 32 tile if that does, else 64 x 64 x 32).
+ *                  Must be
  *                  in hpvm_tile_menu for prec and not need a workspace
  *                  (stages != 3).
  *   stream       : hipStream_t or NULL.
@@ -225,7 +226,8 @@ int hpvm_sgemm(int64_t m, int64_t n, int64_t k, float alpha, const float* A,
  * when tiles * s reaches 256), each writing an m x n partial sum to
  * `workspace`, then one launch forming C <- alpha * (sum of the partials,
  * in slice order) + beta * C.  Results then differ from the single launch
- * by rounding only.
+ * by rounding only.  FP32's 32 x 32 x 128 tile splits products of any sizes
+ * with k >= 2048 the same way (without the last condition).
  * workspace: device memory, 16-byte aligned, at least
  * hpvm_sgemm_workspace_bytes(m, n, k, prec, tile) bytes (may be NULL when
  * that is 0); its contents are scratch.  For a split tile it is
@@ -234,7 +236,8 @@ int hpvm_sgemm(int64_t m, int64_t n, int64_t k, float alpha, const float* A,
  * even 128 x 128 tiles would not cover 256 CUs with (BF16 and bf16x3: with
  * k >= 2048) take the DMA-fed tile with the fewest slices (the first in
  * menu order on a tie) when the workspace holds the partial sums; other
- * BF16 products of at least 2^31 multiply-adds (m n k) take the first
+ * FP32 products the tile with the least estimated time, the 32 x 32 x 128
+ * tile's split included; other BF16 products of at least 2^31 multiply-adds (m n k) take the first
  * staged tile, or 128 x 128 x 64 with 64 x 32 leaves when the first would
  * give fewer than 256 tiles (bf16x3 only when the DMA-fed 256 x 256 tile
  * would not cover the CUs or does not suit k and n), and others

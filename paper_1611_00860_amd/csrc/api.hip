@@ -156,18 +156,6 @@ int resolve(int32_t prec, const hpvm_tile* tile, const hpvm::MfmaEntry** entry, 
   return HPVM_OK;
 }
 
-// Built-in choice for tile == NULL when the autotuner has no entry and no
-// workspace lowering applies, for problems the menu's entry 0 would leave
-// CUs idle on.  FP32: entry 0 (256 x 256 DMA-fed tiles) when it gives at
-// least 256 tiles (one per CU of a 256-CU part), else the DMA-fed
-// 128 x 128 x 32 tile when that does (2048^3: 0.128 ms against 0.166 for the
-// best register-staged tile and 0.457 for 64 tiles of 256 x 256), else the
-// 64 x 64 x 16 tile (at 1024 x 1024 x 4096, 64 tiles of 128 x 128 ran at 28
-// TFLOP/s and 256 of 64 x 64 at 75).  BF16 and bf16x3: entry 0 (the
-// DMA-fed 256 x 256 tile) when it gives at least 256 tiles, else the
-// DMA-fed 128 x 128 tile when that does, else the register-staged
-// 64 x 64 x 32 tile (1024^3 BF16: 0.020 ms against 0.064 for 256 x 256).
-// Returns false for entry 0.
 int64_t tiles_of(const hpvm_tile& t, int64_t m, int64_t n) {
   return ((m + t.tile_m - 1) / t.tile_m) * ((n + t.tile_n - 1) / t.tile_n);
 }
@@ -177,16 +165,14 @@ const hpvm::MfmaEntry* f32_mid_entry() {
 }  // namespace
 
 namespace hpvm {
+// Built-in BF16 / bf16x3 choice for tile == NULL when the autotuner has no
+// entry and no workspace lowering applies: false for the menu's entry 0 (the
+// DMA-fed 256 x 256 tile) when it gives at least 256 tiles (one per CU of a
+// 256-CU part), else the DMA-fed 128 x 128 tile when that does, else the
+// 64 x 64 x 32 tile (1024^3 BF16: 0.020 ms against 0.064 for 256 x 256).
 bool default_small_tile(int32_t prec, int64_t m, int64_t n, hpvm_tile* out) {
   const hpvm::MfmaEntry* e0 = hpvm::menu_entry_at(prec, 0);
   if (!e0) return false;
-  if (prec == HPVM_PREC_FP32) {
-    const hpvm::MfmaEntry* mid = f32_mid_entry();
-    const hpvm::MfmaEntry* small = hpvm::find_menu_entry(prec, hpvm_tile{64, 64, 16, 32, 32, 2});
-    if (!mid || !small || tiles_of(e0->tile, m, n) >= 256) return false;
-    *out = tiles_of(mid->tile, m, n) >= 256 ? mid->tile : small->tile;
-    return true;
-  }
   // BF16 / bf16x3: the DMA-fed 128 x 128 tile when it covers the CUs
   // (2048^3 BF16: 0.055 ms against 0.084 for 64 tiles of 256 x 256), else
   // the register-staged 64 x 64 x 32 tile.
@@ -196,17 +182,63 @@ bool default_small_tile(int32_t prec, int64_t m, int64_t n, hpvm_tile* out) {
   *out = tiles_of(mid->tile, m, n) >= 256 ? mid->tile : small->tile;
   return true;
 }
+// The FP32 tile with the least estimated time (microseconds): `start` (launch,
+// the ring's first fill, epilogue) plus, for the most tiles (of every slice)
+// that one of 256 CUs gets, the time their products take at the FP32 MFMA
+// rate (614 GFLOP/s a CU) times `load`.  Both fitted to timings of each tile
+// over 12 products from 512^3 to 4097 x 4099 x 2001; estimated and measured:
+//   256 x 256: 4096^3 929, 932       128 x 128: 2048^3 128, 128
+//   64 x 128: 2048^3 130, 122; 4097 x 4099 x 2001 546, 535;
+//             512 x 4096 x 1024 38.6, 38.0
+//   64 x 64 in two k groups: 1024^3 22.2, 22.8; 1000 x 1003 x 777 18.4, 19.7
+//   32 x 32 in four: 512^3 8.5, 7.6; 256 x 256 x 8192 46, 47;
+//             100 x 3000 x 1500 20.5, 19.5
+// A split contraction adds the summing launch and the partial sums' traffic.
+bool f32_default_tile(int64_t m, int64_t n, int64_t k, int64_t split_ws, hpvm_tile* out) {
+  struct Candidate {
+    hpvm_tile tile;
+    double start, load;
+    bool aligned;  // only where its own loop runs (mfma_f32_dma.hpp)
+  };
+  static const Candidate kCandidates[] = {
+      {{256, 256, 32, 64, 128, 2}, 12.0, 1.05, true}, {{128, 128, 32, 32, 128, 2}, 10.0, 1.08, true},
+      {{64, 128, 32, 32, 64, 2}, 8.0, 1.12, false},   {{64, 64, 32, 16, 32, 2}, 6.5, 1.15, false},
+      {{32, 32, 128, 8, 32, 2}, 6.0, 1.45, false},
+  };
+  double best = 0.0;
+  bool found = false;
+  for (const Candidate& c : kCandidates) {
+    const hpvm_tile& t = c.tile;
+    if (c.aligned && (m < t.tile_m || n < t.tile_n || n % 4 || k % t.tile_k)) continue;
+    const MfmaEntry* e = find_menu_entry(HPVM_PREC_FP32, t);
+    if (!e) continue;
+    int64_t slices = 1;
+    const int64_t bytes = c.aligned ? 0 : entry_split_bytes(e, m, n, k);
+    if (bytes > 0 && (split_ws < 0 || split_ws >= bytes)) slices = bytes / (m * n * (int64_t)sizeof(float));
+    const double per_tile = 2.0 * t.tile_m * t.tile_n * ((double)k / slices) / 614400.0;
+    const double rounds = (double)((tiles_of(t, m, n) * slices + 255) / 256);
+    double time = c.start + rounds * per_tile * c.load;
+    if (slices > 1) time += 4.5 + (double)(bytes + m * n * 4) / 4.0e6;
+    if (!found || time < best) {
+      best = time;
+      *out = t;
+      found = true;
+    }
+  }
+  return found;
+}
 }  // namespace hpvm
 
 namespace {
 
-// The DMA-fed entry whose split contraction needs the fewest partial sums
+// The DMA-fed whole-tile entry whose split contraction needs the fewest partial sums
 // (the deepest slices; the first in menu order on a tie), or null.
 const hpvm::MfmaEntry* fewest_slices(int32_t prec, int64_t m, int64_t n, int64_t k, int64_t* bytes) {
   const hpvm::MfmaEntry* best = nullptr;
   int64_t best_bytes = 0;
   for (int i = 0; i < hpvm::menu_size(prec); ++i) {
     const hpvm::MfmaEntry* e = hpvm::menu_entry_at(prec, i);
+    if (e->tile.tile_m < 128) continue;
     const int64_t b = hpvm::entry_split_bytes(e, m, n, k);
     if (b > 0 && (!best || b < best_bytes)) {
       best = e;
@@ -228,8 +260,9 @@ const hpvm::MfmaEntry* fewest_slices(int32_t prec, int64_t m, int64_t n, int64_t
 // whose conversion pass is then a small share of the time (or, when that
 // gives fewer than 256 tiles, the 128 x 128 x 64 tile with 64 x 32 leaves);
 // bf16x3 products the same only when 256 x 256 tiles would not cover the
-// CUs (or k or n does not suit the DMA-fed tile).  Returns false when
-// neither applies (hpvm_sgemm's choice then): a split tile run as one
+// CUs (or k or n does not suit the DMA-fed tile); other FP32 products the
+// tile with the least estimated time (f32_default_tile).  Returns false when
+// none applies (hpvm_sgemm's choice then): a split tile run as one
 // launch would be the slowest choice there is (64 tiles of 128 x 128 at
 // 1024 x 1024 x 4096 FP32: 28 TFLOP/s against 75 for hpvm_sgemm's 64 x 64
 // tiles).
@@ -247,6 +280,7 @@ bool default_ws_tile(int32_t prec, int64_t m, int64_t n, int64_t k, int64_t ws_b
       return true;
     }
   }
+  if (prec == HPVM_PREC_FP32) return hpvm::f32_default_tile(m, n, k, ws_bytes, out);
   if (prec != HPVM_PREC_BF16 && prec != HPVM_PREC_BF16X3) return false;
   if ((double)m * (double)n * (double)k < 2147483648.0 || !hpvm::staged_k_ok(k)) return false;
   const hpvm::MfmaEntry* staged = nullptr;
@@ -289,6 +323,7 @@ bool choose_tile(int32_t prec, int64_t m, int64_t n, int64_t k, bool ws_ok, int6
     return hpvm::tuned_tile(prec, m, n, k, false, out) != 0;
   }
   if (ws_ok && default_ws_tile(prec, m, n, k, ws_bytes, out)) return true;
+  if (prec == HPVM_PREC_FP32) return hpvm::f32_default_tile(m, n, k, 0, out);
   return hpvm::default_small_tile(prec, m, n, out);
 }
 

@@ -80,8 +80,7 @@ inline int dma_split_count(int64_t tiles, int64_t k, int tk) {
 }
 
 // C <- alpha * (part[0] + ... + part[splits-1]) + beta * C, the slices
-// summed in order, from partial sums [splits][m][n] (n, ldc multiples of 4,
-// part and C 16-byte aligned); beta == 0 never reads C.
+// summed in order, from partial sums [splits][m][n]; beta == 0 never reads C.
 hipError_t launch_split_finish(const float* part, int32_t splits, int64_t m, int64_t n, float alpha, float beta,
                                float* C, int64_t ldc, hipStream_t s);
 
@@ -149,6 +148,11 @@ const MfmaEntry* find_menu_entry(int32_t prec, const hpvm_tile& tile);
 // Built-in tile for tile == NULL (no autotuned entry, no workspace) when the
 // menu's entry 0 would give fewer than 256 tiles; false otherwise.
 bool default_small_tile(int32_t prec, int64_t m, int64_t n, hpvm_tile* out);
+
+// Built-in FP32 tile of the calls that choose among the whole menu
+// (hpvm_sgemm_ws, the consumer): the one with the least estimated time.
+// split_ws: workspace bytes that a split contraction may use (-1: any).
+bool f32_default_tile(int64_t m, int64_t n, int64_t k, int64_t split_ws, hpvm_tile* out);
 
 // Workspace bytes an entry needs for m x n x k (0 for fused entries).
 int64_t entry_workspace_bytes(const MfmaEntry* e, int64_t m, int64_t n, int64_t k);

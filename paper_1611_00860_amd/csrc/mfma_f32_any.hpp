@@ -177,7 +177,7 @@ __device__ __forceinline__ void wait_slabs_barrier(int slabs) {
 // Outputs of the accumulators' row quads [q0, q1) (quad g of block a: the
 // rows acc_row(4 g .. 4 g + 3)).  m_own, n_own: the tile's place in the
 // tile grid; only rows in [m_own, m) and columns in [n_own, n) are stored.
-template <typename OA, typename OB, bool BT, int MODE, int OP, int NA, int NB>
+template <typename OA, typename OB, bool BT, int MODE, int NA, int NB>
 __device__ __forceinline__ void any_epilogue(const GemmArgs& q, const F32DmaOut& o, const f32x16 (&acc)[NA][NB],
                                              int m0, int n0, int m_own, int n_own, bool whole, int wm0, int wn0,
                                              int lane, int z, int q0, int q1) {
@@ -187,7 +187,6 @@ __device__ __forceinline__ void any_epilogue(const GemmArgs& q, const F32DmaOut&
   const int64_t ldo = MODE == kDmaConsume ? o.ldd : q.ldc;
   const float alpha = MODE == kDmaSplit ? 1.0f : q.alpha;
   const bool read_c = MODE != kDmaSplit && q.beta != 0.0f;
-  constexpr bool kBias = MODE == kDmaConsume && (OP == HPVM_CONSUMER_BIAS || OP == HPVM_CONSUMER_BIAS_RELU);
   constexpr int V = BT ? 1 : NB;  // adjacent outputs a lane holds
   using Vec = typename LooseF<V>::type;
   const int I = lane & 31;
@@ -203,9 +202,11 @@ __device__ __forceinline__ void any_epilogue(const GemmArgs& q, const F32DmaOut&
   for (int b0 = 0; b0 < NB; b0 += V) {
     const int col = n0 + OB::index(b0, I, wn0);
     Vec bias{};
-    if constexpr (kBias) {
+    if constexpr (MODE == kDmaConsume) {
+      if (o.op == HPVM_CONSUMER_BIAS || o.op == HPVM_CONSUMER_BIAS_RELU) {
 #pragma unroll
-      for (int e = 0; e < V; ++e) put(bias, e, col + e < q.n ? o.bias[col + e] : 0.0f);
+        for (int e = 0; e < V; ++e) put(bias, e, col + e < q.n ? o.bias[col + e] : 0.0f);
+      }
     }
 #pragma unroll
     for (int a = 0; a < NA; ++a)
@@ -235,7 +236,7 @@ __device__ __forceinline__ void any_epilogue(const GemmArgs& q, const F32DmaOut&
           for (int e = 0; e < V; ++e) {
             float x = alpha * acc[a][b0 + e][4 * g + u];
             if (read_c) x = fmaf(q.beta, at(c[u], e), x);
-            if constexpr (MODE == kDmaConsume) x = consume<OP>(x, at(bias, e), o.lo, o.hi);
+            if constexpr (MODE == kDmaConsume) x = consume_op(o.op, x, at(bias, e), o.lo, o.hi);
             put(v, e, x);
           }
           float* p = out + (int64_t)row[u] * ldo + col;
@@ -431,7 +432,7 @@ __device__ __forceinline__ void f32_any_tile(const GemmArgs& p, int splits, int 
 
 // One launch: a workgroup per tile and contraction slice (slice-major),
 // XCD-aware tile order.
-template <int TM, int TN, int TK, int WM, int WN, bool AT, bool BT, int NST, int KW, int MODE, int OP = 0>
+template <int TM, int TN, int TK, int WM, int WN, bool AT, bool BT, int NST, int KW, int MODE>
 __global__ void __launch_bounds__((AnyShape<TM, TN, TK, WM, WN, AT, BT, NST, KW>::kThreads))
     sgemm_f32_any(GemmArgs p, F32DmaOut o) {
   extern __shared__ __align__(16) char smem[];
@@ -444,8 +445,8 @@ __global__ void __launch_bounds__((AnyShape<TM, TN, TK, WM, WN, AT, BT, NST, KW>
       p, o.splits, tm, tn, z, smem,
       [&](const auto& acc, int m0, int n0, int m_own, int n_own, bool whole, int wm0, int wn0, int lane, int q0,
           int q1) {
-        any_epilogue<typename S::OA, typename S::OB, BT, MODE, OP>(p, o, acc, m0, n0, m_own, n_own, whole, wm0, wn0,
-                                                                   lane, z, q0, q1);
+        any_epilogue<typename S::OA, typename S::OB, BT, MODE>(p, o, acc, m0, n0, m_own, n_own, whole, wm0, wn0, lane,
+                                                               z, q0, q1);
       });
 }
 

@@ -134,6 +134,17 @@ __device__ __forceinline__ float consume(float v, float b, float lo, float hi) {
   return v;
 }
 
+// The same with the op known at run time only.
+__device__ __forceinline__ float consume_op(int op, float v, float b, float lo, float hi) {
+  switch (op) {
+    case HPVM_CONSUMER_RELU: return consume<HPVM_CONSUMER_RELU>(v, b, lo, hi);
+    case HPVM_CONSUMER_BIAS: return consume<HPVM_CONSUMER_BIAS>(v, b, lo, hi);
+    case HPVM_CONSUMER_BIAS_RELU: return consume<HPVM_CONSUMER_BIAS_RELU>(v, b, lo, hi);
+    case HPVM_CONSUMER_CLAMP: return consume<HPVM_CONSUMER_CLAMP>(v, b, lo, hi);
+    default: return v;
+  }
+}
+
 // Where the DMA-fed loop's results go.
 enum F32DmaMode {
   kDmaUpdate = 0,   // C <- alpha acc + beta C (beta == 0 never reads C)
@@ -142,7 +153,7 @@ enum F32DmaMode {
 };
 struct F32DmaOut {
   int32_t splits;     // contraction slices (kDmaSplit), else 1
-  int32_t reserved;
+  int32_t op;         // kDmaConsume on the loop for any size: the consumer
   float* D;           // kDmaConsume: output and its leading dimension
   int64_t ldd;
   const float* bias;  // one value per column (BIAS ops)

@@ -27,6 +27,7 @@
 #include "hpvm_sgemm.h"
 #include "internal.hpp"
 #include "mfma_f32.hpp"
+#include "mfma_f32_any.hpp"
 #include "mfma_f32_dma.hpp"
 
 namespace hpvm {
@@ -270,9 +271,37 @@ struct PairConfig {
   }
 };
 
+// The consumer on the DMA-fed loop for any size (512 x 4096 x 1024, bias +
+// relu, 64 x 64 tiles: 38 us against 47 on the register-staged loop, which
+// remains for k = 0, alpha = 0 and what f32_any_fits leaves out).
+template <int TM, int TN, int TK, int WM, int WN, int NST, int KW>
+struct ConsumerAnyConfig {
+  using S = AnyShape<TM, TN, TK, WM, WN, false, false, NST, KW>;
+  static hipError_t launch(const GemmArgs& args, const ConsumerArgs& c, hipStream_t s) {
+    if (!f32_any_fits(args, false, false)) return ConsumerConfig<64, 64, 16, 32, 32>::launch(args, c, s);
+    GemmArgs a = args;
+    a.tiles_m = (a.m + TM - 1) / TM;
+    a.tiles_n = (a.n + TN - 1) / TN;
+    F32DmaOut o{};
+    o.splits = 1;
+    o.op = c.op;
+    o.D = c.D;
+    o.ldd = c.ldd;
+    o.bias = c.bias;
+    o.lo = c.lo;
+    o.hi = c.hi;
+    auto* fn = &sgemm_f32_any<TM, TN, TK, WM, WN, false, false, NST, KW, kDmaConsume>;
+    hipError_t e = allow_lds_fused(fn, (size_t)S::kLdsBytes);
+    if (e != hipSuccess) return e;
+    void* kargs[] = {&a, &o};
+    return hipLaunchKernel(reinterpret_cast<const void*>(fn), dim3((unsigned)(a.tiles_m * a.tiles_n)),
+                           dim3(S::kThreads), kargs, (size_t)S::kLdsBytes, s);
+  }
+};
+
 // Aligned problems of at least one tile each way (edge tiles moved inward)
 // of the consumer on the DMA-fed loop (the consumer applied in its
-// epilogue); any other problem on the 128 x 128 x 16 tile.
+// epilogue); any other problem on 64 x 128 tiles of the loop for any size.
 template <int TM, int TN, int TK, int WM, int NST>
 struct ConsumerDmaConfig {
   using S = F32DmaShape<TM, TN, TK, WM, 128, false, false, NST>;
@@ -293,7 +322,7 @@ struct ConsumerDmaConfig {
   static hipError_t launch(const GemmArgs& args, const ConsumerArgs& c, hipStream_t s) {
     const bool c_ok = args.beta == 0.0f || (args.ldc % 4 == 0 && (reinterpret_cast<uintptr_t>(args.C) & 15) == 0);
     if (!c_ok || !f32_dma_fits_edges<TM, TN, TK>(args, c.D, c.ldd))
-      return ConsumerConfig<128, 128, 16, 64, 64>::launch(args, c, s);
+      return ConsumerAnyConfig<64, 128, 32, 32, 64, 2, 1>::launch(args, c, s);
     GemmArgs a = args;
     a.tiles_m = (a.m + TM - 1) / TM;
     a.tiles_n = (a.n + TN - 1) / TN;
@@ -388,9 +417,10 @@ struct PairDmaConfig {
   {{TM, TN, TK, WM, 128, NST}, PairDmaConfig<TM, TN, TK, WM, NST>::kThreads,                           \
    PairDmaConfig<TM, TN, TK, WM, NST>::S::kLdsBytes, nullptr, &PairDmaConfig<TM, TN, TK, WM, NST>::launch, \
    &PairDmaConfig<TM, TN, TK, WM, NST>::split_bytes, &PairDmaConfig<TM, TN, TK, WM, NST>::launch_split}
-#define HPVM_CONSUMER_ENTRY(TM, TN, TK, WM, WN)                                                   \
-  {{TM, TN, TK, WM, WN, 2}, ConsumerConfig<TM, TN, TK, WM, WN>::kThreads,                           \
-   ConsumerConfig<TM, TN, TK, WM, WN>::kLds, &ConsumerConfig<TM, TN, TK, WM, WN>::launch, nullptr}
+#define HPVM_CONSUMER_ENTRY(TM, TN, TK, WM, WN, SUB, NST, KW)                                        \
+  {{TM, TN, TK, WM / KW, WN, 2}, ConsumerAnyConfig<TM, TN, SUB, WM, WN, NST, KW>::S::kThreads,             \
+   ConsumerAnyConfig<TM, TN, SUB, WM, WN, NST, KW>::S::kLdsBytes,                                     \
+   &ConsumerAnyConfig<TM, TN, SUB, WM, WN, NST, KW>::launch, nullptr}
 #define HPVM_PAIR_ENTRY(TM, TN, TK, WM, WN)                                                       \
   {{TM, TN, TK, WM, WN, 2}, PairConfig<TM, TN, TK, WM, WN>::kThreads, PairConfig<TM, TN, TK, WM, WN>::kLds, \
    nullptr, &PairConfig<TM, TN, TK, WM, WN>::launch}
@@ -399,12 +429,18 @@ struct PairDmaConfig {
 // order, so the autotuner's choice for a shape carries over.
 static const FusedEntry kConsumerMenu[] = {
     HPVM_CONSUMER_DMA_ENTRY(256, 256, 32, 64, 2),
-    HPVM_CONSUMER_ENTRY(128, 128, 16, 64, 64), HPVM_CONSUMER_ENTRY(256, 128, 16, 128, 64),
-    HPVM_CONSUMER_ENTRY(128, 128, 32, 64, 64), HPVM_CONSUMER_ENTRY(64, 64, 16, 32, 32),
-    HPVM_CONSUMER_ENTRY(128, 64, 16, 64, 32), HPVM_CONSUMER_ENTRY(64, 128, 16, 32, 64),
+    HPVM_CONSUMER_ENTRY(128, 128, 16, 64, 64, 16, 4, 1),
+    HPVM_CONSUMER_ENTRY(256, 128, 16, 128, 64, 16, 3, 1),
+    HPVM_CONSUMER_ENTRY(128, 128, 32, 64, 64, 32, 2, 1),
+    HPVM_CONSUMER_ENTRY(64, 64, 16, 32, 32, 16, 6, 1),
+    HPVM_CONSUMER_ENTRY(128, 64, 16, 64, 32, 16, 4, 1),
+    HPVM_CONSUMER_ENTRY(64, 128, 16, 32, 64, 16, 4, 1),
     HPVM_CONSUMER_DMA_ENTRY(256, 256, 16, 64, 4),
     HPVM_CONSUMER_DMA_ENTRY(128, 256, 32, 32, 2),
     HPVM_CONSUMER_DMA_ENTRY(128, 128, 32, 32, 2),
+    HPVM_CONSUMER_ENTRY(64, 128, 32, 32, 64, 32, 2, 1),
+    HPVM_CONSUMER_ENTRY(64, 64, 32, 32, 32, 16, 3, 2),
+    HPVM_CONSUMER_ENTRY(32, 32, 128, 32, 32, 32, 2, 4),
 };
 // Pair tiles: tile_m x tile_n of each output; 8, 8, 4 and 8 waves.  The
 // first DMA-fed entry's two stages of one A slab and two B slabs take all
@@ -493,8 +529,8 @@ int hpvm_sgemm_consumer(int64_t m, int64_t n, int64_t k, float alpha, const floa
     hpvm_tile tuned;
     if (tuned_tile(HPVM_PREC_FP32, m, n, k, false, &tuned) && find_fused(kConsumerMenu, kNumConsumer, tuned))
       t = tuned;
-    else if (default_small_tile(HPVM_PREC_FP32, m, n, &tuned))
-      t = tuned;  // the single launch's choice for problems entry 0 leaves CUs idle on
+    else if (f32_default_tile(m, n, k, 0, &tuned))
+      t = tuned;  // the single launch's choice
   }
   const FusedEntry* e = find_fused(kConsumerMenu, kNumConsumer, t);
   if (!e)

@@ -115,6 +115,35 @@ struct F32AnyConfig {
            : bt ? run<false, true, kDmaUpdate>(a, 1, s)
                 : run<false, false, kDmaUpdate>(a, 1, s);
   }
+  // Contraction slices of a product whose tiles would not cover 256 CUs
+  // (any sizes): doubled while they would not, each at least 256 deep, at
+  // most 16; from k = 2048 on, where the shorter slices save more than the
+  // summing launch costs, about 5 us (16 x 4096 x 4096: 128 tiles of
+  // 32 x 32, 27 us whole, 16 in two slices; 64 x 64 x 4096: 4 tiles, 25 us
+  // whole, 7 in 16 slices).
+  static int splits(int64_t m, int64_t n, int64_t k) {
+    if (m <= 0 || n < 4 || k < 2048) return 1;
+    const int64_t tiles = ((m + TM - 1) / TM) * ((n + TN - 1) / TN);
+    int sp = 1;
+    while (sp < 16 && tiles * sp < 256 && k / (2 * sp) >= 256) sp *= 2;
+    return sp;
+  }
+  static int64_t split_bytes(int64_t m, int64_t n, int64_t k) {
+    const int sp = splits(m, n, k);
+    return sp > 1 ? (int64_t)sp * m * n * (int64_t)sizeof(float) : 0;
+  }
+  static hipError_t launch_split(const GemmArgs& args, void* workspace, hipStream_t s) {
+    const int sp = splits(args.m, args.n, args.k);
+    if (sp <= 1 || !f32_any_fits(args, false, false)) return launch(args, false, false, s);
+    float* part = static_cast<float*>(workspace);
+    GemmArgs a = args;
+    a.C = part;
+    a.ldc = a.n;
+    a.beta = 0.0f;
+    hipError_t e = run<false, false, kDmaSplit>(a, sp, s);
+    if (e != hipSuccess) return e;
+    return launch_split_finish(part, sp, args.m, args.n, args.alpha, args.beta, args.C, args.ldc, s);
+  }
 };
 
 template <int TM, int TN, int TK, int WM, int WN, bool X3>
@@ -139,39 +168,52 @@ struct Bf16Config {
   }
 };
 
+// Tiles of KW k groups (TK = KW sub-slabs of SUB): a wave computes a WM x WN
+// block of its group and, after the groups' sum, owns WM / KW of its rows.
 #define HPVM_F32_ENTRY(TM, TN, TK, WM, WN, SUB, NST, KW)                                                \
-  {{TM, TN, TK, WM, WN, 2}, HPVM_PREC_FP32, F32AnyConfig<TM, TN, SUB, WM, WN, NST, KW>::kThreads,       \
+  {{TM, TN, TK, WM / KW, WN, 2}, HPVM_PREC_FP32, F32AnyConfig<TM, TN, SUB, WM, WN, NST, KW>::kThreads,       \
    F32AnyConfig<TM, TN, SUB, WM, WN, NST, KW>::kLdsBytes, &F32AnyConfig<TM, TN, SUB, WM, WN, NST, KW>::launch}
 
 // C <- alpha * (slice 0 + ... + slice splits-1) + beta * C, the slices
 // summed in order, from partial sums [splits][m][n]; beta == 0 never reads
-// C.  Four adjacent outputs per lane (n, ldc multiples of 4, C 16-byte
-// aligned).
+// C.  A lane takes four adjacent outputs of a row (fewer at its end); rows
+// may start at any float.
 constexpr int kSplitThreads = 256;
 __global__ void __launch_bounds__(kSplitThreads)
     sgemm_split_finish(const float* __restrict__ part, int32_t splits, int64_t m, int64_t n, float alpha,
                        float beta, float* __restrict__ C, int64_t ldc) {
-  const int64_t c4 = n / 4, units = m * c4, plane = m * n;
+  using Vec = LooseF<4>::type;
+  const int64_t c4 = (n + 3) / 4, units = m * c4, plane = m * n;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < units; u += stride) {
     const int64_t i = u / c4, j = (u - i * c4) * 4;
-    f32x4 v = *reinterpret_cast<const f32x4*>(part + i * n + j);
-    for (int z = 1; z < splits; ++z) v += *reinterpret_cast<const f32x4*>(part + z * plane + i * n + j);
-    f32x4* c = reinterpret_cast<f32x4*>(C + i * ldc + j);
-    if (beta != 0.0f) {
-      const f32x4 old = *c;
+    const float* p = part + i * n + j;
+    float* c = C + i * ldc + j;
+    if (j + 4 <= n) {
+      Vec v = *reinterpret_cast<const Vec*>(p);
+      for (int z = 1; z < splits; ++z) v += *reinterpret_cast<const Vec*>(p + z * plane);
+      if (beta != 0.0f) {
+        const Vec old = *reinterpret_cast<const Vec*>(c);
 #pragma unroll
-      for (int t = 0; t < 4; ++t) v[t] = fmaf(beta, old[t], alpha * v[t]);
+        for (int t = 0; t < 4; ++t) v[t] = fmaf(beta, old[t], alpha * v[t]);
+      } else {
+        v = alpha * v;
+      }
+      *reinterpret_cast<Vec*>(c) = v;
     } else {
-      v = alpha * v;
+      for (int t = 0; j + t < n; ++t) {
+        float v = p[t];
+        for (int z = 1; z < splits; ++z) v += p[z * plane + t];
+        v *= alpha;
+        c[t] = beta != 0.0f ? fmaf(beta, c[t], v) : v;
+      }
     }
-    *c = v;
   }
 }
 
 hipError_t launch_split_finish(const float* part, int32_t splits, int64_t m, int64_t n, float alpha, float beta,
                                float* C, int64_t ldc, hipStream_t s) {
-  const int64_t units = m * n / 4;
+  const int64_t units = m * ((n + 3) / 4);
   const unsigned blocks = (unsigned)std::min<int64_t>(2048, (units + kSplitThreads - 1) / kSplitThreads);
   void* fargs[] = {&part, &splits, &m, &n, &alpha, &beta, &C, &ldc};
   return hipLaunchKernel(reinterpret_cast<const void*>(&sgemm_split_finish), dim3(blocks), dim3(kSplitThreads),
@@ -261,20 +303,30 @@ struct F32DmaConfig {
    &F32DmaConfig<TM, TN, TK, WM, NST>::split_bytes,                                               \
    &F32DmaConfig<TM, TN, TK, WM, NST>::launch_split}
 
+#define HPVM_F32_SPLIT_ENTRY(TM, TN, TK, WM, WN, SUB, NST, KW)                                          \
+  {{TM, TN, TK, WM / KW, WN, 2}, HPVM_PREC_FP32, F32AnyConfig<TM, TN, SUB, WM, WN, NST, KW>::kThreads,  \
+   F32AnyConfig<TM, TN, SUB, WM, WN, NST, KW>::kLdsBytes, &F32AnyConfig<TM, TN, SUB, WM, WN, NST, KW>::launch, \
+   nullptr, nullptr, nullptr, &F32AnyConfig<TM, TN, SUB, WM, WN, NST, KW>::split_bytes,                  \
+   &F32AnyConfig<TM, TN, SUB, WM, WN, NST, KW>::launch_split}
+
 // Entry 0 is the default for large problems.  The stages of the entries on
-// the loop for any size: two of 32-deep slabs, or four of 16-deep ones
-// (alike in time: 64 x 64 tiles, 1000 x 1003 x 777, 21.9 and 22.4 us).
+// the loop for any size: 24 to 64 KB of slabs, alike in time however they
+// are cut (64 x 64 tiles at 1000 x 1003 x 777: two 32-deep slabs 21.9 us,
+// four 16-deep 22.4, six 22.4; in two k groups 20.9 and 19.7).
 static const MfmaEntry kF32Menu[] = {
     HPVM_F32_DMA_ENTRY(256, 256, 32, 64, 2),
     HPVM_F32_ENTRY(128, 128, 16, 64, 64, 16, 4, 1),
     HPVM_F32_ENTRY(256, 128, 16, 128, 64, 16, 3, 1),
     HPVM_F32_ENTRY(128, 128, 32, 64, 64, 32, 2, 1),
-    HPVM_F32_ENTRY(64, 64, 16, 32, 32, 16, 4, 1),
+    HPVM_F32_ENTRY(64, 64, 16, 32, 32, 16, 6, 1),
     HPVM_F32_ENTRY(128, 64, 16, 64, 32, 16, 4, 1),
     HPVM_F32_ENTRY(64, 128, 16, 32, 64, 16, 4, 1),
     HPVM_F32_DMA_ENTRY(256, 256, 16, 64, 4),
     HPVM_F32_DMA_ENTRY(128, 256, 32, 32, 2),
     HPVM_F32_DMA_ENTRY(128, 128, 32, 32, 2),
+    HPVM_F32_ENTRY(64, 128, 32, 32, 64, 32, 2, 1),
+    HPVM_F32_ENTRY(64, 64, 32, 32, 32, 16, 3, 2),
+    HPVM_F32_SPLIT_ENTRY(32, 32, 128, 32, 32, 32, 2, 4),
 };
 
 #define HPVM_BF16_ENTRY(PREC, X3, TM, TN, TK, WM, WN)                                    \

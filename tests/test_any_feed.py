@@ -82,3 +82,23 @@ def test_stages_hold_the_matrix_and_no_access_leaves_it(kc, R, TK, KW):
                             inside = k < depth - k0
                             at = np.where(inside, base + (i * ld + k if kc else k * ld + i), 0)
                             assert np.array_equal(got, np.where(inside, flat[at], 0)), (extent, depth, pad, t, s)
+
+
+@pytest.mark.parametrize("m,n,k", [(1, 4, 1), (128, 128, 128), (16, 4096, 4096), (33, 35, 2051), (1000, 1003, 777),
+                                   (512, 4096, 1024), (3001, 2999, 1001), (64, 64, 2047), (5, 3, 4096)])
+def test_fp32_choice_agrees_with_its_workspace(m, n, k):
+    """With no tile: the workspace asked for is what the described slices fill, a
+    shorter one gives a choice that fits it, and none gives hpvm_sgemm's."""
+    import paper_1611_00860_amd as hp
+
+    hp.autotune_clear()
+    need = hp.workspace_bytes(m, n, k, "fp32")
+    d = hp.describe(m, n, k, "fp32", workspace_bytes=need)
+    assert need == (4 * m * n * d["splits"] if d["splits"] > 1 else 0)
+    assert d == hp.describe(m, n, k, "fp32", workspace_bytes=1 << 40)
+    plain = hp.describe(m, n, k, "fp32")
+    assert plain["splits"] == 1 and plain == hp.describe(m, n, k, "fp32", workspace_bytes=0)
+    assert (need > 0) == (d["splits"] > 1)
+    if need:
+        short = hp.describe(m, n, k, "fp32", workspace_bytes=need - 1)
+        assert 4 * m * n * short["splits"] < need or short["splits"] == 1

@@ -38,3 +38,17 @@ def test_any_size_integers(gpu, m, n, k, pad, misalign):
     nan_c = np.full_like(C, np.nan)
     got = run(gpu, A, B, nan_c, 1.0, 0.0, None, pad, misalign)
     assert np.array_equal(got, oracle.sgemm(A, B, None, 1.0, 0.0))
+
+
+@pytest.mark.parametrize("m,n,k", [(16, 520, 2048), (33, 35, 2051), (64, 64, 4096), (1, 5, 9000)])
+def test_ragged_split_contraction_integers(gpu, m, n, k):
+    """Shallow outputs over a long contraction run in slices with a workspace (and whole without one)."""
+    A, B, C = inputs.sgemm_operands(m, n, k, seed=k, dist="int")
+    product = A.astype(np.float64) @ B.astype(np.float64)
+    assert gpu.workspace_bytes(m, n, k, "fp32") > 0 and np.abs(product).max() < 2 ** 24
+    print(f"case: split {m}x{n}x{k}", flush=True)
+    for pad, misalign in ((0, False), (1, True)):
+        got = run(gpu, A, B, C, 1.0, 2.0, None, pad, misalign)
+        assert np.array_equal(got, product + 2.0 * C.astype(np.float64))
+        got = run(gpu, A, B, np.full_like(C, np.nan), 1.0, 0.0, None, pad, misalign)
+        assert np.array_equal(got, product)
