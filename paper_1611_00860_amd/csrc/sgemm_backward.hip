@@ -2,10 +2,11 @@
 //
 // dA = alpha G B^T reuses the MFMA main loop with B read in transposed form
 // and folds the scalar gradient dalpha = <A, G B^T> into its epilogue (A is
-// read once more, tile by tile, where dA is written).  dB = alpha A^T G is a
-// plain launch of the main loop with A read in transposed form.  One
-// element-wise pass writes dC_in = beta G and the partial sums of
-// dbeta = <G, C_in>; a single workgroup then reduces the partials.  Every
+// read once more, tile by tile, where dA is written).  dB = alpha A^T G runs
+// the main loop with A read in transposed form.  One element-wise pass
+// writes dC_in = beta G and the partial sums of dbeta = <G, C_in>; a single
+// workgroup then reduces the partials.  In FP32 the tiles of both products
+// and the element-wise pass are one launch (sgemm_grad_any).  Every
 // reduction is FP32 with a fixed order, so results repeat bit for bit.
 //
 // FP32 whole-tile problems can instead run both GEMMs on the DMA-fed loop
@@ -34,6 +35,7 @@
 #include "mfma_bf16.hpp"
 #include "mfma_bf16_dma.hpp"
 #include "mfma_f32.hpp"
+#include "mfma_f32_any.hpp"
 #include "mfma_f32_dma.hpp"
 
 namespace hpvm {
@@ -265,10 +267,132 @@ __global__ void __launch_bounds__(kElemThreads) sgemm_grad_tail(SumJob a, SumJob
   else grad_c_block(c, blk - b.blocks, red);
 }
 
+// dA's epilogue on the loop for any size: C (may be null) <- alpha acc, and
+// this lane's share of <aorig, acc> over the row quads [q0, q1).  Each quad
+// loads its elements of A before its stores.
+template <typename OA, typename OB, int NA, int NB>
+__device__ __forceinline__ float any_grad_a_epilogue(const GemmArgs& q, const float* __restrict__ aorig, int64_t ldao,
+                                                     const f32x16 (&acc)[NA][NB], int m0, int n0, int wm0, int wn0,
+                                                     int lane, int q0, int q1) {
+  float part = 0.0f;
+#pragma unroll
+  for (int a = 0; a < NA; ++a)
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const int col = n0 + OB::index(b, lane & 31, wn0);
+      if (col >= q.n) continue;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        if (g < q0 || g >= q1) continue;
+        float x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int row = m0 + OA::index(a, acc_row(4 * g + u, lane), wm0);
+          x[u] = row < q.m ? aorig[(int64_t)row * ldao + col] : 0.0f;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int row = m0 + OA::index(a, acc_row(4 * g + u, lane), wm0);
+          if (row >= q.m) continue;
+          const float v = acc[a][b][4 * g + u];
+          if (q.C) q.C[(int64_t)row * q.ldc + col] = q.alpha * v;
+          part = fmaf(x[u], v, part);
+        }
+      }
+    }
+  return part;
+}
+
+// Both gradients' tiles and the element-wise pass in one launch of three
+// block ranges: dA's tiles (a: G times B transposed, to a.C, which may be
+// null when partial is given), dB's (b: A transposed times G), grad_c's
+// blocks.  An absent range has no blocks.  As separate launches each product
+// filled the CUs unevenly on its own and every launch's end left them idle:
+// 1000 x 1200 x 800, dA 59 + dB 48 + grad_c 5 us on the register-staged
+// loops.
+template <int TM, int TN, int TK, int WM, int WN, int NST, int KW>
+__global__ void __launch_bounds__((AnyShape<TM, TN, TK, WM, WN, false, true, NST, KW>::kThreads))
+    sgemm_grad_any(GemmArgs a, const float* __restrict__ aorig, int64_t ldao, float* __restrict__ partial, GemmArgs b,
+                   GradCJob c, int32_t tiles_a, int32_t tiles_b) {
+  extern __shared__ __align__(16) char smem[];
+  using SA = AnyShape<TM, TN, TK, WM, WN, false, true, NST, KW>;
+  using SB = AnyShape<TM, TN, TK, WM, WN, true, false, NST, KW>;
+  int t = blockIdx.x, tm, tn;
+  if (t < tiles_a) {
+    tile_coords(a.tiles_m, a.tiles_n, t, tm, tn);
+    float part = 0.0f;
+    f32_any_tile<TM, TN, TK, WM, WN, false, true, NST, KW>(
+        a, 1, tm, tn, 0, smem,
+        [&](const auto& acc, int m0, int n0, int m_own, int n_own, bool whole, int wm0, int wn0, int lane, int q0,
+            int q1) {
+          if (partial)
+            part = any_grad_a_epilogue<typename SA::OA, typename SA::OB>(a, aorig, ldao, acc, m0, n0, wm0, wn0, lane,
+                                                                         q0, q1);
+          else
+            any_epilogue<typename SA::OA, typename SA::OB, true, kDmaUpdate>(a, F32DmaOut{}, acc, m0, n0, m_own,
+                                                                             n_own, whole, wm0, wn0, lane, 0, q0, q1);
+        });
+    if (!partial) return;
+    __syncthreads();  // the k groups' sums in LDS have been read
+    const float s = block_sum(part, reinterpret_cast<float*>(smem));
+    if (threadIdx.x == 0) partial[t] = s;
+    return;
+  }
+  t -= tiles_a;
+  if (t < tiles_b) {
+    tile_coords(b.tiles_m, b.tiles_n, t, tm, tn);
+    f32_any_tile<TM, TN, TK, WM, WN, true, false, NST, KW>(
+        b, 1, tm, tn, 0, smem,
+        [&](const auto& acc, int m0, int n0, int m_own, int n_own, bool whole, int wm0, int wn0, int lane, int q0,
+            int q1) {
+          any_epilogue<typename SB::OA, typename SB::OB, false, kDmaUpdate>(b, F32DmaOut{}, acc, m0, n0, m_own, n_own,
+                                                                            whole, wm0, wn0, lane, 0, q0, q1);
+        });
+    return;
+  }
+  grad_c_block(c, t - tiles_b, reinterpret_cast<float*>(smem));
+}
+
 namespace {
 
-// One candidate tile of the backward.  Fused entries run dA through
-// sgemm_grad_a and dB through the fused menu entry's launch; staged entries
+// sgemm_grad_any on one tile; a null pointer leaves a range out.
+template <int TM, int TN, int TK, int WM, int WN, int NST, int KW>
+hipError_t launch_grad_any(const GemmArgs* ga, const float* aorig, int64_t ldao, float* partial, const GemmArgs* gb,
+                           const GradCJob* gc, hipStream_t s) {
+  using S = AnyShape<TM, TN, TK, WM, WN, false, true, NST, KW>;
+  GemmArgs a{}, b{};
+  GradCJob c{};
+  auto tiles = [](GemmArgs& p) {
+    p.tiles_m = (p.m + TM - 1) / TM;
+    p.tiles_n = (p.n + TN - 1) / TN;
+    return p.tiles_m * p.tiles_n;
+  };
+  int32_t ta = 0, tb = 0;
+  if (ga) {
+    a = *ga;
+    ta = tiles(a);
+  }
+  if (gb) {
+    b = *gb;
+    tb = tiles(b);
+  }
+  if (gc) c = *gc;
+  auto* fn = &sgemm_grad_any<TM, TN, TK, WM, WN, NST, KW>;
+  hipError_t e = hipSuccess;
+  if (S::kLdsBytes > 65536)
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)S::kLdsBytes);
+  if (e != hipSuccess) return e;
+  void* kargs[] = {&a, &aorig, &ldao, &partial, &b, &c, &ta, &tb};
+  return hipLaunchKernel(reinterpret_cast<const void*>(fn), dim3((unsigned)(ta + tb + c.blocks)), dim3(S::kThreads),
+                         kargs, (size_t)S::kLdsBytes, s);
+}
+
+// One candidate tile of the backward.  Fused FP32 entries run everything
+// through sgemm_grad_any (what f32_any_fits leaves out: sgemm_grad_a and the
+// single launch on 64 x 64 x 16 tiles); fused BF16 and bf16x3 entries run dA
+// through sgemm_grad_a and dB through the fused menu entry's launch; staged
+// entries
 // run both through the staged lowering (one conversion launch into the
 // workspace, with the transposition of each operand folded into it).
 struct BwdEntry {
@@ -278,6 +402,8 @@ struct BwdEntry {
   int64_t lds;
   void (*grad_a)(GemmArgs, const float*, int64_t, float*);  // null for staged entries
   bool dma = false;  // split-contraction DMA-fed entry
+  hipError_t (*any)(const GemmArgs*, const float*, int64_t, float*, const GemmArgs*, const GradCJob*,
+                    hipStream_t) = nullptr;  // FP32
   // DMA entries: the entry for what the DMA-fed loop does not cover (FP32:
   // the passes that are not whole aligned tiles; BF16: the whole call).
   int fallback = 1;
@@ -290,6 +416,15 @@ constexpr BwdEntry fused_entry() {
                               : Bf16TileShape<TM, TN, TK, WM, WN, PREC == HPVM_PREC_BF16X3>::kLdsBytes;
   return BwdEntry{{TM, TN, TK, WM, WN, 2}, PREC, (TM / WM) * (TN / WN) * kWave, lds,
                   &sgemm_grad_a<TM, TN, TK, WM, WN, PREC>};
+}
+// FP32 on the loop for any size: SUB deep sub-slabs, KW of them per slab.
+constexpr hpvm_tile kOddTile{64, 64, 16, 32, 32, 2};  // of the products it leaves out
+template <int TM, int TN, int TK, int WM, int WN, int SUB, int NST, int KW>
+constexpr BwdEntry any_entry() {
+  BwdEntry e = fused_entry<64, 64, 16, 32, 32, HPVM_PREC_FP32>();
+  e.tile = hpvm_tile{TM, TN, TK, WM / KW, WN, 2};
+  e.any = &launch_grad_any<TM, TN, SUB, WM, WN, NST, KW>;
+  return e;
 }
 constexpr BwdEntry staged_entry(int tm, int tn, int tk, int wm, int wn, int prec) {
   return BwdEntry{{tm, tn, tk, wm, wn, 3}, prec, 0, 0, nullptr};
@@ -304,8 +439,7 @@ using DmaA = F32DmaShape<kDmaTile, kDmaTile, kDmaK, kDmaWM, kDmaWN, false, true,
 using DmaB = F32DmaShape<kDmaTile, kDmaTile, kDmaK, kDmaWM, kDmaWN, true, false, kDmaStages>;
 constexpr BwdEntry dma_entry() {
   BwdEntry e{{kDmaTile, kDmaTile, kDmaK, kDmaWM, kDmaWN, kDmaStages}, HPVM_PREC_FP32, DmaA::NW * kWave,
-             DmaA::kLdsBytes > DmaB::kLdsBytes ? DmaA::kLdsBytes : DmaB::kLdsBytes,
-             &sgemm_grad_a<128, 128, 32, 64, 64, HPVM_PREC_FP32>};
+             DmaA::kLdsBytes > DmaB::kLdsBytes ? DmaA::kLdsBytes : DmaB::kLdsBytes, nullptr};
   e.dma = true;
   return e;
 }
@@ -322,16 +456,19 @@ constexpr BwdEntry bf16_dma_entry(int fallback) {
   return e;
 }
 
-// Per precision, in the order the built-in choice tries them.  kBwd[1] is
-// the DMA entry's fallback for problems that are not whole tiles.
+// Per precision; BF16 and bf16x3 in the order the built-in choice tries them.
+// kBwd[1] is the FP32 DMA entry's fallback for passes that are not whole tiles.
 constexpr BwdEntry kBwd[] = {
     dma_entry(),
-    fused_entry<128, 128, 32, 64, 64, HPVM_PREC_FP32>(),
-    fused_entry<128, 128, 16, 64, 64, HPVM_PREC_FP32>(),
-    fused_entry<128, 64, 16, 64, 32, HPVM_PREC_FP32>(),
-    fused_entry<64, 128, 16, 32, 64, HPVM_PREC_FP32>(),
-    fused_entry<64, 64, 16, 32, 32, HPVM_PREC_FP32>(),
-    bf16_dma_entry(7),
+    any_entry<64, 128, 32, 32, 64, 32, 2, 1>(),
+    any_entry<128, 128, 32, 64, 64, 32, 2, 1>(),
+    any_entry<128, 128, 16, 64, 64, 16, 4, 1>(),
+    any_entry<128, 64, 16, 64, 32, 16, 4, 1>(),
+    any_entry<64, 128, 16, 32, 64, 16, 4, 1>(),
+    any_entry<64, 64, 16, 32, 32, 16, 6, 1>(),
+    any_entry<64, 64, 32, 32, 32, 16, 3, 2>(),
+    any_entry<32, 32, 128, 32, 32, 32, 2, 4>(),
+    bf16_dma_entry(10),
     staged_entry(128, 128, 64, 64, 32, HPVM_PREC_BF16),
     staged_entry(128, 128, 64, 64, 64, HPVM_PREC_BF16),
     staged_entry(256, 256, 64, 128, 64, HPVM_PREC_BF16),
@@ -346,8 +483,9 @@ constexpr BwdEntry kBwd[] = {
     fused_entry<64, 64, 32, 32, 32, HPVM_PREC_BF16X3>(),
 };
 constexpr int kNumBwd = sizeof(kBwd) / sizeof(kBwd[0]);
-static_assert(kBwd[6].dma && kBwd[6].prec == HPVM_PREC_BF16 && !kBwd[7].grad_a && kBwd[7].prec == HPVM_PREC_BF16,
+static_assert(kBwd[9].dma && kBwd[9].prec == HPVM_PREC_BF16 && !kBwd[10].grad_a && kBwd[10].prec == HPVM_PREC_BF16,
               "the BF16 DMA entry falls back to the staged entry after it");
+static_assert(kBwd[0].dma && kBwd[1].any, "the FP32 DMA entry falls back to the entry after it");
 
 int64_t tiles_for(const hpvm_tile& t, int64_t rows, int64_t cols) {
   return ((rows + t.tile_m - 1) / t.tile_m) * ((cols + t.tile_n - 1) / t.tile_n);
@@ -406,10 +544,51 @@ int64_t split_sum_blocks(int64_t rows, int64_t cols) {
   return std::max<int64_t>(1, std::min<int64_t>(kElemBlocks, (rows * cols / 4 + kElemThreads - 1) / kElemThreads));
 }
 
-// Built-in choice: the DMA entry when dA is whole tiles, else the first
-// entry giving at least one tile per CU of a 256-CU part, else the one
-// giving the most tiles -- counting dA's tiles, plus dB's for a staged entry
-// that runs both products in one launch.
+// Built-in FP32 choice: the least estimated time, by the single launch's model
+// (f32_default_tile) over both gradients' tiles: `start` plus, for the most
+// tiles one of 256 CUs gets, at least one of the deeper gradient's, their
+// products at the FP32 MFMA rate (614 GFLOP/s a CU) times `load`.  The DMA
+// entry (whole 256 x 256 tiles) adds the launch of its slice sums, about
+// 6 us, and their traffic.
+const BwdEntry* f32_pick(int64_t m, int64_t n, int64_t k) {
+  struct Candidate {
+    hpvm_tile tile;
+    double start, load;
+  };
+  static const Candidate kCandidates[] = {
+      {{kDmaTile, kDmaTile, kDmaK, kDmaWM, kDmaWN, kDmaStages}, 12.0, 1.05},
+      {{64, 128, 32, 32, 64, 2}, 8.0, 1.12},
+      {{64, 64, 32, 16, 32, 2}, 6.5, 1.15},
+      {{32, 32, 128, 8, 32, 2}, 6.0, 1.45},
+  };
+  const BwdEntry* pick = nullptr;
+  double best = 0.0;
+  for (const Candidate& c : kCandidates) {
+    const BwdEntry* e = find_bwd(HPVM_PREC_FP32, c.tile);
+    if (!e) continue;
+    const double ta = (double)tiles_for(c.tile, m, k), tb = (double)tiles_for(c.tile, k, n);
+    double slices = 1.0, extra = 0.0;
+    if (e->dma) {
+      slices = pair_splits(m, n, k);
+      if (slices == 0.0) continue;
+      extra = 6.0 + (2.0 * slices + 1.0) * ((double)m * k + (double)k * n) * 4.0 / 4.0e6;
+    }
+    const double per_k = 2.0 * c.tile.tile_m * c.tile.tile_n / 614400.0 / slices;
+    const double deep = (double)std::max(m, n) * per_k, mean = (ta * n + tb * m) / std::max(ta + tb, 1.0) * per_k;
+    const double rounds = (double)(((int64_t)((ta + tb) * slices) + 255) / 256);
+    const double time = c.start + c.load * std::max(rounds * mean, deep) + extra;
+    if (!pick || time < best) {
+      best = time;
+      pick = e;
+    }
+  }
+  return pick;
+}
+
+// Built-in choice for BF16 and bf16x3: the first entry giving at least one
+// tile per CU of a 256-CU part, else the one giving the most tiles --
+// counting dA's tiles, plus dB's for a staged entry that runs both products
+// in one launch.
 int64_t launch_tiles(const BwdEntry& e, int64_t m, int64_t n, int64_t k) {
   int64_t tiles = tiles_for(e.tile, m, k);
   if (!e.grad_a) {
@@ -427,15 +606,12 @@ const BwdEntry* pick(int32_t prec, int64_t m, int64_t n, int64_t k) {
   }
   const BwdEntry* most = nullptr;
   const bool staged_ok = staged_k_ok(n) && staged_k_ok(m);  // the dA and dB contractions
+  if (prec == HPVM_PREC_FP32) return f32_pick(m, n, k);
   for (int i = 0; i < kNumBwd; ++i) {
-    if (kBwd[i].prec != prec) continue;
-    if (kBwd[i].dma) {
-      // FP32 only: the BF16 DMA entry reads FP32 slabs where the staged
-      // products read bfloat16 planes, twice the bytes (4096 x 4096 x 1024:
-      // 0.181 ms against 0.131 for the staged 128 x 128 x 64 tile).
-      if (prec == HPVM_PREC_FP32 && dma_splits(m, k, n)) return &kBwd[i];
-      continue;
-    }
+    // The BF16 DMA entry reads FP32 slabs where the staged products read
+    // bfloat16 planes, twice the bytes (4096 x 4096 x 1024: 0.181 ms against
+    // 0.131 for the staged 128 x 128 x 64 tile).
+    if (kBwd[i].prec != prec || kBwd[i].dma) continue;
     if (!kBwd[i].grad_a && !staged_ok) continue;
     const int64_t tiles = launch_tiles(kBwd[i], m, n, k);
     if (tiles >= kTargetTiles) return &kBwd[i];
@@ -498,6 +674,7 @@ BwdLayout bwd_layout(const BwdEntry* e, int64_t m, int64_t n, int64_t k) {
   auto up = [](int64_t b) { return (b + 255) / 256 * 256; };
   BwdLayout L;
   L.na = (m > 0 && k > 0) ? tiles_for(e->dma ? kBwd[e->fallback].tile : e->tile, m, k) : 0;
+  if (e->prec == HPVM_PREC_FP32 && m > 0 && k > 0) L.na = std::max(L.na, tiles_for(kOddTile, m, k));
   const DmaPlan d = dma_plan(e, m, n, k);
   if (d.sa) L.na = std::max(L.na, split_sum_blocks(m, k));
   L.nb = elem_blocks(m, n);
@@ -764,7 +941,7 @@ int hpvm_sgemm_backward(int64_t m, int64_t n, int64_t k, float alpha, float beta
   // A DMA entry runs a pass it does not cover in whole, aligned tiles on
   // its fallback entry.
   const BwdEntry* fb = cfg->dma ? &kBwd[cfg->fallback] : cfg;
-  const MfmaEntry* me = find_menu_entry(prec, fb->tile);
+  const MfmaEntry* me = find_menu_entry(prec, fb->any ? kOddTile : fb->tile);
   const bool dma_a = plan.sa && vec16(G, ldg) && vec16(B, ldb) && (!dA || vec16(dA, ldda)) &&
                      (!dalpha || vec16(A, lda));
   const bool dma_b = plan.sb && vec16(A, lda) && vec16(G, ldg) && vec16(dB, lddb);
@@ -791,6 +968,7 @@ int hpvm_sgemm_backward(int64_t m, int64_t n, int64_t k, float alpha, float beta
   // tiles and aligned.
   const bool dma_pair = cfg->dma && run_a && run_b && dma_a && dma_b && plan.sp > 0;
   GemmArgs a_pair{};
+  bool any_a = false;  // dA waits for the launch it shares with dB and grad_c (fb->any)
   if (staged && (run_a || run_b)) {
     if (!me || !me->launch_staged_planes) return hip_error(hipErrorInvalidValue, "backward staged entry");
     P = bwd_planes(prec, stage, m, n, k);
@@ -849,8 +1027,9 @@ int hpvm_sgemm_backward(int64_t m, int64_t n, int64_t k, float alpha, float beta
     a.beta = 0.0f;
     a.vec_a = vec16(G, ldg);
     a.vec_b = vec16(B, ldb);
-    a.tiles_m = (a.m + fb->tile.tile_m - 1) / fb->tile.tile_m;
-    a.tiles_n = (a.n + fb->tile.tile_n - 1) / fb->tile.tile_n;
+    const hpvm_tile& at = fb->any ? kOddTile : fb->tile;  // sgemm_grad_a's
+    a.tiles_m = (a.m + at.tile_m - 1) / at.tile_m;
+    a.tiles_n = (a.n + at.tile_n - 1) / at.tile_n;
     if (dma_a) {
       if (dma_pair)
         a_pair = a;  // launched with dB below
@@ -866,6 +1045,10 @@ int hpvm_sgemm_backward(int64_t m, int64_t n, int64_t k, float alpha, float beta
         a_pair = a;  // launched with dB below
       else
         e = me->launch_staged_planes(a, StagedPlanes{P.gh, P.gl, P.bh, P.bl}, A, lda, dalpha ? pa : nullptr, s);
+    } else if (fb->any && f32_any_fits(a, false, true)) {
+      any_a = true;
+      a_pair = a;
+      na = dalpha ? tiles_for(fb->tile, m, k) : 0;
     } else if (dalpha) {
       // Fused pass: dA (when requested) and the per-tile partials of dalpha.
       if (fb->lds > 65536)
@@ -889,6 +1072,8 @@ int hpvm_sgemm_backward(int64_t m, int64_t n, int64_t k, float alpha, float beta
   if (e != hipSuccess) return hip_error(e, "backward dA launch");
 
   // dB: contraction over m.
+  GemmArgs b_any{};
+  bool any_b = false;
   if (dB && kn && m == 0) {
     e = launch_scale(dB, lddb, k, n, 0.0f, s);
   } else if (run_b) {
@@ -918,6 +1103,10 @@ int hpvm_sgemm_backward(int64_t m, int64_t n, int64_t k, float alpha, float beta
                                                           nullptr, 0, nullptr, s)
               : launch_split<HPVM_PREC_BF16, true, false>(b, plan.sb, reinterpret_cast<float*>(stage), dB, lddb,
                                                           nullptr, 0, nullptr, s);
+    else if (fb->any && f32_any_fits(b, true, false)) {
+      any_b = true;
+      b_any = b;
+    }
     else if (!me) e = hipErrorInvalidValue;
     else if (staged && pair)
       e = me->launch_staged_pair(a_pair, StagedPlanes{P.gh, P.gl, P.bh, P.bl}, A, lda, dalpha ? pa : nullptr, b,
@@ -927,6 +1116,14 @@ int hpvm_sgemm_backward(int64_t m, int64_t n, int64_t k, float alpha, float beta
     else e = me->launch(b, true, false, s);
   }
   if (e != hipSuccess) return hip_error(e, "backward dB launch");
+
+  if (any_a || any_b) {
+    const bool with_c = grad_c && !gc_done;
+    e = fb->any(any_a ? &a_pair : nullptr, A, lda, dalpha ? pa : nullptr, any_b ? &b_any : nullptr,
+                with_c ? &gc : nullptr, s);
+    gc_done = gc_done || with_c;
+  }
+  if (e != hipSuccess) return hip_error(e, "backward gradients launch");
 
   if (grad_c && !gc_done) {
     void* kargs[] = {&gc};

@@ -52,3 +52,25 @@ def test_ragged_split_contraction_integers(gpu, m, n, k):
         assert np.array_equal(got, product + 2.0 * C.astype(np.float64))
         got = run(gpu, A, B, np.full_like(C, np.nan), 1.0, 0.0, None, pad, misalign)
         assert np.array_equal(got, product)
+
+
+@pytest.mark.parametrize("m,n,k", [(33, 35, 37), (64, 128, 64), (130, 67, 129), (5, 260, 300), (257, 3, 66), (70, 90, 2)])
+@pytest.mark.parametrize("pad,misalign", [(0, False), (3, True)])
+def test_any_size_backward_integers(gpu, m, n, k, pad, misalign):
+    """Both gradients, dC_in and both scalars, every FP32 tile, each alone and
+    together: exact on integers (all sums stay below 2^24)."""
+    import torch
+
+    A, B, C, G = (np.clip(x, -2, 2) for x in inputs.backward_operands(m, n, k, seed=m + n + k, dist="int"))
+    a, b, c, g = (x.astype(np.float64) for x in (A, B, C, G))
+    ref = {"dA": 2 * (g @ b.T), "dB": 2 * (a.T @ g), "dC_in": -1 * g, "dalpha": (g * (a @ b)).sum(),
+           "dbeta": (g * c).sum()}
+    assert max(np.abs(v).max() for v in ref.values()) < 2 ** 24
+    dev = [to_dev(x, pad, misalign) for x in (A, B, C, G)]
+    for tile in [None] + gpu.backward_menu("fp32"):
+        print(f"case: backward {m}x{n}x{k} pad {pad} misalign {misalign} tile {tile}", flush=True)
+        for need in (("dA", "dB", "dC_in", "dalpha", "dbeta"), ("dA",), ("dB", "dbeta"), ("dalpha",), ("dA", "dB")):
+            got = gpu.sgemm_backward(*dev, 2.0, -1.0, need=need, tile=tile)
+            torch.cuda.synchronize()
+            for name in need:
+                assert np.array_equal(to_host(got[name]), ref[name]), (tile, need, name)
