@@ -89,14 +89,13 @@ typedef enum hpvm_precision {
  *                   tiling against (Sec. 3.4, 5.1): one lane per element of
  *                   C reading A and B from global memory, tile_m x tile_n
  *                   lanes per launch group; 1 = one buffer
- *                   (literal lowering); 2 = FP32 tiles with other leaves
- *                   than 128 wide: a ring of two to four LDS stages filled
+ *                   (literal lowering); 2 = tiles with leaves less than
+ *                   128 wide: a ring of two to four LDS stages filled
  *                   straight from HBM, for any sizes and alignment (but for
  *                   products with n < 4 or rows 2^22 floats or more apart,
- *                   which run a 64 x 64 x 16 tile filled through
- *                   registers); BF16 and bf16x3: two stages filled through
- *                   registers, conversion to bfloat16 fused into that copy;
- *                   3 = staged BF16 / bf16x3 lowering: operands
+ *                   which run a 64 x 64 tile filled through registers), and
+ *                   for BF16 and bf16x3 converted as each MFMA fragment is
+ *                   read; 3 = staged BF16 / bf16x3 lowering: operands
  *                   converted into a workspace by a separate pass, then
  *                   moved into LDS stages: straight from HBM for every BF16
  *                   tile and for bf16x3's 256 x 256 tile and 128 x 128 x 64
@@ -112,9 +111,8 @@ typedef enum hpvm_precision {
  *                   16-byte aligned with leading dimensions that are
  *                   multiples of 4 (edge tiles computed from a corner moved
  *                   inward, storing only the outputs they own); any other
- *                   problem given such a tile runs a 64 x 128 x 32 FP32
- *                   tile for any size, or the register-staged BF16 / bf16x3 tile of the
- *                   same size with tile_k = 32.
+ *                   problem given such a tile runs a 64 x 128 x 32 tile
+ *                   for any size (BF16 / bf16x3 256 x 256 tiles: 128 x 256).
  * hpvm_tile_menu lists the combinations compiled into this library.       */
 typedef struct hpvm_tile {
   int32_t tile_m;
@@ -199,11 +197,8 @@ typedef struct hpvm_edge {
  *   prec         : hpvm_precision.
  *   tile         : hierarchy shape, or NULL to take the autotuned choice for
  *                  this shape class (until hpvm_autotune has run, the
- *                  built-in default: FP32 the tile with the least
- *                  estimated time; BF16 and bf16x3 the menu's entry 0 when
- *                  it gives at least 256 tiles, else the DMA-fed
- *                  128 x 128 x 32 tile if that does, else 64 x 64 x 32).
- *                  Must be
+ *                  built-in default: the tile with the least estimated
+ *                  time).  Must be
  *                  in hpvm_tile_menu for prec and not need a workspace
  *                  (stages != 3).
  *   stream       : hipStream_t or NULL.
@@ -227,7 +222,8 @@ int hpvm_sgemm(int64_t m, int64_t n, int64_t k, float alpha, const float* A,
  * `workspace`, then one launch forming C <- alpha * (sum of the partials,
  * in slice order) + beta * C.  Results then differ from the single launch
  * by rounding only.  FP32's 32 x 32 x 128 tile splits products of any sizes
- * with k >= 2048 the same way (without the last condition).
+ * with k >= 2048 the same way (without the last condition), BF16's and
+ * bf16x3's 32 x 128 x 32 tile those with k >= 1024 (up to 512 workgroups).
  * workspace: device memory, 16-byte aligned, at least
  * hpvm_sgemm_workspace_bytes(m, n, k, prec, tile) bytes (may be NULL when
  * that is 0); its contents are scratch.  For a split tile it is
@@ -236,12 +232,14 @@ int hpvm_sgemm(int64_t m, int64_t n, int64_t k, float alpha, const float* A,
  * even 128 x 128 tiles would not cover 256 CUs with (BF16 and bf16x3: with
  * k >= 2048) take the DMA-fed tile with the fewest slices (the first in
  * menu order on a tie) when the workspace holds the partial sums; other
- * FP32 products the tile with the least estimated time, the 32 x 32 x 128
- * tile's split included; other BF16 products of at least 2^31 multiply-adds (m n k) take the first
- * staged tile, or 128 x 128 x 64 with 64 x 32 leaves when the first would
- * give fewer than 256 tiles (bf16x3 only when the DMA-fed 256 x 256 tile
- * would not cover the CUs or does not suit k and n), and others
- * hpvm_sgemm's choice.  Every other argument and rule is hpvm_sgemm's.     */
+ * FP32 products, and BF16 and bf16x3 ones of less than 2^31 multiply-adds
+ * (m n k), the tile with the least estimated time, splits included; larger
+ * BF16 products take the first staged tile, or, when that would give fewer
+ * than 256 tiles, 128 x 128 x 64 with 64 x 32 leaves or a 128 x 256 tile of
+ * FP32 operands, whichever is estimated faster (bf16x3 only when the
+ * DMA-fed 256 x 256 tile would not cover the CUs or does not suit k and n),
+ * and others hpvm_sgemm's choice.  Every other argument and rule is
+ * hpvm_sgemm's.                                                            */
 int hpvm_sgemm_ws(int64_t m, int64_t n, int64_t k, float alpha, const float* A, int64_t lda,
                   const float* B, int64_t ldb, float beta, float* C, int64_t ldc, int32_t prec,
                   const hpvm_tile* tile, void* workspace, int64_t workspace_bytes, void* stream);

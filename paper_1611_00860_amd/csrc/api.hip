@@ -165,23 +165,6 @@ const hpvm::MfmaEntry* f32_mid_entry() {
 }  // namespace
 
 namespace hpvm {
-// Built-in BF16 / bf16x3 choice for tile == NULL when the autotuner has no
-// entry and no workspace lowering applies: false for the menu's entry 0 (the
-// DMA-fed 256 x 256 tile) when it gives at least 256 tiles (one per CU of a
-// 256-CU part), else the DMA-fed 128 x 128 tile when that does, else the
-// 64 x 64 x 32 tile (1024^3 BF16: 0.020 ms against 0.064 for 256 x 256).
-bool default_small_tile(int32_t prec, int64_t m, int64_t n, hpvm_tile* out) {
-  const hpvm::MfmaEntry* e0 = hpvm::menu_entry_at(prec, 0);
-  if (!e0) return false;
-  // BF16 / bf16x3: the DMA-fed 128 x 128 tile when it covers the CUs
-  // (2048^3 BF16: 0.055 ms against 0.084 for 64 tiles of 256 x 256), else
-  // the register-staged 64 x 64 x 32 tile.
-  const hpvm::MfmaEntry* mid = hpvm::find_menu_entry(prec, hpvm_tile{128, 128, 32, 64, 64, 4});
-  const hpvm::MfmaEntry* small = hpvm::find_menu_entry(prec, hpvm_tile{64, 64, 32, 32, 32, 2});
-  if (!small || !mid || tiles_of(e0->tile, m, n) >= 256) return false;
-  *out = tiles_of(mid->tile, m, n) >= 256 ? mid->tile : small->tile;
-  return true;
-}
 // The FP32 tile with the least estimated time (microseconds): `start` (launch,
 // the ring's first fill, epilogue) plus, for the most tiles (of every slice)
 // that one of 256 CUs gets, the time their products take at the FP32 MFMA
@@ -227,6 +210,55 @@ bool f32_default_tile(int64_t m, int64_t n, int64_t k, int64_t split_ws, hpvm_ti
   }
   return found;
 }
+
+// The same for BF16 and bf16x3: 6 us plus, for the most tiles (of every
+// slice) that one of 256 CUs gets, the time of their 32-deep slabs.  These
+// loops move FP32 operands and convert them in registers, so a slab's time
+// is that of its transfers, LDS reads and conversions, not of its MFMAs.
+// Fitted to timings of each tile; estimated and measured, BF16:
+//   64 x 64: 1024^3 15.0, 14.9 us     64 x 128: 1500 x 1100 x 900 17.9, 17.7
+//   128 x 128 (4 stages): 2048^3 53, 55
+//   128 x 256: 3000 x 2500 x 2000 57, 57; bf16x3 115, 106 to 118
+//   256 x 256: 8192^3 1486, 1480; bf16x3 2658, 2650
+static bool bf16_default_tile(int32_t prec, int64_t m, int64_t n, int64_t k, int64_t split_ws, hpvm_tile* out,
+                              double* estimate = nullptr, bool large_only = false) {
+  const bool x3 = prec == HPVM_PREC_BF16X3;
+  struct Candidate {
+    hpvm_tile tile;
+    double slab, slab_x3;  // us
+    bool aligned;          // only where its own loop runs (mfma_bf16_dma.hpp)
+  };
+  const Candidate kCandidates[] = {
+      {menu_entry_at(prec, 0)->tile, 1.445, 2.59, true},
+      {{128, 256, 32, 64, 64, 2}, 0.82, 1.75, false},
+      {{128, 128, 32, 64, 64, 4}, 0.73, 1.20, true},
+      {{64, 128, 32, 32, 64, 2}, 0.41, 0.71, false},
+      {{64, 64, 32, 32, 32, 2}, 0.28, 0.44, false},
+      {{32, 128, 32, 32, 32, 2}, 0.29, 0.46, false},
+  };
+  double best = 0.0;
+  bool found = false;
+  for (const Candidate& c : kCandidates) {
+    const hpvm_tile& t = c.tile;
+    if (c.aligned && (m < t.tile_m || n < t.tile_n || n % 4 || k % t.tile_k)) continue;
+    if (large_only && t.tile_m * t.tile_n < 128 * 256) continue;
+    const MfmaEntry* e = find_menu_entry(prec, t);
+    if (!e) continue;
+    int64_t slices = 1;
+    const int64_t bytes = c.aligned ? 0 : entry_split_bytes(e, m, n, k);
+    if (bytes > 0 && (split_ws < 0 || split_ws >= bytes)) slices = bytes / (m * n * (int64_t)sizeof(float));
+    const double rounds = (double)((tiles_of(t, m, n) * slices + 255) / 256);
+    double time = 6.0 + rounds * (double)k / (32.0 * slices) * (x3 ? c.slab_x3 : c.slab);
+    if (slices > 1) time += 4.5 + (double)(bytes + m * n * 4) / 4.0e6;
+    if (!found || time < best) {
+      best = time;
+      *out = t;
+      found = true;
+    }
+  }
+  if (estimate) *estimate = best;
+  return found;
+}
 }  // namespace hpvm
 
 namespace {
@@ -250,57 +282,59 @@ const hpvm::MfmaEntry* fewest_slices(int32_t prec, int64_t m, int64_t n, int64_t
 }
 
 // Built-in choice of hpvm_sgemm_ws (and of hpvm_sgemm_workspace_bytes) for
-// tile == NULL when the autotuner has no entry: products that even 128 x 128
-// tiles would not cover the CUs with (BF16 and bf16x3: with k >= 2048) take
-// the DMA-fed entry that splits the contraction into the deepest slices,
-// provided `ws_bytes` (the caller's workspace; -1 = as much as needed)
-// holds its partial sums (BF16 512 x 512 x 4096: 0.035 ms against 0.095 on
-// 64 x 64 tiles, 1024 x 1024 x 4096: 0.047 against 0.069 staged); other
-// BF16 products of at least 2^31 multiply-adds take the first staged tile,
-// whose conversion pass is then a small share of the time (or, when that
-// gives fewer than 256 tiles, the 128 x 128 x 64 tile with 64 x 32 leaves);
-// bf16x3 products the same only when 256 x 256 tiles would not cover the
-// CUs (or k or n does not suit the DMA-fed tile); other FP32 products the
-// tile with the least estimated time (f32_default_tile).  Returns false when
-// none applies (hpvm_sgemm's choice then): a split tile run as one
-// launch would be the slowest choice there is (64 tiles of 128 x 128 at
-// 1024 x 1024 x 4096 FP32: 28 TFLOP/s against 75 for hpvm_sgemm's 64 x 64
-// tiles).
+// tile == NULL when the autotuner has no entry; ws_bytes: the caller's
+// workspace (-1 = as much as needed).  In order:
+//  * whole-tile products that even 128 x 128 tiles would not cover the CUs
+//    with (BF16 and bf16x3: with k >= 2048; at 1024^3 the 64 x 64 tiles were
+//    faster) take the DMA-fed entry that splits the contraction into the
+//    deepest slices when the workspace holds its partial sums (BF16
+//    512 x 512 x 4096: 0.035 ms against 0.095 on 64 x 64 tiles); with a
+//    smaller workspace, hpvm_sgemm's choice;
+//  * FP32, and BF16 / bf16x3 products under 2^31 multiply-adds, the tile
+//    with the least estimated time, splits that fit the workspace included;
+//  * larger BF16 products the first staged tile, whose conversion pass is
+//    then a small share of the time (8192^3: 1.07 ms against 1.48), when it
+//    gives at least 256 tiles; bf16x3 ones the DMA-fed 256 x 256 tile then,
+//    which converts in its fragment reads (8192^3: 2.71 ms against 2.82
+//    staged);
+//  * the rest the staged 128 x 128 x 64 tile of 64 x 32 waves (2048^3 BF16:
+//    0.039 ms against 0.070 for the first staged tile), unless 128 x 256
+//    tiles on the FP32 operands are estimated faster (3000 x 2500 x 2000:
+//    57 us against 51 staged, bf16x3 118 against 116).  Estimate of the
+//    staged: its pass, 3 us and its bytes at 4.8 TB/s, and per 32-deep slab
+//    and round 0.27 us (BF16), 0.65 (bf16x3).
+// Returns false for hpvm_sgemm's choice.
 bool default_ws_tile(int32_t prec, int64_t m, int64_t n, int64_t k, int64_t ws_bytes, hpvm_tile* out) {
-  // The split contraction, only when even 128 x 128 tiles would not cover
-  // the CUs (BF16 / bf16x3: and k >= 2048; at 1024^3 the 64 x 64 tiles were
-  // as fast, 0.031 ms against 0.033), on the entry with the deepest slices.
+  const bool f32 = prec == HPVM_PREC_FP32, x3 = prec == HPVM_PREC_BF16X3;
   const hpvm::MfmaEntry* mid =
-      prec == HPVM_PREC_FP32 ? f32_mid_entry() : hpvm::find_menu_entry(prec, hpvm_tile{128, 128, 32, 64, 64, 4});
-  if (mid && tiles_of(mid->tile, m, n) < 256 && (prec == HPVM_PREC_FP32 || k >= 2048)) {
+      f32 ? f32_mid_entry() : hpvm::find_menu_entry(prec, hpvm_tile{128, 128, 32, 64, 64, 4});
+  if (mid && tiles_of(mid->tile, m, n) < 256 && (f32 || k >= 2048)) {
     int64_t need = 0;
     const hpvm::MfmaEntry* best = fewest_slices(prec, m, n, k, &need);
-    if (best && (ws_bytes < 0 || ws_bytes >= need)) {
+    if (best && ws_bytes >= 0 && ws_bytes < need) return false;
+    if (best) {
       *out = best->tile;
       return true;
     }
   }
-  if (prec == HPVM_PREC_FP32) return hpvm::f32_default_tile(m, n, k, ws_bytes, out);
-  if (prec != HPVM_PREC_BF16 && prec != HPVM_PREC_BF16X3) return false;
-  if ((double)m * (double)n * (double)k < 2147483648.0 || !hpvm::staged_k_ok(k)) return false;
+  if (f32) return hpvm::f32_default_tile(m, n, k, ws_bytes, out);
+  if ((double)m * (double)n * (double)k < 2147483648.0) return hpvm::bf16_default_tile(prec, m, n, k, ws_bytes, out);
   const hpvm::MfmaEntry* staged = nullptr;
-  if (hpvm::staged_menu(prec, &staged) == 0) return false;
-  // Fewer than 256 of the first tile leave CUs idle: eight waves of 64 x 32
-  // on 128 x 128 tiles then ran 1.8-3x faster (2048^3 BF16: 0.039 ms
-  // against 0.070; at 4096^3 the first tile stays ahead, 0.150 against 0.159).
+  if (!hpvm::staged_k_ok(k) || hpvm::staged_menu(prec, &staged) == 0) return false;
   const hpvm::MfmaEntry* small = hpvm::find_menu_entry(prec, hpvm_tile{128, 128, 64, 64, 32, 3});
   const bool big = tiles_of(staged[0].tile, m, n) >= 256;
-  // bf16x3 products that the DMA-fed 256 x 256 tile (menu entry 0) covers
-  // run faster on it, converting in the GEMM's own fragment reads (8192^3:
-  // 2.71 ms against 2.82 staged, 4096^3: 0.353 against 0.366), so they take
-  // no workspace.
   const hpvm::MfmaEntry* e0 = hpvm::menu_entry_at(prec, 0);
-  if (prec == HPVM_PREC_BF16X3 && e0 && tiles_of(e0->tile, m, n) >= 256 && k % e0->tile.tile_k == 0 && n % 4 == 0)
-    return false;
-  const hpvm_tile pick = big || !small ? staged[0].tile : small->tile;
+  if (x3 && e0 && tiles_of(e0->tile, m, n) >= 256 && k % e0->tile.tile_k == 0 && n % 4 == 0) return false;
   // A workspace too small for the planes: the choice without one.
   if (ws_bytes >= 0 && ws_bytes < hpvm::staged_workspace_bytes(prec, m, n, k)) return false;
-  *out = pick;
+  if (!big && small) {
+    const double pass = 3.0 + ((double)m * k + (double)k * n) * (x3 ? 8.0 : 6.0) / 4.8e6;
+    const double rounds = (double)((tiles_of(small->tile, m, n) + 255) / 256);
+    const double time = 6.0 + pass + rounds * (double)k / 32.0 * (x3 ? 0.65 : 0.27);
+    double direct = 0.0;
+    if (hpvm::bf16_default_tile(prec, m, n, k, 0, out, &direct, true) && direct < time) return true;
+  }
+  *out = big || !small ? staged[0].tile : small->tile;
   return true;
 }
 
@@ -309,8 +343,8 @@ bool default_ws_tile(int32_t prec, int64_t m, int64_t n, int64_t k, int64_t ws_b
 // choice needs" (hpvm_sgemm_workspace_bytes asks which tile that is).  In
 // order: the autotuned winner (with a workspace the overall one, unless it
 // splits the contraction and the workspace cannot hold the partial sums:
-// then the winner that needs none), the built-in workspace choice, the
-// built-in small-problem choice; false = the menu's entry 0.
+// then the winner that needs none), the built-in workspace choice, the tile
+// with the least estimated time; false = the menu's entry 0.
 int describe_impl(int64_t m, int64_t n, int64_t k, int32_t prec, const hpvm_tile* tile, bool ws_ok,
                   int64_t ws_bytes, hpvm_dfg* out);
 
@@ -323,8 +357,8 @@ bool choose_tile(int32_t prec, int64_t m, int64_t n, int64_t k, bool ws_ok, int6
     return hpvm::tuned_tile(prec, m, n, k, false, out) != 0;
   }
   if (ws_ok && default_ws_tile(prec, m, n, k, ws_bytes, out)) return true;
-  if (prec == HPVM_PREC_FP32) return hpvm::f32_default_tile(m, n, k, 0, out);
-  return hpvm::default_small_tile(prec, m, n, out);
+  return prec == HPVM_PREC_FP32 ? hpvm::f32_default_tile(m, n, k, 0, out)
+                                : hpvm::bf16_default_tile(prec, m, n, k, 0, out);
 }
 
 }  // namespace

@@ -145,10 +145,6 @@ const MfmaEntry* menu_entry_at(int32_t prec, int index);
 int menu_size(int32_t prec);
 const MfmaEntry* find_menu_entry(int32_t prec, const hpvm_tile& tile);
 
-// Built-in tile for tile == NULL (no autotuned entry, no workspace) when the
-// menu's entry 0 would give fewer than 256 tiles; false otherwise.
-bool default_small_tile(int32_t prec, int64_t m, int64_t n, hpvm_tile* out);
-
 // Built-in FP32 tile of the calls that choose among the whole menu
 // (hpvm_sgemm_ws, the consumer): the one with the least estimated time.
 // split_ws: workspace bytes that a split contraction may use (-1: any).

@@ -148,9 +148,10 @@ struct AnyShape {
   // A group's waves move that group's sub-slab.
   static constexpr int QA = OA::kDma / NWT, QB = OB::kDma / NWT, Q = QA + QB;
   static constexpr int kSlab = KW * TK;
+  static constexpr int kTm = TM, kTn = TN, kTk = TK, kWm = WM, kWn = WN, kNst = NST, kKw = KW;
+  static constexpr bool kAt = AT, kBt = BT;
   static_assert(TM % WM == 0 && TN % WN == 0, "wave tiles");
   static_assert(QA * NWT == OA::kDma && QB * NWT == OB::kDma, "DMA instructions split evenly over a group's waves");
-  static_assert((TK / 8) % 2 == 0, "a slab's last group uses fragment buffer 1");
   static_assert(KW == 1 || (int64_t)NW * OA::kBlocks * OB::kBlocks * 4096 <= kLdsBytes, "partials fit the ring");
   // The groups share the four row quads (with KW = 8 the first four take one each).
   static_assert(KW == 1 || KW == 2 || KW == 4 || KW == 8, "groups share the four row quads");
@@ -252,23 +253,65 @@ __device__ __forceinline__ void any_epilogue(const GemmArgs& q, const F32DmaOut&
   }
 }
 
+// The arithmetic of one wave on staged sub-slabs: kSteps steps per sub-slab
+// (an even number, or one where the buffer does not matter), each read from
+// LDS one step ahead into buffer `buf` and multiplied from it.  MathF32: steps of 8 k, the fragments as read.
+template <typename S>
+struct MathF32 {
+  using OA = typename S::OA;
+  using OB = typename S::OB;
+  static constexpr int NA = OA::kBlocks, NB = OB::kBlocks, kSteps = S::kTk / 8;
+  f32x16 acc[NA][NB];
+  typename OA::Frag fa[2][OA::kFrags];
+  typename OB::Frag fb[2][OB::kFrags];
+  int foff[kSteps], wm0, wn0, lane;
+
+  __device__ __forceinline__ MathF32(int wm, int wn, int ln) : wm0(wm), wn0(wn), lane(ln) {
+#pragma unroll
+    for (int g = 0; g < kSteps; ++g) foff[g] = OA::Rows::frag(lane, g);
+    zero_acc(acc);
+  }
+  // Step g of the sub-slab at st into buffer buf.
+  __device__ __forceinline__ void read(int buf, const char* st, int g) {
+#pragma unroll
+    for (int j = 0; j < OB::kFrags; ++j) fb[buf][j] = OB::frag(st + OA::kBytes, j, g, wn0, lane, foff[g]);
+#pragma unroll
+    for (int j = 0; j < OA::kFrags; ++j) fa[buf][j] = OA::frag(st, j, g, wm0, lane, foff[g]);
+  }
+  // The first step read of all is ready to be multiplied.
+  __device__ __forceinline__ void first() {}
+  // Multiplies buffer buf; the next step (if any) was read into buf ^ 1.
+  __device__ __forceinline__ void multiply(int buf) {
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int a = 0; a < NA; ++a)
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(OA::pick(fa[buf], a, q), OB::pick(fb[buf], b, q),
+                                                           acc[a][b], 0, 0, 0);
+  }
+};
+
 // Accumulates tile (tm, tn) over contraction slice z on the whole
 // workgroup, with the Allocation at smem (S::kLdsBytes), and hands the
 // accumulators to `epilogue(acc, m0, n0, m_own, n_own, whole, wm0, wn0,
 // lane, q0, q1)`.  Ends past a barrier with no transfer outstanding and (KW
 // = 1) no LDS read pending, so smem may be reused at once.
-template <int TM, int TN, int TK, int WM, int WN, bool AT, bool BT, int NST, int KW, typename Epilogue>
-__device__ __forceinline__ void f32_any_tile(const GemmArgs& p, int splits, int tm, int tn, int z, char* smem,
-                                             Epilogue epilogue) {
-  using S = AnyShape<TM, TN, TK, WM, WN, AT, BT, NST, KW>;
+template <typename S, typename Math, typename Epilogue>
+__device__ __forceinline__ void any_tile(const GemmArgs& p, int splits, int tm, int tn, int z, char* smem,
+                                         Epilogue epilogue) {
   using OA = typename S::OA;
   using OB = typename S::OB;
-  constexpr int NA = OA::kBlocks, NB = OB::kBlocks, KG = TK / 8;
-
+  constexpr int NA = OA::kBlocks, NB = OB::kBlocks, KW = S::kKw, NST = S::kNst, TK = S::kTk;
+  constexpr int TM = S::kTm, TN = S::kTn, kSteps = Math::kSteps;
+  constexpr bool AT = S::kAt, BT = S::kBt;
+  static_assert(kSteps == 1 || kSteps % 2 == 0, "a sub-slab's last step uses buffer 1");
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int kw = KW == 1 ? 0 : wave / S::NWT, wt = KW == 1 ? wave : wave % S::NWT;
-  const int wm0 = (wt / S::NWN) * WM, wn0 = (wt % S::NWN) * WN;
+  const int wm0 = (wt / S::NWN) * S::kWm, wn0 = (wt % S::NWN) * S::kWn;
   // The tile's place, and the corner it is computed from (MN sides of at
   // least one tile move inward).
   const int m_own = tm * TM, n_own = tn * TN;
@@ -329,30 +372,7 @@ __device__ __forceinline__ void f32_any_tile(const GemmArgs& p, int splits, int 
     }
   };
 
-  int foff[KG];
-#pragma unroll
-  for (int g = 0; g < KG; ++g) foff[g] = OA::Rows::frag(lane, g);
-  f32x16 acc[NA][NB];
-  zero_acc(acc);
-  typename OA::Frag fa[2][OA::kFrags];
-  typename OB::Frag fb[2][OB::kFrags];
-  auto read = [&](int buf, const char* st, int g) {
-#pragma unroll
-    for (int j = 0; j < OB::kFrags; ++j) fb[buf][j] = OB::frag(st + OA::kBytes, j, g, wn0, lane, foff[g]);
-#pragma unroll
-    for (int j = 0; j < OA::kFrags; ++j) fa[buf][j] = OA::frag(st, j, g, wm0, lane, foff[g]);
-  };
-  auto mfma = [&](int buf) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int a = 0; a < NA; ++a)
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(OA::pick(fa[buf], a, q), OB::pick(fb[buf], b, q),
-                                                           acc[a][b], 0, 0, 0);
-  };
-
+  Math math(wm0, wn0, lane);
   if (slabs > 0) {
 #pragma unroll
     for (int i = 0; i < NST - 1; ++i) bring(i, i);
@@ -366,32 +386,32 @@ __device__ __forceinline__ void f32_any_tile(const GemmArgs& p, int splits, int 
 #pragma unroll
       for (int j = 0; j < S::QB; ++j) asm volatile("" : "+v"(tb[j]));
     }
-    read(0, sub, 0);
+    math.read(0, sub, 0);
     bring(NST - 1, NST - 1);
+    math.first();
   }
   int st = 0;
   for (int s = 0; s < slabs; ++s) {
     const char* cur = sub + st * S::kStage;
 #pragma unroll
-    for (int g = 0; g + 1 < KG; ++g) {
-      read((g + 1) & 1, cur, g + 1);
-      __builtin_amdgcn_sched_barrier(0);
-      mfma(g & 1);
+    for (int g = 0; g + 1 < kSteps; ++g) {
+      math.read((g + 1) & 1, cur, g + 1);
+      math.multiply(g & 1);
     }
     // Slab s + 1 has landed everywhere and slab s is no longer read: bring
-    // slab s + NST into its stage and read slab s + 1's first group under
-    // the last group's MFMAs.
+    // slab s + NST into its stage and read slab s + 1's first step under the
+    // last step's MFMAs.
     const int nst = st + 1 == NST ? 0 : st + 1;
     const int newest = s + NST < dma ? s + NST : dma;  // DMA slabs requested so far
     wait_slabs_barrier<S::Q, NST - 2>(newest - (s + 2));
     if (s + 1 < slabs) {
-      read(0, sub + nst * S::kStage, 0);
+      math.read(0, sub + nst * S::kStage, 0);
       bring(s + NST, st);
     }
-    __builtin_amdgcn_sched_barrier(0);
-    mfma(1);
+    math.multiply(1);
     st = nst;
   }
+  auto& acc = math.acc;
   const bool whole = m_own + TM <= p.m && n_own + TN <= p.n;
   if constexpr (KW == 1) {
     epilogue(acc, m0, n0, m_own, n_own, whole, wm0, wn0, lane, 0, 4);
@@ -428,6 +448,13 @@ __device__ __forceinline__ void f32_any_tile(const GemmArgs& p, int splits, int 
         }
     epilogue(acc, m0, n0, m_own, n_own, whole, wm0, wn0, lane, kw * kQuads, (kw + 1) * kQuads);
   }
+}
+
+template <int TM, int TN, int TK, int WM, int WN, bool AT, bool BT, int NST, int KW, typename Epilogue>
+__device__ __forceinline__ void f32_any_tile(const GemmArgs& p, int splits, int tm, int tn, int z, char* smem,
+                                             Epilogue epilogue) {
+  using S = AnyShape<TM, TN, TK, WM, WN, AT, BT, NST, KW>;
+  any_tile<S, MathF32<S>>(p, splits, tm, tn, z, smem, epilogue);
 }
 
 // One launch: a workgroup per tile and contraction slice (slice-major),

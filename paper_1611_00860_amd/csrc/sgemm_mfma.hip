@@ -12,6 +12,7 @@
 #include "mfma_f32_any.hpp"
 #include "mfma_f32_dma.hpp"
 #include "mfma_bf16.hpp"
+#include "mfma_bf16_any.hpp"
 #include "mfma_bf16_dma.hpp"
 #include "mfma_f32.hpp"
 
@@ -33,7 +34,8 @@ __global__ void __launch_bounds__((TM / WM) * (TN / WN) * kWave) sgemm_mfma_f32(
                             tn * TN + (wave % (TN / WN)) * WN, lane);
 }
 
-// BF16 kernel (X3 = false) and bf16x3 kernel (X3 = true).
+// BF16 kernel (X3 = false) and bf16x3 kernel (X3 = true), register-staged:
+// as the FP32 one, for what the DMA-fed loop does not take.
 template <int TM, int TN, int TK, int WM, int WN, bool AT, bool BT, bool X3>
 __global__ void __launch_bounds__((TM / WM) * (TN / WN) * kWave)
     sgemm_mfma_bf16(GemmArgs p) {
@@ -82,70 +84,6 @@ struct F32Config {
   }
 };
 
-// The DMA-fed loop for any size and alignment (mfma_f32_any.hpp): TK deep
-// sub-slabs, KW of them per slab, NST stages.  It replaced register-staged
-// loops of the same tiles, which loaded one slab ahead (and element by
-// element where an operand was not 16-byte aligned) and waited a memory
-// round trip for nearly every slab: 1000 x 1003 x 777, 64 x 64 tiles, 21.6 us
-// against 56; 512 x 4096 x 1024 38.5 against 47 (54 under a profiler).
-template <int TM, int TN, int TK, int WM, int WN, int NST, int KW>
-struct F32AnyConfig {
-  template <bool AT, bool BT>
-  using Shape = AnyShape<TM, TN, TK, WM, WN, AT, BT, NST, KW>;
-  static constexpr int kThreads = Shape<false, false>::kThreads;
-  static constexpr int64_t kLdsBytes = Shape<false, false>::kLdsBytes;
-  template <bool AT, bool BT, int MODE>
-  static hipError_t run(const GemmArgs& args, int splits, hipStream_t s) {
-    GemmArgs a = args;
-    a.tiles_m = (a.m + TM - 1) / TM;
-    a.tiles_n = (a.n + TN - 1) / TN;
-    F32DmaOut o{};
-    o.splits = splits;
-    void* kargs[] = {&a, &o};
-    auto* fn = &sgemm_f32_any<TM, TN, TK, WM, WN, AT, BT, NST, KW, MODE>;
-    hipError_t e = allow_lds(fn, (size_t)kLdsBytes);
-    if (e != hipSuccess) return e;
-    return hipLaunchKernel(reinterpret_cast<const void*>(fn), dim3((unsigned)(a.tiles_m * a.tiles_n * splits)),
-                           dim3(kThreads), kargs, (size_t)kLdsBytes, s);
-  }
-  static hipError_t launch(const GemmArgs& a, bool at, bool bt, hipStream_t s) {
-    if (at && bt) return hipErrorInvalidValue;
-    if (!f32_any_fits(a, at, bt)) return F32Config<64, 64, 16, 32, 32>::launch(a, at, bt, s);
-    return at   ? run<true, false, kDmaUpdate>(a, 1, s)
-           : bt ? run<false, true, kDmaUpdate>(a, 1, s)
-                : run<false, false, kDmaUpdate>(a, 1, s);
-  }
-  // Contraction slices of a product whose tiles would not cover 256 CUs
-  // (any sizes): doubled while they would not, each at least 256 deep, at
-  // most 16; from k = 2048 on, where the shorter slices save more than the
-  // summing launch costs, about 5 us (16 x 4096 x 4096: 128 tiles of
-  // 32 x 32, 27 us whole, 16 in two slices; 64 x 64 x 4096: 4 tiles, 25 us
-  // whole, 7 in 16 slices).
-  static int splits(int64_t m, int64_t n, int64_t k) {
-    if (m <= 0 || n < 4 || k < 2048) return 1;
-    const int64_t tiles = ((m + TM - 1) / TM) * ((n + TN - 1) / TN);
-    int sp = 1;
-    while (sp < 16 && tiles * sp < 256 && k / (2 * sp) >= 256) sp *= 2;
-    return sp;
-  }
-  static int64_t split_bytes(int64_t m, int64_t n, int64_t k) {
-    const int sp = splits(m, n, k);
-    return sp > 1 ? (int64_t)sp * m * n * (int64_t)sizeof(float) : 0;
-  }
-  static hipError_t launch_split(const GemmArgs& args, void* workspace, hipStream_t s) {
-    const int sp = splits(args.m, args.n, args.k);
-    if (sp <= 1 || !f32_any_fits(args, false, false)) return launch(args, false, false, s);
-    float* part = static_cast<float*>(workspace);
-    GemmArgs a = args;
-    a.C = part;
-    a.ldc = a.n;
-    a.beta = 0.0f;
-    hipError_t e = run<false, false, kDmaSplit>(a, sp, s);
-    if (e != hipSuccess) return e;
-    return launch_split_finish(part, sp, args.m, args.n, args.alpha, args.beta, args.C, args.ldc, s);
-  }
-};
-
 template <int TM, int TN, int TK, int WM, int WN, bool X3>
 struct Bf16Config {
   static constexpr int kThreads = (TM / WM) * (TN / WN) * kWave;
@@ -170,9 +108,83 @@ struct Bf16Config {
 
 // Tiles of KW k groups (TK = KW sub-slabs of SUB): a wave computes a WM x WN
 // block of its group and, after the groups' sum, owns WM / KW of its rows.
+
+// The DMA-fed loops for any size and alignment (mfma_f32_any.hpp,
+// mfma_bf16_any.hpp): TK deep sub-slabs, KW of them per slab, NST stages.  It replaced register-staged
+// loops of the same tiles, which loaded one slab ahead (and element by
+// element where an operand was not 16-byte aligned) and waited a memory
+// round trip for nearly every slab: 1000 x 1003 x 777, 64 x 64 tiles, 21.6 us
+// against 56; 512 x 4096 x 1024 38.5 against 47 (54 under a profiler); BF16
+// 1500 x 1100 x 900, 64 x 128 tiles, 17.7 against 30.6.
+template <int PREC, int TM, int TN, int TK, int WM, int WN, int NST, int KW>
+struct AnyConfig {
+  template <bool AT, bool BT>
+  using Shape = AnyShape<TM, TN, TK, WM, WN, AT, BT, NST, KW>;
+  static constexpr int kThreads = Shape<false, false>::kThreads;
+  static constexpr int64_t kLdsBytes = Shape<false, false>::kLdsBytes;
+  template <bool AT, bool BT, int MODE>
+  static hipError_t run(const GemmArgs& args, int splits, hipStream_t s) {
+    GemmArgs a = args;
+    a.tiles_m = (a.m + TM - 1) / TM;
+    a.tiles_n = (a.n + TN - 1) / TN;
+    F32DmaOut o{};
+    o.splits = splits;
+    void* kargs[] = {&a, &o};
+    void (*fn)(GemmArgs, F32DmaOut);
+    if constexpr (PREC == HPVM_PREC_FP32) fn = &sgemm_f32_any<TM, TN, TK, WM, WN, AT, BT, NST, KW, MODE>;
+    else fn = &sgemm_bf16_any<TM, TN, TK, WM, WN, AT, BT, NST, KW, PREC == HPVM_PREC_BF16X3, MODE>;
+    hipError_t e = allow_lds(fn, (size_t)kLdsBytes);
+    if (e != hipSuccess) return e;
+    return hipLaunchKernel(reinterpret_cast<const void*>(fn), dim3((unsigned)(a.tiles_m * a.tiles_n * splits)),
+                           dim3(kThreads), kargs, (size_t)kLdsBytes, s);
+  }
+  static hipError_t launch(const GemmArgs& a, bool at, bool bt, hipStream_t s) {
+    if (at && bt) return hipErrorInvalidValue;
+    if (!f32_any_fits(a, at, bt)) {
+      if constexpr (PREC == HPVM_PREC_FP32) return F32Config<64, 64, 16, 32, 32>::launch(a, at, bt, s);
+      else return Bf16Config<64, 64, 32, 32, 32, PREC == HPVM_PREC_BF16X3>::launch(a, at, bt, s);
+    }
+    return at   ? run<true, false, kDmaUpdate>(a, 1, s)
+           : bt ? run<false, true, kDmaUpdate>(a, 1, s)
+                : run<false, false, kDmaUpdate>(a, 1, s);
+  }
+  // Contraction slices of a product whose tiles would leave CUs idle (any
+  // sizes): doubled while they would, each at least 256 deep, at most 16.
+  // FP32, 32 x 32 tiles: up to one workgroup a CU, from k = 2048 on, where
+  // the shorter slices save more than the summing launch costs, about 5 us
+  // (16 x 4096 x 4096: 128 tiles, 27 us whole, 16 in two slices;
+  // 64 x 64 x 4096: 4 tiles, 25 us whole, 7 in 16 slices).  BF16 and bf16x3,
+  // 32 x 128 tiles: up to two a CU, from k = 1024 on (16 x 4096 x 4096: 32
+  // tiles, 40 us whole, 15.4 in eight or sixteen slices).
+  static int splits(int64_t m, int64_t n, int64_t k) {
+    constexpr bool f32 = PREC == HPVM_PREC_FP32;
+    if (m <= 0 || n < 4 || k < (f32 ? 2048 : 1024)) return 1;
+    const int64_t tiles = ((m + TM - 1) / TM) * ((n + TN - 1) / TN);
+    int sp = 1;
+    while (sp < 16 && tiles * sp < (f32 ? 256 : 512) && k / (2 * sp) >= 256) sp *= 2;
+    return sp;
+  }
+  static int64_t split_bytes(int64_t m, int64_t n, int64_t k) {
+    const int sp = splits(m, n, k);
+    return sp > 1 ? (int64_t)sp * m * n * (int64_t)sizeof(float) : 0;
+  }
+  static hipError_t launch_split(const GemmArgs& args, void* workspace, hipStream_t s) {
+    const int sp = splits(args.m, args.n, args.k);
+    if (sp <= 1 || !f32_any_fits(args, false, false)) return launch(args, false, false, s);
+    float* part = static_cast<float*>(workspace);
+    GemmArgs a = args;
+    a.C = part;
+    a.ldc = a.n;
+    a.beta = 0.0f;
+    hipError_t e = run<false, false, kDmaSplit>(a, sp, s);
+    if (e != hipSuccess) return e;
+    return launch_split_finish(part, sp, args.m, args.n, args.alpha, args.beta, args.C, args.ldc, s);
+  }
+};
+
 #define HPVM_F32_ENTRY(TM, TN, TK, WM, WN, SUB, NST, KW)                                                \
-  {{TM, TN, TK, WM / KW, WN, 2}, HPVM_PREC_FP32, F32AnyConfig<TM, TN, SUB, WM, WN, NST, KW>::kThreads,       \
-   F32AnyConfig<TM, TN, SUB, WM, WN, NST, KW>::kLdsBytes, &F32AnyConfig<TM, TN, SUB, WM, WN, NST, KW>::launch}
+  {{TM, TN, TK, WM / KW, WN, 2}, HPVM_PREC_FP32, AnyConfig<HPVM_PREC_FP32, TM, TN, SUB, WM, WN, NST, KW>::kThreads,       \
+   AnyConfig<HPVM_PREC_FP32, TM, TN, SUB, WM, WN, NST, KW>::kLdsBytes, &AnyConfig<HPVM_PREC_FP32, TM, TN, SUB, WM, WN, NST, KW>::launch}
 
 // C <- alpha * (slice 0 + ... + slice splits-1) + beta * C, the slices
 // summed in order, from partial sums [splits][m][n]; beta == 0 never reads
@@ -233,7 +245,7 @@ struct F32DmaConfig {
   static constexpr int kThreads = S::NW * kWave;
   static hipError_t launch(const GemmArgs& args, bool at, bool bt, hipStream_t s) {
     if (at || bt || !f32_dma_fits_edges<TM, TN, TK>(args, args.C, args.ldc))
-      return F32AnyConfig<64, 128, 32, 32, 64, 2, 1>::launch(args, at, bt, s);
+      return AnyConfig<HPVM_PREC_FP32, 64, 128, 32, 32, 64, 2, 1>::launch(args, at, bt, s);
     GemmArgs a = args;
     a.tiles_m = (a.m + TM - 1) / TM;
     a.tiles_n = (a.n + TN - 1) / TN;
@@ -304,10 +316,10 @@ struct F32DmaConfig {
    &F32DmaConfig<TM, TN, TK, WM, NST>::launch_split}
 
 #define HPVM_F32_SPLIT_ENTRY(TM, TN, TK, WM, WN, SUB, NST, KW)                                          \
-  {{TM, TN, TK, WM / KW, WN, 2}, HPVM_PREC_FP32, F32AnyConfig<TM, TN, SUB, WM, WN, NST, KW>::kThreads,  \
-   F32AnyConfig<TM, TN, SUB, WM, WN, NST, KW>::kLdsBytes, &F32AnyConfig<TM, TN, SUB, WM, WN, NST, KW>::launch, \
-   nullptr, nullptr, nullptr, &F32AnyConfig<TM, TN, SUB, WM, WN, NST, KW>::split_bytes,                  \
-   &F32AnyConfig<TM, TN, SUB, WM, WN, NST, KW>::launch_split}
+  {{TM, TN, TK, WM / KW, WN, 2}, HPVM_PREC_FP32, AnyConfig<HPVM_PREC_FP32, TM, TN, SUB, WM, WN, NST, KW>::kThreads,  \
+   AnyConfig<HPVM_PREC_FP32, TM, TN, SUB, WM, WN, NST, KW>::kLdsBytes, &AnyConfig<HPVM_PREC_FP32, TM, TN, SUB, WM, WN, NST, KW>::launch, \
+   nullptr, nullptr, nullptr, &AnyConfig<HPVM_PREC_FP32, TM, TN, SUB, WM, WN, NST, KW>::split_bytes,                  \
+   &AnyConfig<HPVM_PREC_FP32, TM, TN, SUB, WM, WN, NST, KW>::launch_split}
 
 // Entry 0 is the default for large problems.  The stages of the entries on
 // the loop for any size: 24 to 64 KB of slabs, alike in time however they
@@ -329,23 +341,32 @@ static const MfmaEntry kF32Menu[] = {
     HPVM_F32_SPLIT_ENTRY(32, 32, 128, 32, 32, 32, 2, 4),
 };
 
-#define HPVM_BF16_ENTRY(PREC, X3, TM, TN, TK, WM, WN)                                    \
-  {{TM, TN, TK, WM, WN, 2}, PREC, Bf16Config<TM, TN, TK, WM, WN, X3>::kThreads,           \
-   Bf16Config<TM, TN, TK, WM, WN, X3>::lds(false, false), &Bf16Config<TM, TN, TK, WM, WN, X3>::launch}
+// BF16 and bf16x3 entries on the loop for any size.
+#define HPVM_BF16_ENTRY(PREC, TM, TN, TK, WM, WN, SUB, NST)                                               \
+  {{TM, TN, TK, WM, WN, 2}, PREC, AnyConfig<PREC, TM, TN, SUB, WM, WN, NST, 1>::kThreads,                 \
+   AnyConfig<PREC, TM, TN, SUB, WM, WN, NST, 1>::kLdsBytes, &AnyConfig<PREC, TM, TN, SUB, WM, WN, NST, 1>::launch}
+#define HPVM_BF16_SPLIT_ENTRY(PREC, TM, TN, TK, WM, WN, SUB, NST)                                         \
+  {{TM, TN, TK, WM, WN, 2}, PREC, AnyConfig<PREC, TM, TN, SUB, WM, WN, NST, 1>::kThreads,                 \
+   AnyConfig<PREC, TM, TN, SUB, WM, WN, NST, 1>::kLdsBytes, &AnyConfig<PREC, TM, TN, SUB, WM, WN, NST, 1>::launch, \
+   nullptr, nullptr, nullptr, &AnyConfig<PREC, TM, TN, SUB, WM, WN, NST, 1>::split_bytes,                  \
+   &AnyConfig<PREC, TM, TN, SUB, WM, WN, NST, 1>::launch_split}
 
 // BF16 / bf16x3 products on the FP32 DMA-fed loop (mfma_bf16_dma.hpp):
 // problems of at least one tile each way with k a multiple of the slab, n a
 // multiple of 4 and 16-byte rows, no transposed operand (edge tiles moved
-// inward as in the FP32 loop); any other problem takes the register-staged
-// tile of the same size (FM x FN x 32 with FWM x FWN waves).  The split
+// inward as in the FP32 loop); any other problem takes the loop for any
+// size, on 128 x 256 tiles (64 x 128 for the 128 x 128 entry).  The split
 // contraction is the FP32 entries' (same slice rule, same ordered sum).
-template <int TM, int TN, int TK, int WM, int WN, int NST, bool X3, int FWM, int FWN>
+template <int TM, int TN, int TK, int WM, int WN, int NST, bool X3>
 struct Bf16SrcConfig {
   using S = Bf16SrcShape<TM, TN, TK, WM, WN, false, false, NST>;
+  static constexpr int kPrec = X3 ? HPVM_PREC_BF16X3 : HPVM_PREC_BF16;
+  using Other = typename std::conditional<(TM > 128), AnyConfig<kPrec, 128, 256, 32, 64, 64, 3, 1>,
+                                          AnyConfig<kPrec, 64, 128, 32, 32, 64, 3, 1>>::type;
   static constexpr int kThreads = S::NW * kWave;
   static hipError_t launch(const GemmArgs& args, bool at, bool bt, hipStream_t s) {
     if (at || bt || !f32_dma_fits_edges<TM, TN, TK>(args, args.C, args.ldc))
-      return Bf16Config<TM, TN, 32, FWM, FWN, X3>::launch(args, at, bt, s);
+      return Other::launch(args, at, bt, s);
     GemmArgs a = args;
     a.tiles_m = (a.m + TM - 1) / TM;
     a.tiles_n = (a.n + TN - 1) / TN;
@@ -393,41 +414,46 @@ struct Bf16SrcConfig {
   }
 };
 
-#define HPVM_BF16SRC_ENTRY(PREC, X3, TM, TN, TK, WM, WN, NST, FWM, FWN)                                    \
-  {{TM, TN, TK, WM, WN, NST}, PREC, Bf16SrcConfig<TM, TN, TK, WM, WN, NST, X3, FWM, FWN>::kThreads,         \
-   Bf16SrcConfig<TM, TN, TK, WM, WN, NST, X3, FWM, FWN>::S::kLdsBytes,                                       \
-   &Bf16SrcConfig<TM, TN, TK, WM, WN, NST, X3, FWM, FWN>::launch,                                            \
+#define HPVM_BF16SRC_ENTRY(PREC, X3, TM, TN, TK, WM, WN, NST)                                    \
+  {{TM, TN, TK, WM, WN, NST}, PREC, Bf16SrcConfig<TM, TN, TK, WM, WN, NST, X3>::kThreads,         \
+   Bf16SrcConfig<TM, TN, TK, WM, WN, NST, X3>::S::kLdsBytes,                                       \
+   &Bf16SrcConfig<TM, TN, TK, WM, WN, NST, X3>::launch,                                            \
    nullptr,                                                                                                   \
    nullptr,                                                                                                   \
    nullptr,                                                                                                   \
-   &Bf16SrcConfig<TM, TN, TK, WM, WN, NST, X3, FWM, FWN>::split_bytes,                                       \
-   &Bf16SrcConfig<TM, TN, TK, WM, WN, NST, X3, FWM, FWN>::launch_split}
+   &Bf16SrcConfig<TM, TN, TK, WM, WN, NST, X3>::split_bytes,                                       \
+   &Bf16SrcConfig<TM, TN, TK, WM, WN, NST, X3>::launch_split}
 
-// Entry 0 is the default when no tile is given: BF16 and bf16x3 on the
-// DMA-fed loop, falling back to the register-staged 256 x 256 x 32 tile.
+// Entry 0 is the default for large products.
 // bf16x3 takes 16-deep slabs in 4 stages first (8192^3: 2.65 ms against
 // 2.87 for 32-deep slabs in 2 stages), BF16 32-deep slabs in 2 stages
 // (8192^3: 1.46 ms against 1.51, 4096^3: 0.167 against 0.176; a fifth
 // 16-deep stage, all 160 KB of LDS, gave 1.45).
 static const MfmaEntry kBf16Menu[] = {
-    HPVM_BF16SRC_ENTRY(HPVM_PREC_BF16, false, 256, 256, 32, 64, 128, 2, 128, 64),
-    HPVM_BF16SRC_ENTRY(HPVM_PREC_BF16, false, 256, 256, 16, 64, 128, 4, 128, 64),
-    HPVM_BF16SRC_ENTRY(HPVM_PREC_BF16, false, 128, 128, 32, 64, 64, 4, 64, 64),
-    HPVM_BF16_ENTRY(HPVM_PREC_BF16, false, 256, 256, 32, 128, 64),
-    HPVM_BF16_ENTRY(HPVM_PREC_BF16, false, 256, 128, 32, 128, 64),
-    HPVM_BF16_ENTRY(HPVM_PREC_BF16, false, 128, 128, 32, 64, 64),
-    HPVM_BF16_ENTRY(HPVM_PREC_BF16, false, 128, 128, 64, 64, 64),
-    HPVM_BF16_ENTRY(HPVM_PREC_BF16, false, 64, 64, 32, 32, 32),
+    HPVM_BF16SRC_ENTRY(HPVM_PREC_BF16, false, 256, 256, 32, 64, 128, 2),
+    HPVM_BF16SRC_ENTRY(HPVM_PREC_BF16, false, 256, 256, 16, 64, 128, 4),
+    HPVM_BF16SRC_ENTRY(HPVM_PREC_BF16, false, 128, 128, 32, 64, 64, 4),
+    HPVM_BF16_ENTRY(HPVM_PREC_BF16, 256, 256, 32, 128, 64, 16, 4),
+    HPVM_BF16_ENTRY(HPVM_PREC_BF16, 256, 128, 32, 128, 64, 32, 3),
+    HPVM_BF16_ENTRY(HPVM_PREC_BF16, 128, 128, 32, 64, 64, 32, 2),
+    HPVM_BF16_ENTRY(HPVM_PREC_BF16, 128, 128, 64, 64, 64, 32, 4),
+    HPVM_BF16_ENTRY(HPVM_PREC_BF16, 64, 64, 32, 32, 32, 32, 3),
+    HPVM_BF16_ENTRY(HPVM_PREC_BF16, 64, 128, 32, 32, 64, 32, 3),
+    HPVM_BF16_ENTRY(HPVM_PREC_BF16, 128, 256, 32, 64, 64, 32, 3),
+    HPVM_BF16_SPLIT_ENTRY(HPVM_PREC_BF16, 32, 128, 32, 32, 32, 32, 4),
 };
 
 static const MfmaEntry kBf16x3Menu[] = {
-    HPVM_BF16SRC_ENTRY(HPVM_PREC_BF16X3, true, 256, 256, 16, 128, 128, 4, 128, 64),
-    HPVM_BF16SRC_ENTRY(HPVM_PREC_BF16X3, true, 256, 256, 32, 128, 128, 2, 128, 64),
-    HPVM_BF16SRC_ENTRY(HPVM_PREC_BF16X3, true, 128, 128, 32, 64, 64, 4, 64, 64),
-    HPVM_BF16_ENTRY(HPVM_PREC_BF16X3, true, 256, 256, 32, 128, 64),
-    HPVM_BF16_ENTRY(HPVM_PREC_BF16X3, true, 256, 128, 32, 128, 64),
-    HPVM_BF16_ENTRY(HPVM_PREC_BF16X3, true, 128, 128, 32, 64, 64),
-    HPVM_BF16_ENTRY(HPVM_PREC_BF16X3, true, 64, 64, 32, 32, 32),
+    HPVM_BF16SRC_ENTRY(HPVM_PREC_BF16X3, true, 256, 256, 16, 128, 128, 4),
+    HPVM_BF16SRC_ENTRY(HPVM_PREC_BF16X3, true, 256, 256, 32, 128, 128, 2),
+    HPVM_BF16SRC_ENTRY(HPVM_PREC_BF16X3, true, 128, 128, 32, 64, 64, 4),
+    HPVM_BF16_ENTRY(HPVM_PREC_BF16X3, 256, 256, 32, 128, 64, 16, 4),
+    HPVM_BF16_ENTRY(HPVM_PREC_BF16X3, 256, 128, 32, 128, 64, 32, 3),
+    HPVM_BF16_ENTRY(HPVM_PREC_BF16X3, 128, 128, 32, 64, 64, 32, 2),
+    HPVM_BF16_ENTRY(HPVM_PREC_BF16X3, 64, 64, 32, 32, 32, 32, 3),
+    HPVM_BF16_ENTRY(HPVM_PREC_BF16X3, 64, 128, 32, 32, 64, 32, 3),
+    HPVM_BF16_ENTRY(HPVM_PREC_BF16X3, 128, 256, 32, 64, 64, 32, 3),
+    HPVM_BF16_SPLIT_ENTRY(HPVM_PREC_BF16X3, 32, 128, 32, 32, 32, 32, 4),
 };
 
 int mfma_menu(int32_t prec, const MfmaEntry** entries) {
