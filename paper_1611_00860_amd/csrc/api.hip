@@ -177,6 +177,8 @@ namespace hpvm {
 //   32 x 32 in four: 512^3 8.5, 7.6; 256 x 256 x 8192 46, 47;
 //             100 x 3000 x 1500 20.5, 19.5
 // A split contraction adds the summing launch and the partial sums' traffic.
+// The 256 x 256 tile, alone too large to run beside an open streaming graph
+// (128 KB of LDS), is taken only when it gives a tile per CU.
 bool f32_default_tile(int64_t m, int64_t n, int64_t k, int64_t split_ws, hpvm_tile* out) {
   struct Candidate {
     hpvm_tile tile;
@@ -193,6 +195,7 @@ bool f32_default_tile(int64_t m, int64_t n, int64_t k, int64_t split_ws, hpvm_ti
   for (const Candidate& c : kCandidates) {
     const hpvm_tile& t = c.tile;
     if (c.aligned && (m < t.tile_m || n < t.tile_n || n % 4 || k % t.tile_k)) continue;
+    if (t.tile_m == 256 && tiles_of(t, m, n) < 256) continue;
     const MfmaEntry* e = find_menu_entry(HPVM_PREC_FP32, t);
     if (!e) continue;
     int64_t slices = 1;
@@ -220,19 +223,24 @@ bool f32_default_tile(int64_t m, int64_t n, int64_t k, int64_t split_ws, hpvm_ti
 //   128 x 128 (4 stages): 2048^3 53, 55
 //   128 x 256: 3000 x 2500 x 2000 57, 57; bf16x3 115, 106 to 118
 //   256 x 256: 8192^3 1486, 1480; bf16x3 2658, 2650
+// The tiles that need most of a CU's LDS or registers, and so cannot run
+// beside an open streaming graph, are taken only when they give a tile per
+// CU or the smaller ones need more rounds; bf16x3's 64 x 128 (192 registers;
+// 27 us against 29 at 1500 x 1100 x 900) not at all.
 static bool bf16_default_tile(int32_t prec, int64_t m, int64_t n, int64_t k, int64_t split_ws, hpvm_tile* out,
                               double* estimate = nullptr, bool large_only = false) {
   const bool x3 = prec == HPVM_PREC_BF16X3;
   struct Candidate {
     hpvm_tile tile;
-    double slab, slab_x3;  // us
+    double slab, slab_x3;  // us; 0: left out
     bool aligned;          // only where its own loop runs (mfma_bf16_dma.hpp)
   };
+  if (!menu_entry_at(prec, 0)) return false;
   const Candidate kCandidates[] = {
       {menu_entry_at(prec, 0)->tile, 1.445, 2.59, true},
-      {{128, 256, 32, 64, 64, 2}, 0.82, 1.75, false},
+      {{128, 256, 32, 64, 64, 2}, 0.83, 1.77, false},
       {{128, 128, 32, 64, 64, 4}, 0.73, 1.20, true},
-      {{64, 128, 32, 32, 64, 2}, 0.41, 0.71, false},
+      {{64, 128, 32, 32, 64, 2}, 0.41, 0.0, false},
       {{64, 64, 32, 32, 32, 2}, 0.28, 0.44, false},
       {{32, 128, 32, 32, 32, 2}, 0.29, 0.46, false},
   };
@@ -240,8 +248,8 @@ static bool bf16_default_tile(int32_t prec, int64_t m, int64_t n, int64_t k, int
   bool found = false;
   for (const Candidate& c : kCandidates) {
     const hpvm_tile& t = c.tile;
-    if (c.aligned && (m < t.tile_m || n < t.tile_n || n % 4 || k % t.tile_k)) continue;
-    if (large_only && t.tile_m * t.tile_n < 128 * 256) continue;
+    if (c.aligned && (m < t.tile_m || n < t.tile_n || n % 4 || k % t.tile_k || tiles_of(t, m, n) < 256)) continue;
+    if ((large_only && t.tile_m * t.tile_n < 128 * 256) || (x3 ? c.slab_x3 : c.slab) == 0.0) continue;
     const MfmaEntry* e = find_menu_entry(prec, t);
     if (!e) continue;
     int64_t slices = 1;

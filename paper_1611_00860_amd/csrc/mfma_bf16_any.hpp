@@ -118,11 +118,16 @@ struct MathBf16 {
   }
 };
 
+// The smaller waves keep to a third of a SIMD's registers (see
+// F32DmaShape::kMinWaves); bf16x3's hi and lo parts leave that to 32 x 32.
+template <int WM, int WN, bool X3>
+constexpr int kBf16AnyMinWaves = WM * WN <= (X3 ? 32 * 32 : 32 * 64) ? 3 : 1;
+
 // One launch: a workgroup per tile and contraction slice (slice-major),
 // XCD-aware tile order.
 template <int TM, int TN, int TK, int WM, int WN, bool AT, bool BT, int NST, int KW, bool X3, int MODE>
 __global__ void __launch_bounds__((AnyShape<TM, TN, TK, WM, WN, AT, BT, NST, KW>::kThreads))
-    sgemm_bf16_any(GemmArgs p, F32DmaOut o) {
+    __attribute__((amdgpu_waves_per_eu(kBf16AnyMinWaves<WM, WN, X3>))) sgemm_bf16_any(GemmArgs p, F32DmaOut o) {
   extern __shared__ __align__(16) char smem[];
   using S = AnyShape<TM, TN, TK, WM, WN, AT, BT, NST, KW>;
   const int tiles = p.tiles_m * p.tiles_n;

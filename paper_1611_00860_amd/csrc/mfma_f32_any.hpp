@@ -22,6 +22,8 @@
 // other FP32 lowering.
 #pragma once
 
+#include <type_traits>
+
 #include "device_common.hpp"
 #include "hpvm_sgemm.h"
 #include "lds_dma.hpp"
@@ -135,6 +137,10 @@ struct AnyOperand {
   }
   // Row or column of block b's element x for a wave starting at w0.
   __device__ static int index(int b, int x, int w0) { return KC ? w0 + 32 * b + x : w0 + V * x + b; }
+  // The A side's row of accumulator register r is row(a, r, w0) (uniform)
+  // plus lane_row(lane).
+  __device__ static int row(int b, int r, int w0) { return index(b, acc_row(r, 0), w0); }
+  __device__ static int lane_row(int lane) { return (KC ? 4 : 4 * V) * (lane >> 5); }
 };
 
 template <int TM, int TN, int TK, int WM, int WN, bool AT, bool BT, int NST, int KW>
@@ -148,6 +154,9 @@ struct AnyShape {
   // A group's waves move that group's sub-slab.
   static constexpr int QA = OA::kDma / NWT, QB = OB::kDma / NWT, Q = QA + QB;
   static constexpr int kSlab = KW * TK;
+  // Four FP32 waves of up to 64 x 64 keep to a third of a SIMD's registers
+  // (see F32DmaShape::kMinWaves), eight of 32 x 32 to a sixth.
+  static constexpr int kMinWaves = WM * WN > 64 * 64 ? 1 : NW == 4 ? 3 : NW == 8 && WM * WN <= 32 * 32 ? 6 : 1;
   static constexpr int kTm = TM, kTn = TN, kTk = TK, kWm = WM, kWn = WN, kNst = NST, kKw = KW;
   static constexpr bool kAt = AT, kBt = BT;
   static_assert(TM % WM == 0 && TN % WN == 0, "wave tiles");
@@ -178,7 +187,7 @@ __device__ __forceinline__ void wait_slabs_barrier(int slabs) {
 // Outputs of the accumulators' row quads [q0, q1) (quad g of block a: the
 // rows acc_row(4 g .. 4 g + 3)).  m_own, n_own: the tile's place in the
 // tile grid; only rows in [m_own, m) and columns in [n_own, n) are stored.
-template <typename OA, typename OB, bool BT, int MODE, int NA, int NB>
+template <typename OA, typename OB, bool BT, int MODE, int BATCH = 32, int NA, int NB>
 __device__ __forceinline__ void any_epilogue(const GemmArgs& q, const F32DmaOut& o, const f32x16 (&acc)[NA][NB],
                                              int m0, int n0, int m_own, int n_own, bool whole, int wm0, int wn0,
                                              int lane, int z, int q0, int q1) {
@@ -191,6 +200,9 @@ __device__ __forceinline__ void any_epilogue(const GemmArgs& q, const F32DmaOut&
   constexpr int V = BT ? 1 : NB;  // adjacent outputs a lane holds
   using Vec = typename LooseF<V>::type;
   const int I = lane & 31;
+  // An output's address is its row's (uniform) plus the lane's 32-bit byte
+  // offset, so that no address is held per row.
+  const int lrow = OA::lane_row(lane);
   auto at = [](const Vec& v, int e) -> float {
     if constexpr (V == 1) return v;
     else return v[e];
@@ -199,58 +211,72 @@ __device__ __forceinline__ void any_epilogue(const GemmArgs& q, const F32DmaOut&
     if constexpr (V == 1) v = x;
     else v[e] = x;
   };
+  // Up to BATCH elements of C per lane are loaded before any of their outputs
+  // is stored (see store_c).
+  constexpr int kRows = BATCH / V < 16 ? BATCH / V : 16;  // of a block
+  constexpr int kBatch = NA * 16 * V <= BATCH ? NA : BATCH / (16 * V) > 0 ? BATCH / (16 * V) : 1;
+  auto store = [&](auto all) {
+    constexpr bool kAll = decltype(all)::value;  // the tile owns all its outputs
 #pragma unroll
-  for (int b0 = 0; b0 < NB; b0 += V) {
-    const int col = n0 + OB::index(b0, I, wn0);
-    Vec bias{};
-    if constexpr (MODE == kDmaConsume) {
-      if (o.op == HPVM_CONSUMER_BIAS || o.op == HPVM_CONSUMER_BIAS_RELU) {
+    for (int b0 = 0; b0 < NB; b0 += V) {
+      const int col = n0 + OB::index(b0, I, wn0);
+      const uint32_t coff = (uint32_t)((lrow * q.ldc + col) * 4), ooff = (uint32_t)((lrow * ldo + col) * 4);
+      Vec bias{};
+      if constexpr (MODE == kDmaConsume) {
+        if (o.op == HPVM_CONSUMER_BIAS || o.op == HPVM_CONSUMER_BIAS_RELU) {
 #pragma unroll
-        for (int e = 0; e < V; ++e) put(bias, e, col + e < q.n ? o.bias[col + e] : 0.0f);
+          for (int e = 0; e < V; ++e) put(bias, e, col + e < q.n ? o.bias[col + e] : 0.0f);
+        }
+      }
+#pragma unroll
+      for (int ar = 0; ar < NA * 16; ar += kBatch * kRows) {
+        const int a0 = ar / 16, r0 = ar % 16;
+        Vec c[kBatch][kRows];
+        if (read_c) {
+#pragma unroll
+          for (int a = 0; a < kBatch; ++a)
+#pragma unroll
+            for (int r = 0; r < kRows; ++r) {
+              if (a0 + a >= NA || (r0 + r) / 4 < q0 || (r0 + r) / 4 >= q1) continue;
+              const int urow = m0 + OA::row(a0 + a, r0 + r, wm0);
+              if constexpr (kAll) {
+                c[a][r] = *reinterpret_cast<const Vec*>(
+                    reinterpret_cast<const char*>(cin + (int64_t)urow * q.ldc) + coff);
+              } else {  // past the edge: some element of C, not used
+                const float* p = cin + (int64_t)(urow + lrow < q.m ? urow + lrow : q.m - 1) * q.ldc;
+#pragma unroll
+                for (int e = 0; e < V; ++e) put(c[a][r], e, p[col + e < q.n ? col + e : q.n - 1]);
+              }
+            }
+        }
+#pragma unroll
+        for (int a = 0; a < kBatch; ++a)
+#pragma unroll
+          for (int r = 0; r < kRows; ++r) {
+            if (a0 + a >= NA || (r0 + r) / 4 < q0 || (r0 + r) / 4 >= q1) continue;
+            const int urow = m0 + OA::row(a0 + a, r0 + r, wm0), row = urow + lrow;
+            Vec v{};
+#pragma unroll
+            for (int e = 0; e < V; ++e) {
+              float x = alpha * acc[a0 + a][b0 + e][r0 + r];
+              if (read_c) x = fmaf(q.beta, at(c[a][r], e), x);
+              if constexpr (MODE == kDmaConsume) x = consume_op(o.op, x, at(bias, e), o.lo, o.hi);
+              put(v, e, x);
+            }
+            float* p = reinterpret_cast<float*>(reinterpret_cast<char*>(out + (int64_t)urow * ldo) + ooff);
+            if constexpr (kAll) {
+              *reinterpret_cast<Vec*>(p) = v;
+            } else if (row >= m_own && row < q.m) {
+#pragma unroll
+              for (int e = 0; e < V; ++e)
+                if (col + e >= n_own && col + e < q.n) p[e] = at(v, e);
+            }
+          }
       }
     }
-#pragma unroll
-    for (int a = 0; a < NA; ++a)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        if (g < q0 || g >= q1) continue;
-        Vec c[4];
-        int row[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          row[u] = m0 + OA::index(a, acc_row(4 * g + u, lane), wm0);
-          c[u] = Vec{};
-          if (!read_c) continue;
-          const float* p = cin + (int64_t)row[u] * q.ldc + col;
-          if (whole) {
-            c[u] = *reinterpret_cast<const Vec*>(p);
-          } else if (row[u] >= m_own && row[u] < q.m) {
-#pragma unroll
-            for (int e = 0; e < V; ++e)
-              if (col + e >= n_own && col + e < q.n) put(c[u], e, p[e]);
-          }
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          Vec v{};
-#pragma unroll
-          for (int e = 0; e < V; ++e) {
-            float x = alpha * acc[a][b0 + e][4 * g + u];
-            if (read_c) x = fmaf(q.beta, at(c[u], e), x);
-            if constexpr (MODE == kDmaConsume) x = consume_op(o.op, x, at(bias, e), o.lo, o.hi);
-            put(v, e, x);
-          }
-          float* p = out + (int64_t)row[u] * ldo + col;
-          if (whole) {
-            *reinterpret_cast<Vec*>(p) = v;
-          } else if (row[u] >= m_own && row[u] < q.m) {
-#pragma unroll
-            for (int e = 0; e < V; ++e)
-              if (col + e >= n_own && col + e < q.n) p[e] = at(v, e);
-          }
-        }
-      }
-  }
+  };
+  if (whole) store(std::true_type{});
+  else store(std::false_type{});
 }
 
 // The arithmetic of one wave on staged sub-slabs: kSteps steps per sub-slab
@@ -461,7 +487,7 @@ __device__ __forceinline__ void f32_any_tile(const GemmArgs& p, int splits, int 
 // XCD-aware tile order.
 template <int TM, int TN, int TK, int WM, int WN, bool AT, bool BT, int NST, int KW, int MODE>
 __global__ void __launch_bounds__((AnyShape<TM, TN, TK, WM, WN, AT, BT, NST, KW>::kThreads))
-    sgemm_f32_any(GemmArgs p, F32DmaOut o) {
+    __attribute__((amdgpu_waves_per_eu((AnyShape<TM, TN, TK, WM, WN, AT, BT, NST, KW>::kMinWaves)))) sgemm_f32_any(GemmArgs p, F32DmaOut o) {
   extern __shared__ __align__(16) char smem[];
   using S = AnyShape<TM, TN, TK, WM, WN, AT, BT, NST, KW>;
   const int tiles = p.tiles_m * p.tiles_n;
@@ -477,12 +503,15 @@ __global__ void __launch_bounds__((AnyShape<TM, TN, TK, WM, WN, AT, BT, NST, KW>
       });
 }
 
+// Row pitch (floats) up to which a tile's rows lie within 32-bit byte offsets
+// of its corner (at most 256 rows of an operand).
+constexpr int64_t kAnyPitch = 1 << 22;
+
 // True when the loop covers the product: something to contract, MN
-// operands at least one 16-byte unit wide, and a tile's rows within 32-bit
-// byte offsets of its corner (at most 256 rows of either operand).
+// operands at least one 16-byte unit wide, and pitches within kAnyPitch.
 inline bool f32_any_fits(const GemmArgs& a, bool at, bool bt) {
-  return a.m > 0 && a.n > 0 && a.k > 0 && a.m < (1 << 30) && a.n < (1 << 30) && (!at || a.m >= 4) && (bt || a.n >= 4) && a.lda < (1 << 22) &&
-         a.ldb < (1 << 22);
+  return a.m > 0 && a.n > 0 && a.k > 0 && a.m < (1 << 30) && a.n < (1 << 30) && (!at || a.m >= 4) && (bt || a.n >= 4) &&
+         a.lda < kAnyPitch && a.ldb < kAnyPitch && a.ldc < kAnyPitch;
 }
 
 }  // namespace hpvm

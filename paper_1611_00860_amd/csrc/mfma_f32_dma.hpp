@@ -113,6 +113,10 @@ struct F32DmaShape {
   static constexpr int64_t kLdsBytes = (int64_t)NST * kStage;
   static constexpr int QA = OA::kDma / NW, QB = kOuts * OB::kDma / NW, Q = QA + QB;
   static constexpr int kMaxWaves = (163840 / (NST * kStage)) * NW / 4;
+  // 128 x 128 tiles of four waves keep to a third of a SIMD's registers: two
+  // resident workgroups of a streaming graph leave that much, and smaller
+  // products must be able to run beside one.
+  static constexpr int kMinWaves = (NW == 4 && !PAIR) ? 3 : 1;
   static_assert(TM % WM == 0 && TN % WN == 0, "wave tiles");
   static_assert(QA * NW == OA::kDma && QB * NW == kOuts * OB::kDma, "DMA instructions split evenly over the waves");
   static_assert(!PAIR || (!AT && !BT), "the pair reads A and both B as stored");
@@ -178,36 +182,45 @@ __device__ __forceinline__ void dma_epilogue(const GemmArgs& q, const F32DmaOut&
   const int I = lane & 31;
   if constexpr (!BT) {
     // The NB blocks give a lane NB adjacent outputs of a row: one vector
-    // access per row.  A group of 4 rows loads its C values first.
+    // access per row.  A row's address is the lane's first plus a uniform
+    // multiple of the pitch.
     using VB = typename OB::Frag;
     const int64_t col = n0 + OB::index(0, I, wn0);
+    const int64_t lrow = m0 + OA::index(0, 4 * (lane >> 5), 0);
+    const float* cl = cin + lrow * q.ldc + col;
+    float* ol = out + lrow * ldo + col;
     const bool col_own = !EDGES || col >= n_own;  // the lane's NB columns are owned together (n % 4 == 0)
     VB bias{};
     if constexpr (MODE == kDmaConsume && kBias) {
 #pragma unroll
       for (int b = 0; b < NB; ++b) bias[b] = o.bias[col + b];
     }
+    // Up to 64 elements of C per lane (32 in the smaller wave tiles) are
+    // loaded before any of their outputs is stored (see store_c).
+    constexpr int kBatch = NA * NB >= 8 ? 64 : 32, kRows = kBatch / NB < 16 ? kBatch / NB : 16;
 #pragma unroll
     for (int a = 0; a < NA; ++a)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        VB c[4];
+      for (int r0 = 0; r0 < 16; r0 += kRows) {
+        VB c[kRows];
+        if (read_c) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int64_t i = m0 + OA::index(a, acc_row(4 * g + u, lane), wm0);
-          if (read_c && col_own && (!EDGES || i >= m_own)) c[u] = *reinterpret_cast<const VB*>(cin + i * q.ldc + col);
+          for (int r = 0; r < kRows; ++r) {
+            const int64_t i = OA::index(a, acc_row(r0 + r, 0), wm0);
+            if (col_own && (!EDGES || lrow + i >= m_own)) c[r] = *reinterpret_cast<const VB*>(cl + i * q.ldc);
+          }
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int64_t i = m0 + OA::index(a, acc_row(4 * g + u, lane), wm0);
+        for (int r = 0; r < kRows; ++r) {
+          const int64_t i = OA::index(a, acc_row(r0 + r, 0), wm0);
           VB v;
 #pragma unroll
           for (int b = 0; b < NB; ++b) {
-            v[b] = alpha * acc[a][b][4 * g + u];
-            if (read_c) v[b] = fmaf(q.beta, c[u][b], v[b]);
+            v[b] = alpha * acc[a][b][r0 + r];
+            if (read_c) v[b] = fmaf(q.beta, c[r][b], v[b]);
             if constexpr (MODE == kDmaConsume) v[b] = consume<OP>(v[b], bias[b], o.lo, o.hi);
           }
-          if (col_own && (!EDGES || i >= m_own)) *reinterpret_cast<VB*>(out + i * ldo + col) = v;
+          if (col_own && (!EDGES || lrow + i >= m_own)) *reinterpret_cast<VB*>(ol + i * ldo) = v;
         }
       }
   } else {
@@ -352,7 +365,10 @@ __device__ __forceinline__ void f32_dma_tile(const GemmArgs& p, const GemmArgs& 
 template <int TM, int TN, int TK, int WM, int WN, bool AT, bool BT, int NST, int MODE, int OP = 0,
           bool PAIR = false, bool EDGES = false>
 __global__ void __launch_bounds__((F32DmaShape<TM, TN, TK, WM, WN, AT, BT, NST, PAIR>::NW * kWave))
-    __attribute__((amdgpu_waves_per_eu(1, (F32DmaShape<TM, TN, TK, WM, WN, AT, BT, NST, PAIR>::kMaxWaves))))
+    __attribute__((amdgpu_waves_per_eu((F32DmaShape<TM, TN, TK, WM, WN, AT, BT, NST, PAIR>::kMinWaves),
+                                       (F32DmaShape<TM, TN, TK, WM, WN, AT, BT, NST, PAIR>::kMaxWaves > 3
+                                            ? F32DmaShape<TM, TN, TK, WM, WN, AT, BT, NST, PAIR>::kMaxWaves
+                                            : 3))))
     sgemm_f32_dma(GemmArgs p, GemmArgs p2, F32DmaOut o) {
   extern __shared__ __align__(16) char smem[];
   const int tiles = p.tiles_m * p.tiles_n;

@@ -268,36 +268,37 @@ __global__ void __launch_bounds__(kElemThreads) sgemm_grad_tail(SumJob a, SumJob
 }
 
 // dA's epilogue on the loop for any size: C (may be null) <- alpha acc, and
-// this lane's share of <aorig, acc> over the row quads [q0, q1).  Each quad
+// this lane's share of <aorig, acc> over the row quads [q0, q1).  Each block
 // loads its elements of A before its stores.
 template <typename OA, typename OB, int NA, int NB>
 __device__ __forceinline__ float any_grad_a_epilogue(const GemmArgs& q, const float* __restrict__ aorig, int64_t ldao,
                                                      const f32x16 (&acc)[NA][NB], int m0, int n0, int wm0, int wn0,
                                                      int lane, int q0, int q1) {
   float part = 0.0f;
+  const int lrow = OA::lane_row(lane);
 #pragma unroll
   for (int a = 0; a < NA; ++a)
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
       const int col = n0 + OB::index(b, lane & 31, wn0);
-      if (col >= q.n) continue;
+      const uint32_t aoff = (uint32_t)((lrow * ldao + col) * 4), coff = (uint32_t)((lrow * q.ldc + col) * 4);
+      float x[16];
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        if (g < q0 || g >= q1) continue;
-        float x[4];
+      for (int r = 0; r < 16; ++r) {
+        if (r / 4 < q0 || r / 4 >= q1) continue;
+        const int urow = m0 + OA::row(a, r, wm0);
+        x[r] = col < q.n && urow + lrow < q.m
+                   ? *reinterpret_cast<const float*>(reinterpret_cast<const char*>(aorig + (int64_t)urow * ldao) + aoff)
+                   : 0.0f;
+      }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int row = m0 + OA::index(a, acc_row(4 * g + u, lane), wm0);
-          x[u] = row < q.m ? aorig[(int64_t)row * ldao + col] : 0.0f;
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int row = m0 + OA::index(a, acc_row(4 * g + u, lane), wm0);
-          if (row >= q.m) continue;
-          const float v = acc[a][b][4 * g + u];
-          if (q.C) q.C[(int64_t)row * q.ldc + col] = q.alpha * v;
-          part = fmaf(x[u], v, part);
-        }
+      for (int r = 0; r < 16; ++r) {
+        if (r / 4 < q0 || r / 4 >= q1) continue;
+        const int urow = m0 + OA::row(a, r, wm0);
+        if (col >= q.n || urow + lrow >= q.m) continue;
+        const float v = acc[a][b][r];
+        if (q.C) *reinterpret_cast<float*>(reinterpret_cast<char*>(q.C + (int64_t)urow * q.ldc) + coff) = q.alpha * v;
+        part = fmaf(x[r], v, part);
       }
     }
   return part;
@@ -312,7 +313,7 @@ __device__ __forceinline__ float any_grad_a_epilogue(const GemmArgs& q, const fl
 // loops.
 template <int TM, int TN, int TK, int WM, int WN, int NST, int KW>
 __global__ void __launch_bounds__((AnyShape<TM, TN, TK, WM, WN, false, true, NST, KW>::kThreads))
-    sgemm_grad_any(GemmArgs a, const float* __restrict__ aorig, int64_t ldao, float* __restrict__ partial, GemmArgs b,
+    __attribute__((amdgpu_waves_per_eu((AnyShape<TM, TN, TK, WM, WN, false, true, NST, KW>::kMinWaves)))) sgemm_grad_any(GemmArgs a, const float* __restrict__ aorig, int64_t ldao, float* __restrict__ partial, GemmArgs b,
                    GradCJob c, int32_t tiles_a, int32_t tiles_b) {
   extern __shared__ __align__(16) char smem[];
   using SA = AnyShape<TM, TN, TK, WM, WN, false, true, NST, KW>;
@@ -549,17 +550,21 @@ int64_t split_sum_blocks(int64_t rows, int64_t cols) {
 // tiles one of 256 CUs gets, at least one of the deeper gradient's, their
 // products at the FP32 MFMA rate (614 GFLOP/s a CU) times `load`.  The DMA
 // entry (whole 256 x 256 tiles) adds the launch of its slice sums, about
-// 6 us, and their traffic.
+// 6 us, and their traffic.  dalpha = <A, G B^T> cancels, so how the products
+// are rounded shows in it: the DMA entry's shorter sums are given up, and
+// the k groups of the 32 x 32 tile taken for the others' plain order in k,
+// only where that saves 30% (`worth`; 1024^3 81 -> 43 us;
+// 64 x 4096 x 1000 93 -> 42).
 const BwdEntry* f32_pick(int64_t m, int64_t n, int64_t k) {
   struct Candidate {
     hpvm_tile tile;
-    double start, load;
+    double start, load, worth;
   };
   static const Candidate kCandidates[] = {
-      {{kDmaTile, kDmaTile, kDmaK, kDmaWM, kDmaWN, kDmaStages}, 12.0, 1.05},
-      {{64, 128, 32, 32, 64, 2}, 8.0, 1.12},
-      {{64, 64, 32, 16, 32, 2}, 6.5, 1.15},
-      {{32, 32, 128, 8, 32, 2}, 6.0, 1.45},
+      {{kDmaTile, kDmaTile, kDmaK, kDmaWM, kDmaWN, kDmaStages}, 12.0, 1.05, 0.7},
+      {{64, 128, 32, 32, 64, 2}, 8.0, 1.12, 1.0},
+      {{64, 64, 16, 32, 32, 2}, 7.8, 1.12, 1.0},
+      {{32, 32, 128, 8, 32, 2}, 6.0, 1.45, 1.0 / 0.7},
   };
   const BwdEntry* pick = nullptr;
   double best = 0.0;
@@ -576,7 +581,7 @@ const BwdEntry* f32_pick(int64_t m, int64_t n, int64_t k) {
     const double per_k = 2.0 * c.tile.tile_m * c.tile.tile_n / 614400.0 / slices;
     const double deep = (double)std::max(m, n) * per_k, mean = (ta * n + tb * m) / std::max(ta + tb, 1.0) * per_k;
     const double rounds = (double)(((int64_t)((ta + tb) * slices) + 255) / 256);
-    const double time = c.start + c.load * std::max(rounds * mean, deep) + extra;
+    const double time = c.worth * (c.start + c.load * std::max(rounds * mean, deep) + extra);
     if (!pick || time < best) {
       best = time;
       pick = e;
@@ -1045,7 +1050,7 @@ int hpvm_sgemm_backward(int64_t m, int64_t n, int64_t k, float alpha, float beta
         a_pair = a;  // launched with dB below
       else
         e = me->launch_staged_planes(a, StagedPlanes{P.gh, P.gl, P.bh, P.bl}, A, lda, dalpha ? pa : nullptr, s);
-    } else if (fb->any && f32_any_fits(a, false, true)) {
+    } else if (fb->any && f32_any_fits(a, false, true) && lda < kAnyPitch) {
       any_a = true;
       a_pair = a;
       na = dalpha ? tiles_for(fb->tile, m, k) : 0;

@@ -278,7 +278,8 @@ template <int TM, int TN, int TK, int WM, int WN, int NST, int KW>
 struct ConsumerAnyConfig {
   using S = AnyShape<TM, TN, TK, WM, WN, false, false, NST, KW>;
   static hipError_t launch(const GemmArgs& args, const ConsumerArgs& c, hipStream_t s) {
-    if (!f32_any_fits(args, false, false)) return ConsumerConfig<64, 64, 16, 32, 32>::launch(args, c, s);
+    if (!f32_any_fits(args, false, false) || c.ldd >= kAnyPitch)
+      return ConsumerConfig<64, 64, 16, 32, 32>::launch(args, c, s);
     GemmArgs a = args;
     a.tiles_m = (a.m + TM - 1) / TM;
     a.tiles_n = (a.n + TN - 1) / TN;
