@@ -56,7 +56,13 @@ __global__ void __launch_bounds__(kGroupedThreads) __attribute__((amdgpu_waves_p
     __syncthreads();
     const int t = next_tile;
     __syncthreads();
-    if (t >= total_tiles) break;
+    if (t >= total_tiles) {
+      // Every workgroup makes one claim past the end; the last of them leaves
+      // the counter at zero for the next launch (a launch of its own to clear
+      // it took 5 us).
+      if (t == total_tiles + (int32_t)gridDim.x - 1 && threadIdx.x == 0) *counter = 0;
+      break;
+    }
     const GroupDesc& d = descs[tile_inst[t]];
     GemmArgs p;
     p.A = d.A;
@@ -72,11 +78,11 @@ __global__ void __launch_bounds__(kGroupedThreads) __attribute__((amdgpu_waves_p
     p.beta = d.beta;
     p.vec_a = d.vec_a;
     p.vec_b = d.vec_b;
-    run_shape_tile(d.shape, p, d.tiles_n, t - d.tile_start, lds);
+    run_shape_tile<kGroupedLds>(d.shape, p, d.tiles_n, t - d.tile_start, lds);
   }
 }
 
-// Clears the tile counter (a kernel, so graphs hold no memset node).
+// Clears the tile counter (the one node of an empty batch's graph).
 __global__ void grouped_reset(int32_t* counter) {
   if (threadIdx.x == 0) *counter = 0;
 }
@@ -140,9 +146,7 @@ void build_schedule(Plan* p, float* scratch) {
   std::vector<int> order(count);
   std::iota(order.begin(), order.end(), 0);
   auto work = [&](int i) {
-    const hpvm_tile& t = kGroupedShapes[p->shape[i]].tile;
-    const int64_t k = p->user[i].alpha != 0.0f ? p->user[i].k : 0;
-    return (double)t.tile_m * t.tile_n * (double)(k + 32);
+    return tile_cost(p->user[i].alpha != 0.0f ? p->user[i].k : 0, p->shape[i]);
   };
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return work(a) > work(b); });
   std::vector<int64_t> scratch_off(count, 0);
@@ -247,6 +251,8 @@ hipError_t upload(Plan* p, void* ws, hipStream_t s) {
     e = hipMemcpyAsync(l.descs, p->dev.data(), p->dev.size() * sizeof(GroupDesc), hipMemcpyHostToDevice, s);
   if (e == hipSuccess && !p->tile_inst.empty())
     e = hipMemcpyAsync(l.tile_inst, p->tile_inst.data(), p->tile_inst.size() * 4, hipMemcpyHostToDevice, s);
+  static const int32_t kZero = 0;  // the counter; each launch leaves it cleared
+  if (e == hipSuccess) e = hipMemcpyAsync(l.counter, &kZero, sizeof kZero, hipMemcpyHostToDevice, s);
   // The host vectors may change (autotuning), so finish the copies now.
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e == hipSuccess) {
@@ -271,9 +277,7 @@ hipError_t persistent_grid(Plan* p) {
 
 hipError_t enqueue(Plan* p, void* ws, hipStream_t s) {
   WsLayout l = layout(p, ws);
-  void* rargs[] = {&l.counter};
-  hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(&grouped_reset), dim3(1), dim3(64), rargs, 0, s);
-  if (e != hipSuccess || p->total_tiles == 0) return e;
+  if (p->total_tiles == 0) return hipSuccess;
   const GroupDesc* d = l.descs;
   const int32_t* ti = l.tile_inst;
   int32_t total = p->total_tiles;
@@ -428,7 +432,7 @@ int hpvm_grouped_capture(void* plan, void* workspace, int64_t workspace_bytes_, 
   WsLayout l = layout(p, workspace);
   e = hipGraphCreate(&g->graph, 0);
   hipGraphNode_t reset_node = nullptr, run_node = nullptr;
-  if (e == hipSuccess) {
+  if (e == hipSuccess && p->total_tiles == 0) {
     void* rargs[] = {&l.counter};
     hipKernelNodeParams kp{};
     kp.func = reinterpret_cast<void*>(&grouped_reset);
@@ -452,7 +456,7 @@ int hpvm_grouped_capture(void* plan, void* workspace, int64_t workspace_bytes_, 
     kp.sharedMemBytes = (unsigned)kGroupedLds;
     kp.kernelParams = kargs;
     kp.extra = nullptr;
-    e = hipGraphAddKernelNode(&run_node, g->graph, &reset_node, 1, &kp);
+    e = hipGraphAddKernelNode(&run_node, g->graph, nullptr, 0, &kp);
   }
   if (e == hipSuccess) e = hipGraphInstantiate(&g->exec, g->graph, nullptr, nullptr, 0);
   if (e != hipSuccess) {

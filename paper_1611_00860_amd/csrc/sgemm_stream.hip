@@ -217,7 +217,7 @@ __global__ void __launch_bounds__(kGroupedThreads) __attribute__((amdgpu_waves_p
     p.vec_b = uni(task.p.vec_b);
     p.tiles_m = 0;
     p.tiles_n = 0;
-    run_shape_tile(uni(task.shape), p, uni(task.tiles_n), uni(task.local), lds);
+    run_shape_tile<kStreamLds>(uni(task.shape), p, uni(task.tiles_n), uni(task.local), lds);
     // The tile's C stores: complete within the workgroup, then one
     // device-scope release (a write-back of this XCD's L2) by thread 0
     // before it counts the tile; the barrier carries the other lanes'
@@ -443,7 +443,7 @@ int hpvm_stream_open(const hpvm_stream_config* cfg, void** handle) {
     uint64_t idle_ticks = (uint64_t)s->idle_ms * (uint64_t)rate_khz;
     void* kargs[] = {&dctl, &dslots, &dtmap, &ddone, &cap, &ticket, &pending, &idle_ticks};
     e = hipLaunchKernel(reinterpret_cast<const void*>(&sgemm_stream_f32), dim3(s->grid), dim3(kGroupedThreads),
-                        kargs, (size_t)kGroupedLds, s->stream);
+                        kargs, (size_t)kStreamLds, s->stream);
   }
   if (e == hipSuccess) e = hipEventRecord(s->finished, s->stream);
   if (e != hipSuccess) {
