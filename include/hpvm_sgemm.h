@@ -244,6 +244,16 @@ int hpvm_sgemm_ws(int64_t m, int64_t n, int64_t k, float alpha, const float* A, 
                   const float* B, int64_t ldb, float beta, float* C, int64_t ldc, int32_t prec,
                   const hpvm_tile* tile, void* workspace, int64_t workspace_bytes, void* stream);
 
+/* D <- alpha * A B + beta * C: hpvm_sgemm_ws with the result in a matrix of
+ * its own (what an out-of-place caller would copy C for first).  C is only
+ * read, and not at all when beta == 0 (NULL then); D may be C itself, with
+ * ldd == ldc, else it must not overlap C; it must not overlap A or B.  C may.
+ * Same tile, workspace and rounding as hpvm_sgemm_ws.                       */
+int hpvm_sgemm_into(int64_t m, int64_t n, int64_t k, float alpha, const float* A, int64_t lda,
+                    const float* B, int64_t ldb, float beta, const float* C, int64_t ldc, float* D,
+                    int64_t ldd, int32_t prec, const hpvm_tile* tile, void* workspace,
+                    int64_t workspace_bytes, void* stream);
+
 /* Workspace bytes hpvm_sgemm_ws needs for these sizes and tile (NULL = the
  * tile it would pick): the staged lowering's planes, or s * m * n * 4 for a
  * split contraction of s slices; 0 otherwise.                              */

@@ -148,6 +148,27 @@ def sgemm(A, B, C, alpha: float = 1.0, beta: float = 0.0, prec="fp32", tile=None
     return C
 
 
+def sgemm_into(A, B, C, D, alpha: float = 1.0, beta: float = 0.0, prec="fp32", tile=None, stream=None):
+    """D <- alpha * A @ B + beta * C (hpvm_sgemm_into); returns D.  C is only read."""
+    import torch
+
+    lib = load()
+    m, k = A.shape
+    k2, n = B.shape
+    if k2 != k or tuple(C.shape) != (m, n) or tuple(D.shape) != (m, n):
+        raise ValueError(f"shape mismatch: A {tuple(A.shape)}, B {tuple(B.shape)}, C {tuple(C.shape)}, "
+                         f"D {tuple(D.shape)}")
+    pa, lda = _mat(A, "A")
+    pb, ldb = _mat(B, "B")
+    pc, ldc = _mat(C, "C")
+    pd, ldd = _mat(D, "D")
+    need = workspace_bytes(m, n, k, prec, tile)
+    ws = _empty(need, torch.uint8, D.device, stream) if need else None
+    _check(lib.hpvm_sgemm_into(m, n, k, float(alpha), pa, lda, pb, ldb, float(beta), pc, ldc, pd, ldd, _prec(prec),
+                               _tile(tile), ctypes.c_void_p(ws.data_ptr() if need else None), need, _stream(stream)))
+    return D
+
+
 # Bytes of the device array hpvm_sgemm_noalloc uses as its workspace (the
 # header's HPVM_NOALLOC_SCRATCH_BYTES).
 NOALLOC_SCRATCH_BYTES = 32 << 20

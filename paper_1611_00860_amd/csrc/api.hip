@@ -510,10 +510,12 @@ int hpvm_dfg_edges(hpvm_edge* out, int32_t capacity, int32_t* count) {
 namespace {
 
 // hpvm_sgemm and hpvm_sgemm_ws: `ws_ok` tells whether a workspace argument
-// exists (it is argument 14/15 of hpvm_sgemm_ws).
+// exists (it is argument 14/15 of hpvm_sgemm_ws).  Cin, ldci: where beta * C
+// is read when that is not C (hpvm_sgemm_into, which checked them).
 int sgemm_impl(int64_t m, int64_t n, int64_t k, float alpha, const float* A, int64_t lda, const float* B,
                int64_t ldb, float beta, float* C, int64_t ldc, int32_t prec, const hpvm_tile* tile, bool ws_ok,
-               void* workspace, int64_t workspace_bytes, void* stream) {
+               void* workspace, int64_t workspace_bytes, void* stream, const float* Cin = nullptr,
+               int64_t ldci = 0) {
   // Checks in argument order; nothing below touches the device until all pass.
   bool reads_ab = false;
   int rc = hpvm::check_gemm_args("", m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, &reads_ab);
@@ -543,7 +545,7 @@ int sgemm_impl(int64_t m, int64_t n, int64_t k, float alpha, const float* A, int
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   hipError_t e;
   if (!reads_ab) {
-    e = hpvm::launch_scale(C, ldc, m, n, beta, s);
+    e = hpvm::launch_scale(C, ldc, m, n, beta, s, Cin, ldci);
     return e == hipSuccess ? ok() : hip_fail(e, "scale launch");
   }
   hpvm::GemmArgs a{};
@@ -558,6 +560,8 @@ int sgemm_impl(int64_t m, int64_t n, int64_t k, float alpha, const float* A, int
   a.k = (int32_t)k;
   a.alpha = alpha;
   a.beta = beta;
+  a.Cin = Cin ? Cin : C;
+  a.ldci = Cin ? ldci : ldc;
   a.vec_a = hpvm::vec16(A, lda);
   a.vec_b = hpvm::vec16(B, ldb);
   const int64_t split = ws_ok ? hpvm::entry_split_bytes(entry, m, n, k) : 0;
@@ -588,6 +592,29 @@ int hpvm_sgemm_ws(int64_t m, int64_t n, int64_t k, float alpha, const float* A, 
                   void* workspace, int64_t workspace_bytes, void* stream) {
   return sgemm_impl(m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, prec, tile, true, workspace, workspace_bytes,
                     stream);
+}
+
+int hpvm_sgemm_into(int64_t m, int64_t n, int64_t k, float alpha, const float* A, int64_t lda, const float* B,
+                    int64_t ldb, float beta, const float* C, int64_t ldc, float* D, int64_t ldd, int32_t prec,
+                    const hpvm_tile* tile, void* workspace, int64_t workspace_bytes, void* stream) {
+  bool reads_ab = false;
+  int rc = hpvm::check_gemm_args("", m, n, k, alpha, A, lda, B, ldb, beta, D, std::max(ldd, std::max<int64_t>(n, 1)),
+                                 &reads_ab);
+  if (rc != HPVM_OK) return rc;
+  const bool reads_c = m > 0 && n > 0 && beta != 0.0f;
+  if (reads_c && !C) return fail(HPVM_INVALID_ARG, "argument 10: C is NULL (beta != 0)");
+  if (ldc < std::max<int64_t>(n, 1))
+    return fail(HPVM_INVALID_ARG, "argument 11: ldc = %lld < max(1, n)", (long long)ldc);
+  if (ldd < std::max<int64_t>(n, 1))
+    return fail(HPVM_INVALID_ARG, "argument 13: ldd = %lld < max(1, n)", (long long)ldd);
+  if (reads_c && !(C == D && ldc == ldd)) {
+    uintptr_t c0, c1, d0, d1;
+    hpvm::matrix_extent(C, m, n, ldc, &c0, &c1);
+    hpvm::matrix_extent(D, m, n, ldd, &d0, &d1);
+    if (c0 < d1 && d0 < c1) return fail(HPVM_INVALID_ARG, "argument 12: D overlaps C without being C itself");
+  }
+  return sgemm_impl(m, n, k, alpha, A, lda, B, ldb, beta, D, ldd, prec, tile, true, workspace, workspace_bytes, stream,
+                    reads_c ? C : nullptr, ldc);
 }
 
 int hpvm_sgemm_workspace_bytes(int64_t m, int64_t n, int64_t k, int32_t prec, const hpvm_tile* tile,

@@ -32,6 +32,9 @@ struct GemmArgs {
   float alpha, beta;
   int32_t vec_a, vec_b;  // 16-byte vector loads allowed for this operand
   int32_t tiles_m, tiles_n;
+  // Where beta * C is read: C and ldc, or another matrix (hpvm_sgemm_into).
+  const float* Cin;
+  int64_t ldci;
 };
 
 // True when the TM x TN tile at (m0, n0) and every K-slab of depth TK lie

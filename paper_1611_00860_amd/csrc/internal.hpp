@@ -79,10 +79,10 @@ inline int dma_split_count(int64_t tiles, int64_t k, int tk) {
   return tiles * sp >= 256 ? sp : 1;
 }
 
-// C <- alpha * (part[0] + ... + part[splits-1]) + beta * C, the slices
-// summed in order, from partial sums [splits][m][n]; beta == 0 never reads C.
-hipError_t launch_split_finish(const float* part, int32_t splits, int64_t m, int64_t n, float alpha, float beta,
-                               float* C, int64_t ldc, hipStream_t s);
+// C <- alpha * (part[0] + ... + part[splits-1]) + beta * C for the product
+// a's sizes, scalars and C (or Cin), the slices summed in order, from partial
+// sums [splits][m][n]; beta == 0 never reads C.
+hipError_t launch_split_finish(const float* part, int32_t splits, const GemmArgs& a, hipStream_t s);
 
 // The compiled fused menu for `prec` (FP32, BF16, BF16X3); returns the count.
 int mfma_menu(int32_t prec, const MfmaEntry** entries);
@@ -163,8 +163,10 @@ hipError_t launch_literal(const GemmArgs& args, int block_x, int block_y, hipStr
 hipError_t launch_flat(const GemmArgs& args, int block_x, int block_y, hipStream_t s);
 int64_t literal_alloc_bytes(int block_x, int block_y);
 
-// C <- beta * C (beta == 0 writes zeros without reading C).
-hipError_t launch_scale(float* C, int64_t ldc, int64_t m, int64_t n, float beta, hipStream_t s);
+// C <- beta * src, src being C itself when null (beta == 0 writes zeros
+// without reading it).
+hipError_t launch_scale(float* C, int64_t ldc, int64_t m, int64_t n, float beta, hipStream_t s,
+                        const float* src = nullptr, int64_t lds = 0);
 
 int hip_error(hipError_t e, const char* what);
 

@@ -95,6 +95,8 @@ template <int BM, int BN>
 __device__ __forceinline__ void store_c(const GemmArgs& p, const f32x16 (&acc)[BM][BN], int row0,
                                         int col0, int lane) {
   const bool read_c = p.beta != 0.0f;
+  const float* cin = p.Cin;
+  const int64_t ldci = p.ldci;
   constexpr int kBlocks = BM * BN, kBatch = kBlocks < 4 ? kBlocks : 4;
 #pragma unroll
   for (int k0 = 0; k0 < kBlocks; k0 += kBatch) {
@@ -107,7 +109,7 @@ __device__ __forceinline__ void store_c(const GemmArgs& p, const f32x16 (&acc)[B
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int i = row0 + 32 * bi + acc_row(r, lane);
-          c[k][r] = (i < p.m && j < p.n) ? p.C[(int64_t)i * p.ldc + j] : 0.0f;
+          c[k][r] = (i < p.m && j < p.n) ? cin[(int64_t)i * ldci + j] : 0.0f;
         }
       }
     }

@@ -192,7 +192,8 @@ __device__ __forceinline__ void any_epilogue(const GemmArgs& q, const F32DmaOut&
                                              int m0, int n0, int m_own, int n_own, bool whole, int wm0, int wn0,
                                              int lane, int z, int q0, int q1) {
   const int64_t plane = (int64_t)q.m * q.ldc;
-  const float* cin = q.C + (MODE == kDmaSplit ? z * plane : 0);
+  const float* cin = q.Cin;
+  const int64_t ldci = q.ldci;
   float* out = MODE == kDmaConsume ? o.D : q.C + (MODE == kDmaSplit ? z * plane : 0);
   const int64_t ldo = MODE == kDmaConsume ? o.ldd : q.ldc;
   const float alpha = MODE == kDmaSplit ? 1.0f : q.alpha;
@@ -220,7 +221,7 @@ __device__ __forceinline__ void any_epilogue(const GemmArgs& q, const F32DmaOut&
 #pragma unroll
     for (int b0 = 0; b0 < NB; b0 += V) {
       const int col = n0 + OB::index(b0, I, wn0);
-      const uint32_t coff = (uint32_t)((lrow * q.ldc + col) * 4), ooff = (uint32_t)((lrow * ldo + col) * 4);
+      const uint32_t coff = (uint32_t)((lrow * ldci + col) * 4), ooff = (uint32_t)((lrow * ldo + col) * 4);
       Vec bias{};
       if constexpr (MODE == kDmaConsume) {
         if (o.op == HPVM_CONSUMER_BIAS || o.op == HPVM_CONSUMER_BIAS_RELU) {
@@ -241,9 +242,9 @@ __device__ __forceinline__ void any_epilogue(const GemmArgs& q, const F32DmaOut&
               const int urow = m0 + OA::row(a0 + a, r0 + r, wm0);
               if constexpr (kAll) {
                 c[a][r] = *reinterpret_cast<const Vec*>(
-                    reinterpret_cast<const char*>(cin + (int64_t)urow * q.ldc) + coff);
+                    reinterpret_cast<const char*>(cin + (int64_t)urow * ldci) + coff);
               } else {  // past the edge: some element of C, not used
-                const float* p = cin + (int64_t)(urow + lrow < q.m ? urow + lrow : q.m - 1) * q.ldc;
+                const float* p = cin + (int64_t)(urow + lrow < q.m ? urow + lrow : q.m - 1) * ldci;
 #pragma unroll
                 for (int e = 0; e < V; ++e) put(c[a][r], e, p[col + e < q.n ? col + e : q.n - 1]);
               }
@@ -511,7 +512,7 @@ constexpr int64_t kAnyPitch = 1 << 22;
 // operands at least one 16-byte unit wide, and pitches within kAnyPitch.
 inline bool f32_any_fits(const GemmArgs& a, bool at, bool bt) {
   return a.m > 0 && a.n > 0 && a.k > 0 && a.m < (1 << 30) && a.n < (1 << 30) && (!at || a.m >= 4) && (bt || a.n >= 4) &&
-         a.lda < kAnyPitch && a.ldb < kAnyPitch && a.ldc < kAnyPitch;
+         a.lda < kAnyPitch && a.ldb < kAnyPitch && a.ldc < kAnyPitch && a.ldci < kAnyPitch;
 }
 
 }  // namespace hpvm

@@ -173,7 +173,8 @@ template <typename OA, typename OB, bool BT, int MODE, int OP, bool EDGES, int N
 __device__ __forceinline__ void dma_epilogue(const GemmArgs& q, const F32DmaOut& o, const f32x16 (&acc)[NA][NB],
                                              int64_t m0, int64_t n0, int64_t m_own, int64_t n_own, int wm0,
                                              int wn0, int lane, int z) {
-  const float* cin = q.C + (MODE == kDmaSplit ? (int64_t)z * q.m * q.ldc : 0);
+  const float* cin = q.Cin;
+  const int64_t ldci = q.ldci;
   float* out = MODE == kDmaConsume ? o.D : q.C + (MODE == kDmaSplit ? (int64_t)z * q.m * q.ldc : 0);
   const int64_t ldo = MODE == kDmaConsume ? o.ldd : q.ldc;
   const float alpha = MODE == kDmaSplit ? 1.0f : q.alpha;
@@ -187,7 +188,7 @@ __device__ __forceinline__ void dma_epilogue(const GemmArgs& q, const F32DmaOut&
     using VB = typename OB::Frag;
     const int64_t col = n0 + OB::index(0, I, wn0);
     const int64_t lrow = m0 + OA::index(0, 4 * (lane >> 5), 0);
-    const float* cl = cin + lrow * q.ldc + col;
+    const float* cl = cin + lrow * ldci + col;
     float* ol = out + lrow * ldo + col;
     const bool col_own = !EDGES || col >= n_own;  // the lane's NB columns are owned together (n % 4 == 0)
     VB bias{};
@@ -207,7 +208,7 @@ __device__ __forceinline__ void dma_epilogue(const GemmArgs& q, const F32DmaOut&
 #pragma unroll
           for (int r = 0; r < kRows; ++r) {
             const int64_t i = OA::index(a, acc_row(r0 + r, 0), wm0);
-            if (col_own && (!EDGES || lrow + i >= m_own)) c[r] = *reinterpret_cast<const VB*>(cl + i * q.ldc);
+            if (col_own && (!EDGES || lrow + i >= m_own)) c[r] = *reinterpret_cast<const VB*>(cl + i * ldci);
           }
         }
 #pragma unroll
@@ -235,7 +236,7 @@ __device__ __forceinline__ void dma_epilogue(const GemmArgs& q, const F32DmaOut&
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
             const int64_t i = m0 + OA::index(a, acc_row(4 * g + u, lane), wm0);
-            c[u] = (read_c && (!EDGES || (col >= n_own && i >= m_own))) ? cin[i * q.ldc + col] : 0.0f;
+            c[u] = (read_c && (!EDGES || (col >= n_own && i >= m_own))) ? cin[i * ldci + col] : 0.0f;
           }
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
@@ -378,13 +379,20 @@ __global__ void __launch_bounds__((F32DmaShape<TM, TN, TK, WM, WN, AT, BT, NST, 
   f32_dma_tile<TM, TN, TK, WM, WN, AT, BT, NST, MODE, OP, PAIR, EDGES>(p, p2, o, tm, tn, z, smem);
 }
 
+// C, where the loop's epilogue reads it (with a split contraction the
+// summing pass does, at any alignment), allows 16-byte loads.
+inline bool cin_aligned(const GemmArgs& a) {
+  return a.beta == 0.0f || (a.ldci % 4 == 0 && (reinterpret_cast<uintptr_t>(a.Cin) & 15) == 0);
+}
+
 // True when the DMA-fed loop covers the problem in whole tiles: m, n and k
 // multiples of the tile (k of splits * TK), every operand and the output
 // 16-byte aligned with leading dimensions that are multiples of 4.
 template <int TM, int TN, int TK>
 inline bool f32_dma_fits(const GemmArgs& a, const void* out, int64_t ldo, int splits) {
   return a.vec_a && a.vec_b && a.m > 0 && a.n > 0 && a.k > 0 && a.m % TM == 0 && a.n % TN == 0 &&
-         a.k % (TK * splits) == 0 && ldo % 4 == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0;
+         a.k % (TK * splits) == 0 && ldo % 4 == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0 &&
+         (splits > 1 || cin_aligned(a));
 }
 
 // True when the DMA-fed loop covers the problem with edge tiles moved
@@ -393,7 +401,7 @@ inline bool f32_dma_fits(const GemmArgs& a, const void* out, int64_t ldo, int sp
 template <int TM, int TN, int TK>
 inline bool f32_dma_fits_edges(const GemmArgs& a, const void* out, int64_t ldo) {
   return a.vec_a && a.vec_b && a.m >= TM && a.n >= TN && a.n % 4 == 0 && a.k > 0 && a.k % TK == 0 &&
-         ldo % 4 == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0;
+         ldo % 4 == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0 && cin_aligned(a);
 }
 
 }  // namespace hpvm

@@ -1024,7 +1024,9 @@ int hpvm_sgemm_backward(int64_t m, int64_t n, int64_t k, float alpha, float beta
     a.B = B;
     a.ldb = ldb;
     a.C = dA;
+    a.Cin = dA;
     a.ldc = ldda;
+    a.ldci = ldda;
     a.m = (int32_t)m;
     a.n = (int32_t)k;
     a.k = (int32_t)n;
@@ -1088,7 +1090,9 @@ int hpvm_sgemm_backward(int64_t m, int64_t n, int64_t k, float alpha, float beta
     b.B = G;
     b.ldb = ldg;
     b.C = dB;
+    b.Cin = dB;
     b.ldc = lddb;
+    b.ldci = lddb;
     b.m = (int32_t)k;
     b.n = (int32_t)n;
     b.k = (int32_t)m;

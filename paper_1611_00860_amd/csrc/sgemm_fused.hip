@@ -405,8 +405,8 @@ struct PairDmaConfig {
     if (e != hipSuccess) return e;
     e = hipLaunchKernel(reinterpret_cast<const void*>(fn), dim3((unsigned)(p1.tiles_m * p1.tiles_n * sp)),
                         dim3(kThreads), kargs, (size_t)S::kLdsBytes, s);
-    if (e == hipSuccess) e = launch_split_finish(part1, sp, a1.m, a1.n, a1.alpha, a1.beta, a1.C, a1.ldc, s);
-    if (e == hipSuccess) e = launch_split_finish(part2, sp, a2.m, a2.n, a2.alpha, a2.beta, a2.C, a2.ldc, s);
+    if (e == hipSuccess) e = launch_split_finish(part1, sp, a1, s);
+    if (e == hipSuccess) e = launch_split_finish(part2, sp, a2, s);
     return e;
   }
 };
@@ -543,9 +543,11 @@ int hpvm_sgemm_consumer(int64_t m, int64_t n, int64_t k, float alpha, const floa
   g.A = A;
   g.B = B;
   g.C = const_cast<float*>(C);  // read only: the consumer store writes D
+  g.Cin = C;
   g.lda = lda;
   g.ldb = ldb;
   g.ldc = ldc;
+  g.ldci = ldc;
   g.m = (int32_t)m;
   g.n = (int32_t)n;
   g.k = reads_ab ? (int32_t)k : 0;  // k == 0 or alpha == 0: A and B are not read
@@ -629,14 +631,18 @@ int pair_impl(int64_t m, int64_t n, int64_t k, const float* A, int64_t lda, floa
   g1.B = B1;
   g1.ldb = ldb1;
   g1.C = C1;
+  g1.Cin = C1;
   g1.ldc = ldc1;
+  g1.ldci = ldc1;
   g1.alpha = alpha1;
   g1.beta = beta1;
   g1.vec_b = vec16(B1, ldb1);
   g2.B = B2;
   g2.ldb = ldb2;
   g2.C = C2;
+  g2.Cin = C2;
   g2.ldc = ldc2;
+  g2.ldci = ldc2;
   g2.alpha = alpha2;
   g2.beta = beta2;
   g2.vec_b = vec16(B2, ldb2);

@@ -68,9 +68,11 @@ __global__ void __launch_bounds__(kGroupedThreads) __attribute__((amdgpu_waves_p
     p.A = d.A;
     p.B = d.B;
     p.C = d.C;
+    p.Cin = d.C;
     p.lda = d.lda;
     p.ldb = d.ldb;
     p.ldc = d.ldc;
+    p.ldci = d.ldc;
     p.m = d.m;
     p.n = d.n;
     p.k = d.k;

@@ -33,7 +33,7 @@ __global__ void sgemm_leaf_literal(GemmArgs p) {
   }
   if (i < p.m && j < p.n) {
     float v = p.alpha * acc;
-    if (p.beta != 0.0f) v = fmaf(p.beta, p.C[i * p.ldc + j], v);
+    if (p.beta != 0.0f) v = fmaf(p.beta, p.Cin[i * p.ldci + j], v);
     p.C[i * p.ldc + j] = v;
   }
 }
@@ -53,7 +53,7 @@ __global__ void sgemm_leaf_flat(GemmArgs p) {
   float acc = 0.0f;
   for (int64_t t = 0; t < p.k; ++t) acc = fmaf(a[t], b[t * p.ldb], acc);
   float v = p.alpha * acc;
-  if (p.beta != 0.0f) v = fmaf(p.beta, p.C[i * p.ldc + j], v);
+  if (p.beta != 0.0f) v = fmaf(p.beta, p.Cin[i * p.ldci + j], v);
   p.C[i * p.ldc + j] = v;
 }
 
@@ -79,23 +79,27 @@ hipError_t launch_literal(const GemmArgs& args, int block_x, int block_y, hipStr
                          (size_t)literal_alloc_bytes(block_x, block_y), s);
 }
 
-// C <- beta * C over an m x n block with leading dimension ldc.
-__global__ void __launch_bounds__(256) scale_c(float* C, int64_t ldc, int64_t m, int64_t n,
-                                               float beta) {
+// C <- beta * src over an m x n block (src may be C).
+__global__ void __launch_bounds__(256) scale_c(const float* src, int64_t lds, float* C, int64_t ldc, int64_t m,
+                                               int64_t n, float beta) {
   const int64_t total = m * n;
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
        e += (int64_t)gridDim.x * blockDim.x) {
     const int64_t i = e / n, j = e - i * n;
-    float* c = C + i * ldc + j;
-    *c = (beta == 0.0f) ? 0.0f : beta * *c;
+    C[i * ldc + j] = (beta == 0.0f) ? 0.0f : beta * src[i * lds + j];
   }
 }
 
-hipError_t launch_scale(float* C, int64_t ldc, int64_t m, int64_t n, float beta, hipStream_t s) {
+hipError_t launch_scale(float* C, int64_t ldc, int64_t m, int64_t n, float beta, hipStream_t s, const float* src,
+                        int64_t lds) {
+  if (!src) {
+    src = C;
+    lds = ldc;
+  }
   const int64_t total = m * n;
   int64_t blocks = (total + 255) / 256;
   if (blocks > 8192) blocks = 8192;
-  void* kargs[] = {&C, &ldc, &m, &n, &beta};
+  void* kargs[] = {&src, &lds, &C, &ldc, &m, &n, &beta};
   return hipLaunchKernel(reinterpret_cast<const void*>(&scale_c), dim3((unsigned)blocks), dim3(256),
                          kargs, 0, s);
 }

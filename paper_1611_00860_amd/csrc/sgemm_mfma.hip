@@ -179,7 +179,7 @@ struct AnyConfig {
     a.beta = 0.0f;
     hipError_t e = run<false, false, kDmaSplit>(a, sp, s);
     if (e != hipSuccess) return e;
-    return launch_split_finish(part, sp, args.m, args.n, args.alpha, args.beta, args.C, args.ldc, s);
+    return launch_split_finish(part, sp, args, s);
   }
 };
 
@@ -193,8 +193,11 @@ struct AnyConfig {
 // may start at any float.
 constexpr int kSplitThreads = 256;
 __global__ void __launch_bounds__(kSplitThreads)
-    sgemm_split_finish(const float* __restrict__ part, int32_t splits, int64_t m, int64_t n, float alpha,
-                       float beta, float* __restrict__ C, int64_t ldc) {
+    sgemm_split_finish(const float* __restrict__ part, int32_t splits, GemmArgs a) {
+  const int64_t m = a.m, n = a.n, ldc = a.ldc, ldci = a.ldci;
+  const float alpha = a.alpha, beta = a.beta;
+  float* C = a.C;
+  const float* cin = a.Cin;
   using Vec = LooseF<4>::type;
   const int64_t c4 = (n + 3) / 4, units = m * c4, plane = m * n;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -202,11 +205,12 @@ __global__ void __launch_bounds__(kSplitThreads)
     const int64_t i = u / c4, j = (u - i * c4) * 4;
     const float* p = part + i * n + j;
     float* c = C + i * ldc + j;
+    const float* o = cin + i * ldci + j;
     if (j + 4 <= n) {
       Vec v = *reinterpret_cast<const Vec*>(p);
       for (int z = 1; z < splits; ++z) v += *reinterpret_cast<const Vec*>(p + z * plane);
       if (beta != 0.0f) {
-        const Vec old = *reinterpret_cast<const Vec*>(c);
+        const Vec old = *reinterpret_cast<const Vec*>(o);
 #pragma unroll
         for (int t = 0; t < 4; ++t) v[t] = fmaf(beta, old[t], alpha * v[t]);
       } else {
@@ -218,17 +222,17 @@ __global__ void __launch_bounds__(kSplitThreads)
         float v = p[t];
         for (int z = 1; z < splits; ++z) v += p[z * plane + t];
         v *= alpha;
-        c[t] = beta != 0.0f ? fmaf(beta, c[t], v) : v;
+        c[t] = beta != 0.0f ? fmaf(beta, o[t], v) : v;
       }
     }
   }
 }
 
-hipError_t launch_split_finish(const float* part, int32_t splits, int64_t m, int64_t n, float alpha, float beta,
-                               float* C, int64_t ldc, hipStream_t s) {
-  const int64_t units = m * ((n + 3) / 4);
+hipError_t launch_split_finish(const float* part, int32_t splits, const GemmArgs& a, hipStream_t s) {
+  GemmArgs args = a;
+  const int64_t units = (int64_t)a.m * ((a.n + 3) / 4);
   const unsigned blocks = (unsigned)std::min<int64_t>(2048, (units + kSplitThreads - 1) / kSplitThreads);
-  void* fargs[] = {&part, &splits, &m, &n, &alpha, &beta, &C, &ldc};
+  void* fargs[] = {&part, &splits, &args};
   return hipLaunchKernel(reinterpret_cast<const void*>(&sgemm_split_finish), dim3(blocks), dim3(kSplitThreads),
                          fargs, 0, s);
 }
@@ -300,7 +304,7 @@ struct F32DmaConfig {
     e = hipLaunchKernel(reinterpret_cast<const void*>(fn), dim3((unsigned)(a.tiles_m * a.tiles_n * sp)),
                         dim3(kThreads), kargs, (size_t)S::kLdsBytes, s);
     if (e != hipSuccess) return e;
-    return launch_split_finish(part, sp, args.m, args.n, args.alpha, args.beta, args.C, args.ldc, s);
+    return launch_split_finish(part, sp, args, s);
   }
 };
 
@@ -422,7 +426,7 @@ struct Bf16SrcConfig {
     e = hipLaunchKernel(reinterpret_cast<const void*>(fn), dim3((unsigned)(a.tiles_m * a.tiles_n * sp)),
                         dim3(kThreads), kargs, (size_t)S::kLdsBytes, s);
     if (e != hipSuccess) return e;
-    return launch_split_finish(part, sp, args.m, args.n, args.alpha, args.beta, args.C, args.ldc, s);
+    return launch_split_finish(part, sp, args, s);
   }
 };
 

@@ -374,6 +374,8 @@ struct StagedArgs {
   int64_t ldc;
   int32_t m, n, slabs, tiles_m, tiles_n;
   float alpha, beta;
+  const float* Cin;  // as GemmArgs
+  int64_t ldci;
   // Backward epilogue (EPI = 1): C (may be null) <- alpha acc, and
   // partial[tile] <- sum over the tile of aorig .* acc.
   const float* aorig;
@@ -512,6 +514,8 @@ __global__ void __launch_bounds__((TM / WM) * (TN / WN) * kWave)
     GemmArgs e{};
     e.C = p.C;
     e.ldc = p.ldc;
+    e.Cin = p.Cin;
+    e.ldci = p.ldci;
     e.m = p.m;
     e.n = p.n;
     e.alpha = p.alpha;
@@ -683,6 +687,8 @@ __device__ __forceinline__ void bf16_dma_tile(const StagedArgs& p, int tile, cha
     GemmArgs e{};
     e.C = p.C;
     e.ldc = p.ldc;
+    e.Cin = p.Cin;
+    e.ldci = p.ldci;
     e.m = p.m;
     e.n = p.n;
     e.alpha = p.alpha;
@@ -800,6 +806,8 @@ StagedArgs staged_args(const GemmArgs& a, const StagedPlanes& P, int tm, int tn,
   p.kp = staged_k_pad(a.k);
   p.C = a.C;
   p.ldc = a.ldc;
+  p.Cin = a.Cin;
+  p.ldci = a.ldci;
   p.m = a.m;
   p.n = a.n;
   p.slabs = (int32_t)(p.kp / tk);

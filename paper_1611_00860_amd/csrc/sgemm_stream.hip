@@ -205,9 +205,11 @@ __global__ void __launch_bounds__(kGroupedThreads) __attribute__((amdgpu_waves_p
     p.A = uni(task.p.A);
     p.B = uni(task.p.B);
     p.C = uni(task.p.C);
+    p.Cin = p.C;
     p.lda = uni(task.p.lda);
     p.ldb = uni(task.p.ldb);
     p.ldc = uni(task.p.ldc);
+    p.ldci = p.ldc;
     p.m = uni(task.p.m);
     p.n = uni(task.p.n);
     p.k = uni(task.p.k);
