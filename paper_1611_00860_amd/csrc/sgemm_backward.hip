@@ -33,6 +33,7 @@
 #include "hpvm_sgemm.h"
 #include "internal.hpp"
 #include "mfma_bf16.hpp"
+#include "mfma_bf16_any.hpp"
 #include "mfma_bf16_dma.hpp"
 #include "mfma_f32.hpp"
 #include "mfma_f32_any.hpp"
@@ -311,9 +312,16 @@ __device__ __forceinline__ float any_grad_a_epilogue(const GemmArgs& q, const fl
 // filled the CUs unevenly on its own and every launch's end left them idle:
 // 1000 x 1200 x 800, dA 59 + dB 48 + grad_c 5 us on the register-staged
 // loops.
-template <int TM, int TN, int TK, int WM, int WN, int NST, int KW>
-__global__ void __launch_bounds__((AnyShape<TM, TN, TK, WM, WN, false, true, NST, KW>::kThreads))
-    __attribute__((amdgpu_waves_per_eu((AnyShape<TM, TN, TK, WM, WN, false, true, NST, KW>::kMinWaves)))) sgemm_grad_any(GemmArgs a, const float* __restrict__ aorig, int64_t ldao, float* __restrict__ partial, GemmArgs b,
+template <int PREC, typename S>
+using AnyMath = std::conditional_t<PREC == HPVM_PREC_FP32, MathF32<S>, MathBf16<S, PREC == HPVM_PREC_BF16X3>>;
+template <int PREC, typename S>
+constexpr int kAnyMinWaves =
+    PREC == HPVM_PREC_FP32 ? S::kMinWaves : kBf16AnyMinWaves<S::kWm, S::kWn, PREC == HPVM_PREC_BF16X3>;
+
+template <int PREC, int TM, int TN, int TK, int WM, int WN, int NST, int KW>
+__global__ void __launch_bounds__((AnyShape<TM, TN, TK, WM, WN, false, true, NST, KW>::kThreads)) __attribute__((
+    amdgpu_waves_per_eu((kAnyMinWaves<PREC, AnyShape<TM, TN, TK, WM, WN, false, true, NST, KW>>))))
+    sgemm_grad_any(GemmArgs a, const float* __restrict__ aorig, int64_t ldao, float* __restrict__ partial, GemmArgs b,
                    GradCJob c, int32_t tiles_a, int32_t tiles_b) {
   extern __shared__ __align__(16) char smem[];
   using SA = AnyShape<TM, TN, TK, WM, WN, false, true, NST, KW>;
@@ -322,7 +330,7 @@ __global__ void __launch_bounds__((AnyShape<TM, TN, TK, WM, WN, false, true, NST
   if (t < tiles_a) {
     tile_coords(a.tiles_m, a.tiles_n, t, tm, tn);
     float part = 0.0f;
-    f32_any_tile<TM, TN, TK, WM, WN, false, true, NST, KW>(
+    any_tile<SA, AnyMath<PREC, SA>>(
         a, 1, tm, tn, 0, smem,
         [&](const auto& acc, int m0, int n0, int m_own, int n_own, bool whole, int wm0, int wn0, int lane, int q0,
             int q1) {
@@ -342,7 +350,7 @@ __global__ void __launch_bounds__((AnyShape<TM, TN, TK, WM, WN, false, true, NST
   t -= tiles_a;
   if (t < tiles_b) {
     tile_coords(b.tiles_m, b.tiles_n, t, tm, tn);
-    f32_any_tile<TM, TN, TK, WM, WN, true, false, NST, KW>(
+    any_tile<SB, AnyMath<PREC, SB>>(
         b, 1, tm, tn, 0, smem,
         [&](const auto& acc, int m0, int n0, int m_own, int n_own, bool whole, int wm0, int wn0, int lane, int q0,
             int q1) {
@@ -357,7 +365,7 @@ __global__ void __launch_bounds__((AnyShape<TM, TN, TK, WM, WN, false, true, NST
 namespace {
 
 // sgemm_grad_any on one tile; a null pointer leaves a range out.
-template <int TM, int TN, int TK, int WM, int WN, int NST, int KW>
+template <int PREC, int TM, int TN, int TK, int WM, int WN, int NST, int KW>
 hipError_t launch_grad_any(const GemmArgs* ga, const float* aorig, int64_t ldao, float* partial, const GemmArgs* gb,
                            const GradCJob* gc, hipStream_t s) {
   using S = AnyShape<TM, TN, TK, WM, WN, false, true, NST, KW>;
@@ -378,7 +386,7 @@ hipError_t launch_grad_any(const GemmArgs* ga, const float* aorig, int64_t ldao,
     tb = tiles(b);
   }
   if (gc) c = *gc;
-  auto* fn = &sgemm_grad_any<TM, TN, TK, WM, WN, NST, KW>;
+  auto* fn = &sgemm_grad_any<PREC, TM, TN, TK, WM, WN, NST, KW>;
   hipError_t e = hipSuccess;
   if (S::kLdsBytes > 65536)
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -389,12 +397,10 @@ hipError_t launch_grad_any(const GemmArgs* ga, const float* aorig, int64_t ldao,
                          kargs, (size_t)S::kLdsBytes, s);
 }
 
-// One candidate tile of the backward.  Fused FP32 entries run everything
-// through sgemm_grad_any (what f32_any_fits leaves out: sgemm_grad_a and the
-// single launch on 64 x 64 x 16 tiles); fused BF16 and bf16x3 entries run dA
-// through sgemm_grad_a and dB through the fused menu entry's launch; staged
-// entries
-// run both through the staged lowering (one conversion launch into the
+// One candidate tile of the backward.  Fused entries run everything through
+// sgemm_grad_any (what f32_any_fits leaves out: sgemm_grad_a and the single
+// launch on odd_tile(prec)); staged entries run both products through the
+// staged lowering (one conversion launch into the
 // workspace, with the transposition of each operand folded into it).
 struct BwdEntry {
   hpvm_tile tile;
@@ -404,7 +410,7 @@ struct BwdEntry {
   void (*grad_a)(GemmArgs, const float*, int64_t, float*);  // null for staged entries
   bool dma = false;  // split-contraction DMA-fed entry
   hipError_t (*any)(const GemmArgs*, const float*, int64_t, float*, const GemmArgs*, const GradCJob*,
-                    hipStream_t) = nullptr;  // FP32
+                    hipStream_t) = nullptr;  // fused entries
   // DMA entries: the entry for what the DMA-fed loop does not cover (FP32:
   // the passes that are not whole aligned tiles; BF16: the whole call).
   int fallback = 1;
@@ -418,13 +424,15 @@ constexpr BwdEntry fused_entry() {
   return BwdEntry{{TM, TN, TK, WM, WN, 2}, PREC, (TM / WM) * (TN / WN) * kWave, lds,
                   &sgemm_grad_a<TM, TN, TK, WM, WN, PREC>};
 }
-// FP32 on the loop for any size: SUB deep sub-slabs, KW of them per slab.
-constexpr hpvm_tile kOddTile{64, 64, 16, 32, 32, 2};  // of the products it leaves out
-template <int TM, int TN, int TK, int WM, int WN, int SUB, int NST, int KW>
+// The loop for any size: SUB deep sub-slabs, KW of them per slab.
+constexpr hpvm_tile odd_tile(int32_t prec) {  // of the products it leaves out
+  return hpvm_tile{64, 64, prec == HPVM_PREC_FP32 ? 16 : 32, 32, 32, 2};
+}
+template <int PREC, int TM, int TN, int TK, int WM, int WN, int SUB, int NST, int KW>
 constexpr BwdEntry any_entry() {
-  BwdEntry e = fused_entry<64, 64, 16, 32, 32, HPVM_PREC_FP32>();
+  BwdEntry e = fused_entry<64, 64, PREC == HPVM_PREC_FP32 ? 16 : 32, 32, 32, PREC>();
   e.tile = hpvm_tile{TM, TN, TK, WM / KW, WN, 2};
-  e.any = &launch_grad_any<TM, TN, SUB, WM, WN, NST, KW>;
+  e.any = &launch_grad_any<PREC, TM, TN, SUB, WM, WN, NST, KW>;
   return e;
 }
 constexpr BwdEntry staged_entry(int tm, int tn, int tk, int wm, int wn, int prec) {
@@ -461,27 +469,27 @@ constexpr BwdEntry bf16_dma_entry(int fallback) {
 // kBwd[1] is the FP32 DMA entry's fallback for passes that are not whole tiles.
 constexpr BwdEntry kBwd[] = {
     dma_entry(),
-    any_entry<64, 128, 32, 32, 64, 32, 2, 1>(),
-    any_entry<128, 128, 32, 64, 64, 32, 2, 1>(),
-    any_entry<128, 128, 16, 64, 64, 16, 4, 1>(),
-    any_entry<128, 64, 16, 64, 32, 16, 4, 1>(),
-    any_entry<64, 128, 16, 32, 64, 16, 4, 1>(),
-    any_entry<64, 64, 16, 32, 32, 16, 6, 1>(),
-    any_entry<64, 64, 32, 32, 32, 16, 3, 2>(),
-    any_entry<32, 32, 128, 32, 32, 32, 2, 4>(),
+    any_entry<HPVM_PREC_FP32, 64, 128, 32, 32, 64, 32, 2, 1>(),
+    any_entry<HPVM_PREC_FP32, 128, 128, 32, 64, 64, 32, 2, 1>(),
+    any_entry<HPVM_PREC_FP32, 128, 128, 16, 64, 64, 16, 4, 1>(),
+    any_entry<HPVM_PREC_FP32, 128, 64, 16, 64, 32, 16, 4, 1>(),
+    any_entry<HPVM_PREC_FP32, 64, 128, 16, 32, 64, 16, 4, 1>(),
+    any_entry<HPVM_PREC_FP32, 64, 64, 16, 32, 32, 16, 6, 1>(),
+    any_entry<HPVM_PREC_FP32, 64, 64, 32, 32, 32, 16, 3, 2>(),
+    any_entry<HPVM_PREC_FP32, 32, 32, 128, 32, 32, 32, 2, 4>(),
     bf16_dma_entry(10),
     staged_entry(128, 128, 64, 64, 32, HPVM_PREC_BF16),
     staged_entry(128, 128, 64, 64, 64, HPVM_PREC_BF16),
     staged_entry(256, 256, 64, 128, 64, HPVM_PREC_BF16),
     staged_entry(256, 128, 64, 128, 64, HPVM_PREC_BF16),
-    fused_entry<128, 128, 32, 64, 64, HPVM_PREC_BF16>(),
-    fused_entry<64, 64, 32, 32, 32, HPVM_PREC_BF16>(),
+    any_entry<HPVM_PREC_BF16, 128, 128, 32, 64, 64, 32, 2, 1>(),
+    any_entry<HPVM_PREC_BF16, 64, 64, 32, 32, 32, 32, 3, 1>(),
     staged_entry(256, 256, 32, 128, 64, HPVM_PREC_BF16X3),
     staged_entry(128, 128, 64, 64, 32, HPVM_PREC_BF16X3),
     staged_entry(128, 128, 64, 64, 64, HPVM_PREC_BF16X3),
     staged_entry(256, 128, 32, 128, 64, HPVM_PREC_BF16X3),
-    fused_entry<128, 128, 32, 64, 64, HPVM_PREC_BF16X3>(),
-    fused_entry<64, 64, 32, 32, 32, HPVM_PREC_BF16X3>(),
+    any_entry<HPVM_PREC_BF16X3, 128, 128, 32, 64, 64, 32, 2, 1>(),
+    any_entry<HPVM_PREC_BF16X3, 64, 64, 32, 32, 32, 32, 3, 1>(),
 };
 constexpr int kNumBwd = sizeof(kBwd) / sizeof(kBwd[0]);
 static_assert(kBwd[9].dma && kBwd[9].prec == HPVM_PREC_BF16 && !kBwd[10].grad_a && kBwd[10].prec == HPVM_PREC_BF16,
@@ -590,17 +598,52 @@ const BwdEntry* f32_pick(int64_t m, int64_t n, int64_t k) {
   return pick;
 }
 
-// Built-in choice for BF16 and bf16x3: the first entry giving at least one
-// tile per CU of a 256-CU part, else the one giving the most tiles --
-// counting dA's tiles, plus dB's for a staged entry that runs both products
-// in one launch.
+// Built-in choice for BF16 and bf16x3: the first staged entry giving at least
+// one tile per CU of a 256-CU part, else the one giving the most (dA's tiles,
+// plus dB's where one launch runs both), or the fused 64 x 64 tiles where
+// those are estimated faster.  Per 32-deep slab a round of 256 fused tiles
+// takes 0.25 us (bf16x3: 0.37), one tile alone 0.28 (0.44); a 128 x 128
+// staged tile 0.27 (0.65), after its pass over the operands at 4.8 TB/s, and
+// 11 us of launches more than the fused.  Fused against staged, BF16 and
+// bf16x3: 1000 x 1200 x 800 30, 34 us against 42, 52; 300 x 3000 x 500 39, 54
+// against 57, 76; 2048^3 123, 190 against 73, 137.
 int64_t launch_tiles(const BwdEntry& e, int64_t m, int64_t n, int64_t k) {
   int64_t tiles = tiles_for(e.tile, m, k);
-  if (!e.grad_a) {
-    const MfmaEntry* me = find_menu_entry(e.prec, e.tile);
-    if (me && me->launch_staged_pair) tiles += tiles_for(e.tile, k, n);
-  }
+  const MfmaEntry* me = find_menu_entry(e.prec, e.tile);
+  if (me && me->launch_staged_pair) tiles += tiles_for(e.tile, k, n);
   return tiles;
+}
+
+const BwdEntry* bf16_pick(int32_t prec, int64_t m, int64_t n, int64_t k) {
+  const bool x3 = prec == HPVM_PREC_BF16X3;
+  const BwdEntry* fused = find_bwd(prec, odd_tile(prec));
+  if (!staged_k_ok(n) || !staged_k_ok(m)) return fused;  // the dA and dB contractions
+  const BwdEntry* staged = nullptr;
+  for (int i = 0; i < kNumBwd; ++i) {
+    // The BF16 DMA entry reads FP32 slabs where the staged products read
+    // bfloat16 planes, twice the bytes (4096 x 4096 x 1024: 0.181 ms against
+    // 0.131 for the staged 128 x 128 x 64 tile).
+    if (kBwd[i].prec != prec || kBwd[i].dma || kBwd[i].grad_a) continue;
+    const int64_t tiles = launch_tiles(kBwd[i], m, n, k);
+    if (!staged || tiles > launch_tiles(*staged, m, n, k)) staged = &kBwd[i];
+    if (tiles >= kTargetTiles) {
+      staged = &kBwd[i];
+      break;
+    }
+  }
+  if (!staged || !fused) return staged ? staged : fused;
+  // Slabs of the most tiles one of 256 CUs gets, and of one of the deeper.
+  const double deep = (double)std::max(m, n) / 32.0;
+  auto slabs = [&](const hpvm_tile& t) {
+    const double ta = (double)tiles_for(t, m, k), tb = (double)tiles_for(t, k, n);
+    const double rounds = (double)(((int64_t)(ta + tb) + 255) / 256);
+    return rounds * (ta * n + tb * m) / std::max(ta + tb, 1.0) / 32.0;
+  };
+  const double tf = 10.0 + std::max(slabs(fused->tile) * (x3 ? 0.37 : 0.25), deep * (x3 ? 0.44 : 0.28));
+  const double bytes = (double)m * n * (x3 ? 20.0 : 16.0) + ((double)m * k + (double)k * n) * (x3 ? 8.0 : 6.0);
+  const double slab = (x3 ? 0.65 : 0.27) * staged->tile.tile_m * staged->tile.tile_n / (128.0 * 128.0);
+  const double ts = 21.0 + bytes / 4.8e6 + std::max(slabs(staged->tile), deep) * slab;
+  return tf < ts ? fused : staged;
 }
 
 const BwdEntry* pick(int32_t prec, int64_t m, int64_t n, int64_t k) {
@@ -609,20 +652,7 @@ const BwdEntry* pick(int32_t prec, int64_t m, int64_t n, int64_t k) {
     const BwdEntry* e = find_bwd(prec, tuned);
     if (e) return e;
   }
-  const BwdEntry* most = nullptr;
-  const bool staged_ok = staged_k_ok(n) && staged_k_ok(m);  // the dA and dB contractions
-  if (prec == HPVM_PREC_FP32) return f32_pick(m, n, k);
-  for (int i = 0; i < kNumBwd; ++i) {
-    // The BF16 DMA entry reads FP32 slabs where the staged products read
-    // bfloat16 planes, twice the bytes (4096 x 4096 x 1024: 0.181 ms against
-    // 0.131 for the staged 128 x 128 x 64 tile).
-    if (kBwd[i].prec != prec || kBwd[i].dma) continue;
-    if (!kBwd[i].grad_a && !staged_ok) continue;
-    const int64_t tiles = launch_tiles(kBwd[i], m, n, k);
-    if (tiles >= kTargetTiles) return &kBwd[i];
-    if (!most || tiles > launch_tiles(*most, m, n, k)) most = &kBwd[i];
-  }
-  return most;
+  return prec == HPVM_PREC_FP32 ? f32_pick(m, n, k) : bf16_pick(prec, m, n, k);
 }
 
 int64_t elem_blocks(int64_t m, int64_t n) {
@@ -679,7 +709,7 @@ BwdLayout bwd_layout(const BwdEntry* e, int64_t m, int64_t n, int64_t k) {
   auto up = [](int64_t b) { return (b + 255) / 256 * 256; };
   BwdLayout L;
   L.na = (m > 0 && k > 0) ? tiles_for(e->dma ? kBwd[e->fallback].tile : e->tile, m, k) : 0;
-  if (e->prec == HPVM_PREC_FP32 && m > 0 && k > 0) L.na = std::max(L.na, tiles_for(kOddTile, m, k));
+  if ((e->any || (e->dma && kBwd[e->fallback].any)) && m > 0 && k > 0) L.na = std::max(L.na, tiles_for(odd_tile(e->prec), m, k));
   const DmaPlan d = dma_plan(e, m, n, k);
   if (d.sa) L.na = std::max(L.na, split_sum_blocks(m, k));
   L.nb = elem_blocks(m, n);
@@ -946,7 +976,7 @@ int hpvm_sgemm_backward(int64_t m, int64_t n, int64_t k, float alpha, float beta
   // A DMA entry runs a pass it does not cover in whole, aligned tiles on
   // its fallback entry.
   const BwdEntry* fb = cfg->dma ? &kBwd[cfg->fallback] : cfg;
-  const MfmaEntry* me = find_menu_entry(prec, fb->any ? kOddTile : fb->tile);
+  const MfmaEntry* me = find_menu_entry(prec, fb->any ? odd_tile(prec) : fb->tile);
   const bool dma_a = plan.sa && vec16(G, ldg) && vec16(B, ldb) && (!dA || vec16(dA, ldda)) &&
                      (!dalpha || vec16(A, lda));
   const bool dma_b = plan.sb && vec16(A, lda) && vec16(G, ldg) && vec16(dB, lddb);
@@ -1034,7 +1064,7 @@ int hpvm_sgemm_backward(int64_t m, int64_t n, int64_t k, float alpha, float beta
     a.beta = 0.0f;
     a.vec_a = vec16(G, ldg);
     a.vec_b = vec16(B, ldb);
-    const hpvm_tile& at = fb->any ? kOddTile : fb->tile;  // sgemm_grad_a's
+    const hpvm_tile at = fb->any ? odd_tile(prec) : fb->tile;  // sgemm_grad_a's
     a.tiles_m = (a.m + at.tile_m - 1) / at.tile_m;
     a.tiles_n = (a.n + at.tile_n - 1) / at.tile_n;
     if (dma_a) {

@@ -74,3 +74,26 @@ def test_any_size_backward_integers(gpu, m, n, k, pad, misalign):
             torch.cuda.synchronize()
             for name in need:
                 assert np.array_equal(to_host(got[name]), ref[name]), (tile, need, name)
+
+
+@pytest.mark.parametrize("m,n,k", [(33, 35, 37), (64, 128, 64), (130, 67, 129), (5, 260, 300), (257, 3, 66), (70, 90, 2)])
+@pytest.mark.parametrize("prec", ["bf16", "bf16x3"])
+def test_any_size_backward_integers_bf16(gpu, prec, m, n, k):
+    """The same for the fused BF16 and bf16x3 tiles (integers to 2 are exact in
+    bfloat16, their lo parts zero)."""
+    import torch
+
+    A, B, C, G = (np.clip(x, -2, 2) for x in inputs.backward_operands(m, n, k, seed=m + n + k, dist="int"))
+    a, b, c, g = (x.astype(np.float64) for x in (A, B, C, G))
+    ref = {"dA": 2 * (g @ b.T), "dB": 2 * (a.T @ g), "dC_in": -1 * g, "dalpha": (g * (a @ b)).sum(),
+           "dbeta": (g * c).sum()}
+    assert max(np.abs(v).max() for v in ref.values()) < 2 ** 24
+    for pad, misalign in ((0, False), (3, True)):
+        dev = [to_dev(x, pad, misalign) for x in (A, B, C, G)]
+        for tile in [None] + [t for t in gpu.backward_menu(prec) if t[5] == 2 and t[4] != 128]:
+            print(f"case: backward {prec} {m}x{n}x{k} pad {pad} tile {tile}", flush=True)
+            for need in (("dA", "dB", "dC_in", "dalpha", "dbeta"), ("dA",), ("dB", "dbeta"), ("dalpha",), ("dA", "dB")):
+                got = gpu.sgemm_backward(*dev, 2.0, -1.0, prec=prec, need=need, tile=tile)
+                torch.cuda.synchronize()
+                for name in need:
+                    assert np.array_equal(to_host(got[name]), ref[name]), (tile, need, name)
