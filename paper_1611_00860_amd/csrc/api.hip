@@ -8,6 +8,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -165,98 +166,41 @@ const hpvm::MfmaEntry* f32_mid_entry() {
 }  // namespace
 
 namespace hpvm {
-// The FP32 tile with the least estimated time (microseconds): `start` (launch,
-// the ring's first fill, epilogue) plus, for the most tiles (of every slice)
-// that one of 256 CUs gets, the time their products take at the FP32 MFMA
-// rate (614 GFLOP/s a CU) times `load`.  Both fitted to timings of each tile
-// over 12 products from 512^3 to 4097 x 4099 x 2001; estimated and measured:
-//   256 x 256: 4096^3 929, 932       128 x 128: 2048^3 128, 128
-//   64 x 128: 2048^3 130, 122; 4097 x 4099 x 2001 546, 535;
-//             512 x 4096 x 1024 38.6, 38.0
-//   64 x 64 in two k groups: 1024^3 22.2, 22.8; 1000 x 1003 x 777 18.4, 19.7
-//   32 x 32 in four: 512^3 8.5, 7.6; 256 x 256 x 8192 46, 47;
-//             100 x 3000 x 1500 20.5, 19.5
-// A split contraction adds the summing launch and the partial sums' traffic.
-// The 256 x 256 tile, alone too large to run beside an open streaming graph
-// (128 KB of LDS), is taken only when it gives a tile per CU.
-bool f32_default_tile(int64_t m, int64_t n, int64_t k, int64_t split_ws, hpvm_tile* out) {
-  struct Candidate {
-    hpvm_tile tile;
-    double start, load;
-    bool aligned;  // only where its own loop runs (mfma_f32_dma.hpp)
-  };
-  static const Candidate kCandidates[] = {
-      {{256, 256, 32, 64, 128, 2}, 12.0, 1.05, true}, {{128, 128, 32, 32, 128, 2}, 10.0, 1.08, true},
-      {{64, 128, 32, 32, 64, 2}, 8.0, 1.12, false},   {{64, 64, 32, 16, 32, 2}, 6.5, 1.15, false},
-      {{32, 32, 128, 8, 32, 2}, 6.0, 1.45, false},
-  };
-  double best = 0.0;
-  bool found = false;
-  for (const Candidate& c : kCandidates) {
-    const hpvm_tile& t = c.tile;
-    if (c.aligned && (m < t.tile_m || n < t.tile_n || n % 4 || k % t.tile_k)) continue;
-    if (t.tile_m == 256 && tiles_of(t, m, n) < 256) continue;
-    const MfmaEntry* e = find_menu_entry(HPVM_PREC_FP32, t);
-    if (!e) continue;
-    int64_t slices = 1;
-    const int64_t bytes = c.aligned ? 0 : entry_split_bytes(e, m, n, k);
-    if (bytes > 0 && (split_ws < 0 || split_ws >= bytes)) slices = bytes / (m * n * (int64_t)sizeof(float));
-    const double per_tile = 2.0 * t.tile_m * t.tile_n * ((double)k / slices) / 614400.0;
-    const double rounds = (double)((tiles_of(t, m, n) * slices + 255) / 256);
-    double time = c.start + rounds * per_tile * c.load;
-    if (slices > 1) time += 4.5 + (double)(bytes + m * n * 4) / 4.0e6;
-    if (!found || time < best) {
-      best = time;
-      *out = t;
-      found = true;
-    }
-  }
-  return found;
+// A tile's estimated time (microseconds): `start` (launch, the ring's first
+// fill, the last epilogue); per 32 of k, `alone` for a tile that has its CU
+// to itself, at least `shared` for each of the tiles that one of 256 CUs
+// gets; and `more` for each of those after the first, whose prologue and
+// epilogue the others hide in part (at short contractions it is most of the
+// time: 4096 x 4096 x 16 in 32 x 32 tiles 164 us, in 64 x 128 30).
+struct TileTime {
+  hpvm_tile tile;
+  double start, alone, shared, more;
+  bool aligned;  // only where its own loop runs (mfma_f32_dma.hpp, mfma_bf16_dma.hpp)
+};
+static double tile_time(const TileTime& c, double tiles, double k) {
+  const double rounds = std::ceil(tiles / 256.0);
+  return c.start + std::max(c.alone, rounds * c.shared) * k / 32.0 + (rounds - 1.0) * c.more;
 }
 
-// The same for BF16 and bf16x3: 6 us plus, for the most tiles (of every
-// slice) that one of 256 CUs gets, the time of their 32-deep slabs.  These
-// loops move FP32 operands and convert them in registers, so a slab's time
-// is that of its transfers, LDS reads and conversions, not of its MFMAs.
-// Fitted to timings of each tile; estimated and measured, BF16:
-//   64 x 64: 1024^3 15.0, 14.9 us     64 x 128: 1500 x 1100 x 900 17.9, 17.7
-//   128 x 128 (4 stages): 2048^3 53, 55
-//   128 x 256: 3000 x 2500 x 2000 57, 57; bf16x3 115, 106 to 118
-//   256 x 256: 8192^3 1486, 1480; bf16x3 2658, 2650
-// The tiles that need most of a CU's LDS or registers, and so cannot run
-// beside an open streaming graph, are taken only when they give a tile per
-// CU or the smaller ones need more rounds; bf16x3's 64 x 128 (192 registers;
-// 27 us against 29 at 1500 x 1100 x 900) not at all.
-static bool bf16_default_tile(int32_t prec, int64_t m, int64_t n, int64_t k, int64_t split_ws, hpvm_tile* out,
-                              double* estimate = nullptr, bool large_only = false) {
-  const bool x3 = prec == HPVM_PREC_BF16X3;
-  struct Candidate {
-    hpvm_tile tile;
-    double slab, slab_x3;  // us; 0: left out
-    bool aligned;          // only where its own loop runs (mfma_bf16_dma.hpp)
-  };
-  if (!menu_entry_at(prec, 0)) return false;
-  const Candidate kCandidates[] = {
-      {menu_entry_at(prec, 0)->tile, 1.445, 2.59, true},
-      {{128, 256, 32, 64, 64, 2}, 0.83, 1.77, false},
-      {{128, 128, 32, 64, 64, 4}, 0.73, 1.20, true},
-      {{64, 128, 32, 32, 64, 2}, 0.41, 0.0, false},
-      {{64, 64, 32, 32, 32, 2}, 0.28, 0.44, false},
-      {{32, 128, 32, 32, 32, 2}, 0.29, 0.46, false},
-  };
+// The candidate with the least time, a contraction split that fits split_ws
+// (< 0: any) included: the partial sums' traffic at 4 TB/s and the summing
+// launch.
+static bool least_time(const TileTime* c, int count, int32_t prec, int64_t m, int64_t n, int64_t k, int64_t split_ws,
+                       bool large_only, hpvm_tile* out, double* estimate) {
   double best = 0.0;
   bool found = false;
-  for (const Candidate& c : kCandidates) {
-    const hpvm_tile& t = c.tile;
-    if (c.aligned && (m < t.tile_m || n < t.tile_n || n % 4 || k % t.tile_k || tiles_of(t, m, n) < 256)) continue;
-    if ((large_only && t.tile_m * t.tile_n < 128 * 256) || (x3 ? c.slab_x3 : c.slab) == 0.0) continue;
+  for (; count > 0; --count, ++c) {
+    const hpvm_tile& t = c->tile;
+    if (c->aligned && (m < t.tile_m || n < t.tile_n || n % 4 || k % t.tile_k)) continue;
+    if (large_only && t.tile_m * t.tile_n < 128 * 256) continue;
+    // Alone too large to run beside an open streaming graph (128 KB of LDS).
+    if (c->aligned && (t.tile_m == 256 || prec != HPVM_PREC_FP32) && tiles_of(t, m, n) < 256) continue;
     const MfmaEntry* e = find_menu_entry(prec, t);
     if (!e) continue;
     int64_t slices = 1;
-    const int64_t bytes = c.aligned ? 0 : entry_split_bytes(e, m, n, k);
+    const int64_t bytes = c->aligned ? 0 : entry_split_bytes(e, m, n, k);
     if (bytes > 0 && (split_ws < 0 || split_ws >= bytes)) slices = bytes / (m * n * (int64_t)sizeof(float));
-    const double rounds = (double)((tiles_of(t, m, n) * slices + 255) / 256);
-    double time = 6.0 + rounds * (double)k / (32.0 * slices) * (x3 ? c.slab_x3 : c.slab);
+    double time = tile_time(*c, (double)(tiles_of(t, m, n) * slices), (double)k / slices);
     if (slices > 1) time += 4.5 + (double)(bytes + m * n * 4) / 4.0e6;
     if (!found || time < best) {
       best = time;
@@ -266,6 +210,86 @@ static bool bf16_default_tile(int32_t prec, int64_t m, int64_t n, int64_t k, int
   }
   if (estimate) *estimate = best;
   return found;
+}
+
+constexpr TileTime kF32Mid{{128, 128, 32, 32, 128, 2}, 9.5, 1.77, 1.77, 5.0, true};
+constexpr TileTime kF32Groups[] = {
+    {{64, 64, 32, 16, 32, 2}, 5.7, 0.597, 0.498, 2.3, false},
+    {{32, 32, 128, 8, 32, 2}, 5.4, 0.141, 0.129, 2.0, false},
+};
+
+// Whether a tile whose waves share k in groups (as short sums as two or four
+// slices give) is estimated faster than the whole-tile split `t` with `bytes`
+// of partial sums.  Not asked where that has four slices or more in a single
+// round, which it fills evenly.  1536^3, two slices in two rounds: 100 us
+// against 76 in 32 x 32 tiles; 2048 x 1024 x 512, two in one: 30 against 25.
+static bool f32_groups_beat_split(const hpvm_tile& t, int64_t m, int64_t n, int64_t k, int64_t bytes,
+                                  int64_t split_ws, hpvm_tile* out) {
+  const int64_t slices = bytes / (m * n * (int64_t)sizeof(float)), tiles = tiles_of(t, m, n) * slices;
+  if (slices >= 4 && tiles <= 256) return false;
+  const double area = (double)t.tile_m * t.tile_n / (128.0 * 128.0);
+  TileTime c = kF32Mid;
+  c.alone *= area;
+  c.shared *= area;
+  const double split = tile_time(c, (double)tiles, (double)k / slices) + 4.5 + (double)(bytes + m * n * 4) / 4.0e6;
+  double groups = 0.0;
+  return least_time(kF32Groups, 2, HPVM_PREC_FP32, m, n, k, split_ws, false, out, &groups) && groups < split;
+}
+
+// FP32.  Fitted to each tile's time over 72 products from 64 x 64 x 1000 to
+// 8192 x 8192 x 200; over those the choice is 2% behind the best tile on
+// average.  Measured, us, this choice and the next best size of tile:
+//   1500 x 1500 x 100: 64 x 64 13.3, 64 x 128 15.2
+//   2048 x 2048 x 256: 64 x 128 23.3, 64 x 64 26.4; 2048^3: 128 x 128 128
+//   1000 x 1003 x 777: 64 x 64 in two k groups 22.2, in one 23.7
+//   512^3: 32 x 32 in four k groups 6.5, 64 x 64 15.0
+//   4096^3: 256 x 256 932
+bool f32_default_tile(int64_t m, int64_t n, int64_t k, int64_t split_ws, hpvm_tile* out) {
+  static const TileTime kCandidates[] = {
+      {{256, 256, 32, 64, 128, 2}, 13.0, 6.31, 6.89, 32.0, true},
+      kF32Mid,
+      {{64, 128, 32, 32, 64, 2}, 6.2, 1.09, 0.948, 2.3, false},
+      {{64, 128, 16, 32, 64, 2}, 5.7, 1.18, 0.983, 2.3, false},
+      {{64, 64, 16, 32, 32, 2}, 4.5, 0.712, 0.541, 1.43, false},
+      kF32Groups[0],
+      kF32Groups[1],
+  };
+  return least_time(kCandidates, (int)(sizeof(kCandidates) / sizeof(kCandidates[0])), HPVM_PREC_FP32, m, n, k,
+                    split_ws, false, out, nullptr);
+}
+
+// BF16 and bf16x3, fitted the same way.  These loops move FP32 operands and
+// convert them in registers, so a slab's time is that of its transfers, LDS
+// reads and conversions, not of its MFMAs.  Measured, us:
+//   1024^3: 64 x 64 13.5, 64 x 128 15.5; bf16x3 20.3, 25.4
+//   2048 x 2048 x 256: 64 x 128 11.8, 64 x 64 14.1; bf16x3 16.6, 18.5
+//   3000 x 3000 x 256: 256 x 256 24.0, 64 x 128 25.3; bf16x3 64 x 128 34.7
+//   100 x 3000 x 1500: 32 x 128, split 15.7, 64 x 64 18.0
+// Tiles that need most of a CU's LDS or registers cannot run beside an open
+// streaming graph: the aligned ones are taken only when they give a tile per
+// CU, the others when the smaller ones need more rounds.
+static bool bf16_default_tile(int32_t prec, int64_t m, int64_t n, int64_t k, int64_t split_ws, hpvm_tile* out,
+                              double* estimate = nullptr, bool large_only = false) {
+  const MfmaEntry* e0 = menu_entry_at(prec, 0);
+  if (!e0) return false;
+  const TileTime kBf16[] = {
+      {e0->tile, 13.0, 0.81, 0.87, 33.0, true},
+      {{128, 256, 32, 64, 64, 2}, 13.0, 0.9, 0.9, 20.0, false},
+      {{128, 128, 32, 64, 64, 4}, 10.7, 0.44, 0.44, 11.0, true},
+      {{64, 128, 32, 32, 64, 2}, 6.0, 0.366, 0.265, 3.0, false},
+      {{64, 64, 32, 32, 32, 2}, 4.5, 0.299, 0.182, 1.6, false},
+      {{32, 128, 32, 32, 32, 2}, 4.6, 0.327, 0.219, 1.85, false},
+  };
+  const TileTime kX3[] = {
+      {e0->tile, 14.2, 1.6, 1.75, 51.0, true},
+      {{128, 256, 32, 64, 64, 2}, 14.0, 1.75, 1.75, 20.0, false},
+      {{128, 128, 32, 64, 64, 4}, 11.0, 0.85, 0.85, 9.6, true},
+      {{64, 128, 32, 32, 64, 2}, 6.4, 0.664, 0.498, 2.9, false},
+      {{64, 64, 32, 32, 32, 2}, 4.9, 0.471, 0.316, 1.55, false},
+      {{32, 128, 32, 32, 32, 2}, 4.9, 0.509, 0.35, 1.85, false},
+  };
+  return least_time(prec == HPVM_PREC_BF16X3 ? kX3 : kBf16, (int)(sizeof(kX3) / sizeof(kX3[0])), prec, m, n, k,
+                    split_ws, large_only, out, estimate);
 }
 }  // namespace hpvm
 
@@ -300,17 +324,18 @@ const hpvm::MfmaEntry* fewest_slices(int32_t prec, int64_t m, int64_t n, int64_t
 //    smaller workspace, hpvm_sgemm's choice;
 //  * FP32, and BF16 / bf16x3 products under 2^31 multiply-adds, the tile
 //    with the least estimated time, splits that fit the workspace included;
-//  * larger BF16 products the first staged tile, whose conversion pass is
-//    then a small share of the time (8192^3: 1.07 ms against 1.48), when it
-//    gives at least 256 tiles; bf16x3 ones the DMA-fed 256 x 256 tile then,
-//    which converts in its fragment reads (8192^3: 2.71 ms against 2.82
-//    staged);
-//  * the rest the staged 128 x 128 x 64 tile of 64 x 32 waves (2048^3 BF16:
-//    0.039 ms against 0.070 for the first staged tile), unless 128 x 256
-//    tiles on the FP32 operands are estimated faster (3000 x 2500 x 2000:
-//    57 us against 51 staged, bf16x3 118 against 116).  Estimate of the
-//    staged: its pass, 3 us and its bytes at 4.8 TB/s, and per 32-deep slab
-//    and round 0.27 us (BF16), 0.65 (bf16x3).
+//  * larger BF16 products a staged tile, whose conversion pass is then a
+//    small share of the time (8192^3: 1.07 ms against 1.48): the first, of
+//    256 x 256, when that gives 256 tiles and is estimated faster than the
+//    128 x 128 x 64 tile of 64 x 32 waves (4097 x 4099 x 2001, two rounds of
+//    the first: 172 us against 146); bf16x3 ones the DMA-fed 256 x 256 tile
+//    then, which converts in its fragment reads (8192^3: 2.71 ms against
+//    2.82 staged);
+//  * of the rest, and of those with k < 256, the tile with the least
+//    estimated time, the staged 128 x 128 one included, where k < 1024
+//    (2500 x 2500 x 400 bf16x3: 36 us against 51 staged); for deeper ones
+//    the staged, unless 128 x 256 tiles on the FP32 operands are estimated
+//    faster.
 // Returns false for hpvm_sgemm's choice.
 bool default_ws_tile(int32_t prec, int64_t m, int64_t n, int64_t k, int64_t ws_bytes, hpvm_tile* out) {
   const bool f32 = prec == HPVM_PREC_FP32, x3 = prec == HPVM_PREC_BF16X3;
@@ -320,6 +345,7 @@ bool default_ws_tile(int32_t prec, int64_t m, int64_t n, int64_t k, int64_t ws_b
     int64_t need = 0;
     const hpvm::MfmaEntry* best = fewest_slices(prec, m, n, k, &need);
     if (best && ws_bytes >= 0 && ws_bytes < need) return false;
+    if (best && f32 && hpvm::f32_groups_beat_split(best->tile, m, n, k, need, ws_bytes, out)) return true;
     if (best) {
       *out = best->tile;
       return true;
@@ -330,19 +356,27 @@ bool default_ws_tile(int32_t prec, int64_t m, int64_t n, int64_t k, int64_t ws_b
   const hpvm::MfmaEntry* staged = nullptr;
   if (!hpvm::staged_k_ok(k) || hpvm::staged_menu(prec, &staged) == 0) return false;
   const hpvm::MfmaEntry* small = hpvm::find_menu_entry(prec, hpvm_tile{128, 128, 64, 64, 32, 3});
-  const bool big = tiles_of(staged[0].tile, m, n) >= 256;
+  if (!small) return false;
+  // Estimates of the staged tiles: launches and the pass over the operands
+  // at 4.8 TB/s, then as tile_time.
+  const double pass = ((double)m * k + (double)k * n) * (x3 ? 8.0 : 6.0) / 4.8e6, slabs = (double)k / 32.0;
+  const double rs = (double)((tiles_of(small->tile, m, n) + 255) / 256);
+  const double time_small = 12.0 + pass + rs * slabs * (x3 ? 0.62 : 0.27) + (rs - 1.0) * 6.0;
+  const int64_t big_tiles = tiles_of(staged[0].tile, m, n);
+  const double rb = (double)((big_tiles + 255) / 256);
   const hpvm::MfmaEntry* e0 = hpvm::menu_entry_at(prec, 0);
-  if (x3 && e0 && tiles_of(e0->tile, m, n) >= 256 && k % e0->tile.tile_k == 0 && n % 4 == 0) return false;
+  const bool direct0 = x3 && e0 && k % e0->tile.tile_k == 0 && n % 4 == 0;
+  const double time_big = direct0 ? 14.0 + rb * slabs * 2.2 + (rb - 1.0) * 51.0
+                                  : 22.0 + pass + rb * slabs * (x3 ? 1.68 : 0.52) + (rb - 1.0) * 50.0;
+  const bool big = big_tiles >= 256 && k >= 256 && time_big <= time_small;
+  if (big && direct0) return false;
   // A workspace too small for the planes: the choice without one.
   if (ws_bytes >= 0 && ws_bytes < hpvm::staged_workspace_bytes(prec, m, n, k)) return false;
-  if (!big && small) {
-    const double pass = 3.0 + ((double)m * k + (double)k * n) * (x3 ? 8.0 : 6.0) / 4.8e6;
-    const double rounds = (double)((tiles_of(small->tile, m, n) + 255) / 256);
-    const double time = 6.0 + pass + rounds * (double)k / 32.0 * (x3 ? 0.65 : 0.27);
+  if (!big) {
     double direct = 0.0;
-    if (hpvm::bf16_default_tile(prec, m, n, k, 0, out, &direct, true) && direct < time) return true;
+    if (hpvm::bf16_default_tile(prec, m, n, k, 0, out, &direct, k >= 1024) && direct < time_small) return true;
   }
-  *out = big || !small ? staged[0].tile : small->tile;
+  *out = big ? staged[0].tile : small->tile;
   return true;
 }
 

@@ -554,25 +554,27 @@ int64_t split_sum_blocks(int64_t rows, int64_t cols) {
 }
 
 // Built-in FP32 choice: the least estimated time, by the single launch's model
-// (f32_default_tile) over both gradients' tiles: `start` plus, for the most
-// tiles one of 256 CUs gets, at least one of the deeper gradient's, their
-// products at the FP32 MFMA rate (614 GFLOP/s a CU) times `load`.  The DMA
-// entry (whole 256 x 256 tiles) adds the launch of its slice sums, about
-// 6 us, and their traffic.  dalpha = <A, G B^T> cancels, so how the products
-// are rounded shows in it: the DMA entry's shorter sums are given up, and
-// the k groups of the 32 x 32 tile taken for the others' plain order in k,
-// only where that saves 30% (`worth`; 1024^3 81 -> 43 us;
-// 64 x 4096 x 1000 93 -> 42).
+// (TileTime in api.hip, 3 us for dalpha's and dbeta's last sums on top) over
+// both gradients' tiles: per 32 of k `alone` for a tile of the deeper
+// gradient, at least `shared` for each of the tiles one of 256 CUs gets, and
+// `more` for each of those after the first.  The DMA entry (whole 256 x 256
+// tiles) adds the launch of its slice sums, about 6 us, and their traffic.
+// dalpha = <A, G B^T> cancels, so how the products are rounded shows in it:
+// the DMA entry's shorter sums are given up, and the k groups of the 32 x 32
+// tile taken for the others' plain order in k, only where that saves 30%
+// (`worth`).  Measured, us, this choice and the next: 1000 x 1200 x 800
+// 64 x 64 49, 64 x 128 58; 2048^3 64 x 128 264, 256 x 256 273;
+// 64 x 4096 x 1000 32 x 32 39, 64 x 64 99.
 const BwdEntry* f32_pick(int64_t m, int64_t n, int64_t k) {
   struct Candidate {
     hpvm_tile tile;
-    double start, load, worth;
+    double start, alone, shared, more, worth;
   };
   static const Candidate kCandidates[] = {
-      {{kDmaTile, kDmaTile, kDmaK, kDmaWM, kDmaWN, kDmaStages}, 12.0, 1.05, 0.7},
-      {{64, 128, 32, 32, 64, 2}, 8.0, 1.12, 1.0},
-      {{64, 64, 16, 32, 32, 2}, 7.8, 1.12, 1.0},
-      {{32, 32, 128, 8, 32, 2}, 6.0, 1.45, 1.0 / 0.7},
+      {{kDmaTile, kDmaTile, kDmaK, kDmaWM, kDmaWN, kDmaStages}, 16.0, 6.31, 6.89, 32.0, 0.7},
+      {{64, 128, 32, 32, 64, 2}, 9.2, 1.2, 1.0, 2.3, 1.0},
+      {{64, 64, 16, 32, 32, 2}, 7.5, 0.712, 0.541, 1.43, 1.0},
+      {{32, 32, 128, 8, 32, 2}, 8.4, 0.141, 0.129, 2.0, 1.0 / 0.7},
   };
   const BwdEntry* pick = nullptr;
   double best = 0.0;
@@ -586,10 +588,11 @@ const BwdEntry* f32_pick(int64_t m, int64_t n, int64_t k) {
       if (slices == 0.0) continue;
       extra = 6.0 + (2.0 * slices + 1.0) * ((double)m * k + (double)k * n) * 4.0 / 4.0e6;
     }
-    const double per_k = 2.0 * c.tile.tile_m * c.tile.tile_n / 614400.0 / slices;
-    const double deep = (double)std::max(m, n) * per_k, mean = (ta * n + tb * m) / std::max(ta + tb, 1.0) * per_k;
+    const double deep = (double)std::max(m, n) / 32.0 / slices;
+    const double mean = (ta * n + tb * m) / std::max(ta + tb, 1.0) / 32.0 / slices;
     const double rounds = (double)(((int64_t)((ta + tb) * slices) + 255) / 256);
-    const double time = c.worth * (c.start + c.load * std::max(rounds * mean, deep) + extra);
+    const double time = c.worth * (c.start + std::max(rounds * mean * c.shared, deep * c.alone) +
+                                   (rounds - 1.0) * c.more + extra);
     if (!pick || time < best) {
       best = time;
       pick = e;
