@@ -244,6 +244,13 @@ int hpvm_sgemm_ws(int64_t m, int64_t n, int64_t k, float alpha, const float* A, 
                   const float* B, int64_t ldb, float beta, float* C, int64_t ldc, int32_t prec,
                   const hpvm_tile* tile, void* workspace, int64_t workspace_bytes, void* stream);
 
+/* hpvm_sgemm_workspace_bytes and, where that is 0, hpvm_sgemm, in one call.
+ * Returns HPVM_OK (launched), an error (negative), or the bytes needed
+ * (positive: nothing was launched; call hpvm_sgemm_ws with that much).      */
+int64_t hpvm_sgemm_or_bytes(int64_t m, int64_t n, int64_t k, float alpha, const float* A, int64_t lda,
+                            const float* B, int64_t ldb, float beta, float* C, int64_t ldc, int32_t prec,
+                            const hpvm_tile* tile, void* stream);
+
 /* D <- alpha * A B + beta * C: hpvm_sgemm_ws with the result in a matrix of
  * its own (what an out-of-place caller would copy C for first).  C is only
  * read, and not at all when beta == 0 (NULL then); D may be C itself, with

@@ -61,13 +61,18 @@ def _tile(tile):
 
 
 def _stream(stream=None):
+    """The HIP stream's handle; without one torch's current stream.  Read raw
+    (0.4 us): torch.cuda.current_stream() builds an object around it, 3 us of
+    every call."""
     import torch
 
     if stream is None:
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         if not torch.cuda.is_available():
-            return ctypes.c_void_p(None)  # host-only calls; a HIP call then fails loudly
+            return None  # host-only calls; a HIP call then fails loudly
         stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    return stream.cuda_stream
 
 
 def _empty(shape, dtype, device, stream=None):
@@ -87,7 +92,7 @@ def _empty(shape, dtype, device, stream=None):
         return torch.empty(shape, dtype=dtype, device=device)
 
 
-def _mat(t, name, rows=None, cols=None):
+def _mat(t, name):
     """(pointer, leading dimension) of a 2-D row-major float32 device tensor."""
     import torch
 
@@ -97,10 +102,12 @@ def _mat(t, name, rows=None, cols=None):
         raise TypeError(f"{name} must be a 2-D float32 tensor")
     if not t.is_cuda:
         raise TypeError(f"{name} must live on the GPU")
-    if t.numel() and t.stride(1) != 1 and t.shape[1] > 1:
+    rows, cols = t.shape
+    step, unit = t.stride()
+    if rows and cols > 1 and unit != 1:
         raise ValueError(f"{name} must have unit column stride (row-major)")
-    ld = t.stride(0) if t.shape[0] > 1 else max(t.shape[1], 1)
-    return ctypes.c_void_p(t.data_ptr() if t.numel() else 0), max(ld, 1)
+    ld = step if rows > 1 else cols
+    return (t.data_ptr() if rows and cols else 0), (ld if ld > 0 else 1)
 
 
 def workspace_bytes(m: int, n: int, k: int, prec="fp32", tile=None) -> int:
@@ -135,15 +142,21 @@ def sgemm(A, B, C, alpha: float = 1.0, beta: float = 0.0, prec="fp32", tile=None
     pa, lda = _mat(A, "A")
     pb, ldb = _mat(B, "B")
     pc, ldc = _mat(C, "C")
-    need = 0 if workspace is False else workspace_bytes(m, n, k, prec, tile)
-    if need == 0:
+    if workspace is False:
         _check(lib.hpvm_sgemm(m, n, k, float(alpha), pa, lda, pb, ldb, float(beta), pc, ldc,
                               _prec(prec), _tile(tile), _stream(stream)))
+        return C
+    # One call into the library where no workspace is needed (1 us less than
+    # asking first).
+    need = lib.hpvm_sgemm_or_bytes(m, n, k, float(alpha), pa, lda, pb, ldb, float(beta), pc, ldc, _prec(prec),
+                                   _tile(tile), _stream(stream))
+    if need <= 0:
+        _check(need)
         return C
     if workspace is None or workspace.numel() * workspace.element_size() < need:
         workspace = _empty(need, torch.uint8, C.device, stream)
     _check(lib.hpvm_sgemm_ws(m, n, k, float(alpha), pa, lda, pb, ldb, float(beta), pc, ldc,
-                             _prec(prec), _tile(tile), ctypes.c_void_p(workspace.data_ptr()),
+                             _prec(prec), _tile(tile), workspace.data_ptr(),
                              workspace.numel() * workspace.element_size(), _stream(stream)))
     return C
 
@@ -165,7 +178,7 @@ def sgemm_into(A, B, C, D, alpha: float = 1.0, beta: float = 0.0, prec="fp32", t
     need = workspace_bytes(m, n, k, prec, tile)
     ws = _empty(need, torch.uint8, D.device, stream) if need else None
     _check(lib.hpvm_sgemm_into(m, n, k, float(alpha), pa, lda, pb, ldb, float(beta), pc, ldc, pd, ldd, _prec(prec),
-                               _tile(tile), ctypes.c_void_p(ws.data_ptr() if need else None), need, _stream(stream)))
+                               _tile(tile), ws.data_ptr() if need else None, need, _stream(stream)))
     return D
 
 
@@ -210,7 +223,7 @@ def launch_root(A, B, C, k: int, alpha: float, beta: float, block, grid, stream=
         return (t.untyped_storage().nbytes() - t.storage_offset() * 4) if t.numel() else 0
 
     bA, bB, bC = bytes_override or (nbytes(A), nbytes(B), nbytes(C))
-    r = _lib.RootIn(pa.value, bA, lda, pb.value, bB, ldb, pc.value, bC, ldc, int(k),
+    r = _lib.RootIn(pa, bA, lda, pb, bB, ldb, pc, bC, ldc, int(k),
                     float(alpha), float(beta), int(block[0]), int(block[1]), int(grid[0]),
                     int(grid[1]))
     _check(lib.hpvm_launch_root(ctypes.byref(r), _stream(stream)))
@@ -309,7 +322,7 @@ def sgemm_backward(A, B, C_in, G, alpha: float, beta: float, prec="fp32", need=(
 
     def mat(name, t, rows, cols):
         if t is None:
-            return ctypes.c_void_p(0), max(cols, 1)
+            return 0, max(cols, 1)
         return _mat(t, name)
 
     pa, lda = mat("A", A, m, k)
@@ -320,11 +333,11 @@ def sgemm_backward(A, B, C_in, G, alpha: float, beta: float, prec="fp32", need=(
     pdb, lddb = mat("dB", out.get("dB"), k, n)
     pdc, lddc = mat("dC_in", out.get("dC_in"), m, n)
     base = scal.data_ptr()
-    da = ctypes.c_void_p(base) if "dalpha" in need else ctypes.c_void_p(0)
-    db = ctypes.c_void_p(base + 4) if "dbeta" in need else ctypes.c_void_p(0)
+    da = base if "dalpha" in need else 0
+    db = base + 4 if "dbeta" in need else 0
     _check(lib.hpvm_sgemm_backward(m, n, k, float(alpha), float(beta), pa, lda, pb, ldb, pci, ldci,
                                    pg, ldg, pda, ldda, pdb, lddb, pdc, lddc, da, db, _prec(prec),
-                                   _tile(tile), ctypes.c_void_p(ws.data_ptr()), ws.numel(),
+                                   _tile(tile), ws.data_ptr(), ws.numel(),
                                    _stream(stream)))
     if "dalpha" in need:
         out["dalpha"] = scal[0]
@@ -352,8 +365,8 @@ def autotune_backward(A, B, G, prec="fp32", reps: int = 3, stream=None):
     best = _lib.Tile()
     ms = ctypes.c_float(0.0)
     _check(lib.hpvm_autotune_backward(m, n, k, _prec(prec), pa, lda, pb, ldb, pg, ldg,
-                                      ctypes.c_void_p(dA.data_ptr()), k, ctypes.c_void_p(dB.data_ptr()), n,
-                                      ctypes.c_void_p(ws.data_ptr()), need, int(reps), _stream(stream),
+                                      dA.data_ptr(), k, dB.data_ptr(), n,
+                                      ws.data_ptr(), need, int(reps), _stream(stream),
                                       ctypes.byref(best), ctypes.byref(ms)))
     return best.as_tuple(), ms.value
 
@@ -385,7 +398,7 @@ def autotune(A, B, prec="fp32", reps: int = 5, scratch=None, stream=None, allow_
     best = _lib.Tile()
     ms = ctypes.c_float(0.0)
     _check(load().hpvm_autotune(m, n, k, _prec(prec), pa, lda, pb, ldb, pc, ldc,
-                                ctypes.c_void_p(ws.data_ptr()), need, int(reps), _stream(stream),
+                                ws.data_ptr(), need, int(reps), _stream(stream),
                                 ctypes.byref(best), ctypes.byref(ms)))
     return best.as_tuple(), ms.value
 
@@ -466,8 +479,8 @@ class GroupedPlan:
             pa, lda = _mat(A, f"A[{i}]")
             pb, ldb = _mat(B, f"B[{i}]")
             pc, ldc = _mat(C, f"C[{i}]")
-            descs[i] = _lib.SgemmDesc(m, nn, k, float(alphas[i]), float(betas[i]), pa.value, lda,
-                                      pb.value, ldb, pc.value, ldc)
+            descs[i] = _lib.SgemmDesc(m, nn, k, float(alphas[i]), float(betas[i]), pa, lda,
+                                      pb, ldb, pc, ldc)
         h = ctypes.c_void_p()
         _check(lib.hpvm_grouped_plan_create(n, descs, _prec(prec), _tile(tile), ctypes.byref(h)))
         self._h = h
@@ -501,7 +514,7 @@ class GroupedPlan:
         scratch = _empty(max(self.info()["scratch_bytes"] // 4, 1), torch.float32, self.workspace.device, stream)
         ws, nb = self._ws(stream)
         best = ctypes.c_float(0.0)
-        _check(load().hpvm_grouped_autotune(self._h, ws, nb, ctypes.c_void_p(scratch.data_ptr()),
+        _check(load().hpvm_grouped_autotune(self._h, ws, nb, scratch.data_ptr(),
                                             scratch.numel() * 4, int(reps), _stream(stream),
                                             ctypes.byref(best)))
         return best.value
@@ -556,7 +569,7 @@ def sgemm_consumer(A, B, C, alpha: float = 1.0, beta: float = 0.0, op="none", bi
         raise ValueError("C and D must be m x n")
     pa, lda = _mat(A, "A")
     pb, ldb = _mat(B, "B")
-    pc, ldc = _mat(C, "C") if C is not None else (ctypes.c_void_p(0), max(n, 1))
+    pc, ldc = _mat(C, "C") if C is not None else (0, max(n, 1))
     pd, ldd = _mat(D, "D")
     code = CONSUMER_OPS[op] if isinstance(op, str) else int(op)
     pbias = 0
@@ -610,7 +623,7 @@ def sgemm_pair(A, B1, C1, B2, C2, alpha1: float = 1.0, beta1: float = 0.0, alpha
         workspace = _empty(need, torch.uint8, C1.device, stream)
     _check(lib.hpvm_sgemm_pair_ws(m, n, k, pa, lda, float(alpha1), p1, l1, float(beta1), q1, m1,
                                   float(alpha2), p2, l2, float(beta2), q2, m2, _tile(tile),
-                                  ctypes.c_void_p(workspace.data_ptr()), workspace.numel() * workspace.element_size(),
+                                  workspace.data_ptr(), workspace.numel() * workspace.element_size(),
                                   _stream(stream)))
     return C1, C2
 
@@ -783,14 +796,14 @@ class SgemmStream:
             k = A.shape[1]
         elif k is None:
             raise ValueError("k is needed when A is None")
-        pa, lda = _mat(A, "A") if A is not None else (ctypes.c_void_p(0), max(k, 1))
-        pb, ldb = _mat(B, "B") if B is not None else (ctypes.c_void_p(0), max(n, 1))
+        pa, lda = _mat(A, "A") if A is not None else (0, max(k, 1))
+        pb, ldb = _mat(B, "B") if B is not None else (0, max(n, 1))
         pc, ldc = _mat(C, "C")
         if A is not None and tuple(A.shape) != (m, k):
             raise ValueError("A must be m x k")
         if B is not None and tuple(B.shape) != (k, n):
             raise ValueError("B must be k x n")
-        d = _lib.SgemmDesc(m, n, k, float(alpha), float(beta), pa.value, lda, pb.value, ldb, pc.value, ldc)
+        d = _lib.SgemmDesc(m, n, k, float(alpha), float(beta), pa, lda, pb, ldb, pc, ldc)
         return d, (A, B, C)
 
     def push_packed(self, packed) -> int:

@@ -109,6 +109,7 @@ SIGNATURES = {
                                      PTile, ctypes.POINTER(f32)]),
     "hpvm_sgemm_ws": (ctypes.c_int, [i64, i64, i64, f32, vp, i64, vp, i64, f32, vp, i64, i32, PTile, vp, i64,
                                      vp]),
+    "hpvm_sgemm_or_bytes": (i64, [i64, i64, i64, f32, vp, i64, vp, i64, f32, vp, i64, i32, PTile, vp]),
     "hpvm_sgemm_into": (ctypes.c_int, [i64, i64, i64, f32, vp, i64, vp, i64, f32, vp, i64, vp, i64, i32, PTile,
                                        vp, i64, vp]),
     "hpvm_sgemm_workspace_bytes": (ctypes.c_int, [i64, i64, i64, i32, PTile, Pi64]),

@@ -665,6 +665,15 @@ int hpvm_sgemm_workspace_bytes(int64_t m, int64_t n, int64_t k, int32_t prec, co
   return ok();
 }
 
+int64_t hpvm_sgemm_or_bytes(int64_t m, int64_t n, int64_t k, float alpha, const float* A, int64_t lda, const float* B,
+                            int64_t ldb, float beta, float* C, int64_t ldc, int32_t prec, const hpvm_tile* tile,
+                            void* stream) {
+  int64_t need = 0;
+  const int rc = hpvm_sgemm_workspace_bytes(m, n, k, prec, tile, &need);
+  if (rc != HPVM_OK || need > 0) return rc != HPVM_OK ? rc : need;
+  return hpvm_sgemm(m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, prec, tile, stream);
+}
+
 int hpvm_launch_root(const hpvm_root_in* r, void* stream) {
   if (!r) return fail(HPVM_INVALID_ARG, "argument 1: args is NULL");
   if (r->block_x <= 0 || r->block_y <= 0 || r->grid_x < 0 || r->grid_y < 0)
