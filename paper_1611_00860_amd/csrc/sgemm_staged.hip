@@ -393,38 +393,43 @@ template <int BM, int BN>
 __device__ __forceinline__ void dalpha_epilogue(const StagedArgs& p, const f32x16 (&acc)[BM][BN], int row0,
                                                 int col0, int lane, int tile, char* smem) {
   constexpr int kBatch = (BM * BN * 16 <= 64) ? BM : 1;  // row blocks loaded together
+  const int64_t ldc = p.ldc, ldao = p.lda_orig;
+  const int i0 = row0 + acc_row(0, lane), j0 = col0 + acc_col(lane);
+  float* out = p.C ? p.C + (int64_t)i0 * ldc + j0 : nullptr;
+  const float* aorig = p.aorig + (int64_t)i0 * ldao + j0;
   float part = 0.0f;
+  auto store = [&](auto all) {  // addresses as in store_c
+    constexpr bool kAll = decltype(all)::value;
 #pragma unroll
-  for (int b0 = 0; b0 < BM; b0 += kBatch) {
-    float a[kBatch][BN][16];
+    for (int b0 = 0; b0 < BM; b0 += kBatch) {
+      float a[kBatch][BN][16];
 #pragma unroll
-    for (int bi = 0; bi < kBatch; ++bi)
+      for (int bi = 0; bi < kBatch; ++bi)
 #pragma unroll
-      for (int bj = 0; bj < BN; ++bj) {
-        const int j = col0 + 32 * bj + acc_col(lane);
+        for (int bj = 0; bj < BN; ++bj)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int i = row0 + 32 * (b0 + bi) + acc_row(r, lane);
-          a[bi][bj][r] = (i < p.m && j < p.n) ? p.aorig[(int64_t)i * p.lda_orig + j] : 0.0f;
-        }
-      }
+          for (int r = 0; r < 16; ++r) {
+            const int i = 32 * (b0 + bi) + acc_row(r, 0), j = 32 * bj;
+            const float* q = aorig + (int64_t)i * ldao + j;
+            if (!kAll && !(i0 + i < p.m && j0 + j < p.n)) q = p.aorig;  // some element, not used
+            a[bi][bj][r] = *q;
+          }
 #pragma unroll
-    for (int bi = 0; bi < kBatch; ++bi)
+      for (int bi = 0; bi < kBatch; ++bi)
 #pragma unroll
-      for (int bj = 0; bj < BN; ++bj) {
-        const int j = col0 + 32 * bj + acc_col(lane);
-        if (j >= p.n) continue;
+        for (int bj = 0; bj < BN; ++bj)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int i = row0 + 32 * (b0 + bi) + acc_row(r, lane);
-          if (i < p.m) {
+          for (int r = 0; r < 16; ++r) {
+            const int i = 32 * (b0 + bi) + acc_row(r, 0), j = 32 * bj;
+            if (!kAll && !(i0 + i < p.m && j0 + j < p.n)) continue;
             const float v = acc[b0 + bi][bj][r];
-            if (p.C) p.C[(int64_t)i * p.ldc + j] = p.alpha * v;
+            if (out) out[(int64_t)i * ldc + j] = p.alpha * v;
             part = fmaf(a[bi][bj][r], v, part);
           }
-        }
-      }
-  }
+    }
+  };
+  if (row0 + 32 * BM <= p.m && col0 + 32 * BN <= p.n) store(std::true_type{});
+  else store(std::false_type{});
   const float sum = block_sum(part, reinterpret_cast<float*>(smem));
   if (threadIdx.x == 0) p.partial[tile] = sum;
 }
