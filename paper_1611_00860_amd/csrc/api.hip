@@ -273,7 +273,7 @@ static bool bf16_default_tile(int32_t prec, int64_t m, int64_t n, int64_t k, int
   const MfmaEntry* e0 = menu_entry_at(prec, 0);
   if (!e0) return false;
   const TileTime kBf16[] = {
-      {e0->tile, 13.0, 0.81, 0.87, 33.0, true},
+      {e0->tile, 28.0, 0.72, 1.15, 28.0, true},
       {{128, 256, 32, 64, 64, 2}, 13.0, 0.9, 0.9, 20.0, false},
       {{128, 128, 32, 64, 64, 4}, 10.7, 0.44, 0.44, 11.0, true},
       {{64, 128, 32, 32, 64, 2}, 6.0, 0.366, 0.265, 3.0, false},
@@ -281,7 +281,7 @@ static bool bf16_default_tile(int32_t prec, int64_t m, int64_t n, int64_t k, int
       {{32, 128, 32, 32, 32, 2}, 4.6, 0.327, 0.219, 1.85, false},
   };
   const TileTime kX3[] = {
-      {e0->tile, 14.2, 1.6, 1.75, 51.0, true},
+      {e0->tile, 28.0, 2.4, 2.2, 48.0, true},
       {{128, 256, 32, 64, 64, 2}, 14.0, 1.75, 1.75, 20.0, false},
       {{128, 128, 32, 64, 64, 4}, 11.0, 0.85, 0.85, 9.6, true},
       {{64, 128, 32, 32, 64, 2}, 6.4, 0.664, 0.498, 2.9, false},
@@ -328,7 +328,7 @@ const hpvm::MfmaEntry* fewest_slices(int32_t prec, int64_t m, int64_t n, int64_t
 //    small share of the time (8192^3: 1.07 ms against 1.48): the first, of
 //    256 x 256, when that gives 256 tiles and is estimated faster than the
 //    128 x 128 x 64 tile of 64 x 32 waves (4097 x 4099 x 2001, two rounds of
-//    the first: 172 us against 146); bf16x3 ones the DMA-fed 256 x 256 tile
+//    the first: 148 us against 138); bf16x3 ones the DMA-fed 256 x 256 tile
 //    then, which converts in its fragment reads (8192^3: 2.71 ms against
 //    2.82 staged);
 //  * of the rest, and of those with k < 256, the tile with the least
@@ -366,8 +366,8 @@ bool default_ws_tile(int32_t prec, int64_t m, int64_t n, int64_t k, int64_t ws_b
   const double rb = (double)((big_tiles + 255) / 256);
   const hpvm::MfmaEntry* e0 = hpvm::menu_entry_at(prec, 0);
   const bool direct0 = x3 && e0 && k % e0->tile.tile_k == 0 && n % 4 == 0;
-  const double time_big = direct0 ? 14.0 + rb * slabs * 2.2 + (rb - 1.0) * 51.0
-                                  : 22.0 + pass + rb * slabs * (x3 ? 1.68 : 0.52) + (rb - 1.0) * 50.0;
+  const double time_big = direct0 ? 28.0 + rb * slabs * 2.2 + (rb - 1.0) * 48.0
+                                  : 26.0 + pass + rb * slabs * (x3 ? 1.9 : 0.85) + (rb - 1.0) * 45.0;
   const bool big = big_tiles >= 256 && k >= 256 && time_big <= time_small;
   if (big && direct0) return false;
   // A workspace too small for the planes: the choice without one.
