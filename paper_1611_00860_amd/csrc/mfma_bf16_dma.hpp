@@ -275,6 +275,7 @@ __global__ void __launch_bounds__((Bf16SrcShape<TM, TN, TK, WM, WN, AT, BT, NST>
     __attribute__((amdgpu_waves_per_eu(1, (Bf16SrcShape<TM, TN, TK, WM, WN, AT, BT, NST>::kMaxWaves))))
     sgemm_bf16src_dma(GemmArgs p, F32DmaOut o) {
   extern __shared__ __align__(16) char smem[];
+  read_early(p);
   const int tiles = p.tiles_m * p.tiles_n;
   const int z = blockIdx.x / tiles;
   int tm, tn;

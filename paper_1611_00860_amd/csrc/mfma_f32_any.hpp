@@ -490,6 +490,8 @@ template <int TM, int TN, int TK, int WM, int WN, bool AT, bool BT, int NST, int
 __global__ void __launch_bounds__((AnyShape<TM, TN, TK, WM, WN, AT, BT, NST, KW>::kThreads))
     __attribute__((amdgpu_waves_per_eu((AnyShape<TM, TN, TK, WM, WN, AT, BT, NST, KW>::kMinWaves)))) sgemm_f32_any(GemmArgs p, F32DmaOut o) {
   extern __shared__ __align__(16) char smem[];
+  read_early(p);
+  if constexpr (MODE == kDmaConsume) read_early(o.D, o.ldd, o.bias, o.op, o.lo, o.hi);
   using S = AnyShape<TM, TN, TK, WM, WN, AT, BT, NST, KW>;
   const int tiles = p.tiles_m * p.tiles_n;
   const int z = blockIdx.x / tiles;

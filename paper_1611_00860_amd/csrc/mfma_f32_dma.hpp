@@ -372,6 +372,8 @@ __global__ void __launch_bounds__((F32DmaShape<TM, TN, TK, WM, WN, AT, BT, NST, 
                                             : 3))))
     sgemm_f32_dma(GemmArgs p, GemmArgs p2, F32DmaOut o) {
   extern __shared__ __align__(16) char smem[];
+  read_early(p);
+  if constexpr (MODE == kDmaConsume) read_early(o.D, o.ldd, o.bias, o.op, o.lo, o.hi);
   const int tiles = p.tiles_m * p.tiles_n;
   const int z = blockIdx.x / tiles;
   int tm, tn;

@@ -328,6 +328,7 @@ __global__ void __launch_bounds__((AnyShape<TM, TN, TK, WM, WN, false, true, NST
   using SB = AnyShape<TM, TN, TK, WM, WN, true, false, NST, KW>;
   int t = blockIdx.x, tm, tn;
   if (t < tiles_a) {
+    read_early(a.C, a.ldc, a.alpha, aorig, ldao, partial);
     tile_coords(a.tiles_m, a.tiles_n, t, tm, tn);
     float part = 0.0f;
     any_tile<SA, AnyMath<PREC, SA>>(
@@ -349,6 +350,7 @@ __global__ void __launch_bounds__((AnyShape<TM, TN, TK, WM, WN, false, true, NST
   }
   t -= tiles_a;
   if (t < tiles_b) {
+    read_early(b.C, b.ldc, b.alpha, b.beta);
     tile_coords(b.tiles_m, b.tiles_n, t, tm, tn);
     any_tile<SB, AnyMath<PREC, SB>>(
         b, 1, tm, tn, 0, smem,

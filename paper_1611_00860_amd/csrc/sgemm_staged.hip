@@ -582,6 +582,8 @@ __device__ __forceinline__ void bf16_dma_tile(const StagedArgs& p, int tile, cha
   constexpr int BM = S::BM, BN = S::BN, QA = S::QA, QB = S::QB, KS = TK / 16, R = S::kRowsPerDma;
   constexpr int P = S::kPlanes;
 
+  if constexpr (EPI == 0) read_early(p.C, p.ldc, p.m, p.n, p.alpha, p.beta, p.Cin, p.ldci);
+  else read_early(p.C, p.ldc, p.m, p.n, p.alpha, p.aorig, p.lda_orig, p.partial);
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int wm0 = (wave / (TN / WN)) * WM, wn0 = (wave % (TN / WN)) * WN;
