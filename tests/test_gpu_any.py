@@ -97,3 +97,41 @@ def test_any_size_backward_integers_bf16(gpu, prec, m, n, k):
                 torch.cuda.synchronize()
                 for name in need:
                     assert np.array_equal(to_host(got[name]), ref[name]), (tile, need, name)
+
+
+@pytest.mark.parametrize("prec", ["bf16", "bf16x3"])
+@pytest.mark.parametrize("m,n,k", [(16, 520, 2048), (33, 35, 2051), (64, 64, 1024), (1, 5, 9000)])
+def test_ragged_split_contraction_integers_bf16(gpu, prec, m, n, k):
+    """The 32 x 128 tile's slices, through a workspace and as one launch."""
+    import torch
+
+    A, B, C = (np.clip(x, -2, 2) for x in inputs.sgemm_operands(m, n, k, seed=m + k, dist="int"))
+    ref = oracle.sgemm(A, B, C, 1.0, -2.0)
+    for pad, misalign in ((0, False), (3, True)):
+        for workspace in (None, False):
+            print(f"case: split {prec} {m}x{n}x{k} pad {pad} workspace {workspace}", flush=True)
+            dA, dB, dC = (to_dev(x, pad, misalign) for x in (A, B, C))
+            gpu.sgemm(dA, dB, dC, 1.0, -2.0, prec=prec, tile=(32, 128, 32, 32, 32, 2), workspace=workspace)
+            torch.cuda.synchronize()
+            assert np.array_equal(to_host(dC), ref)
+
+
+def test_grouped_narrow_instances_replayed(gpu):
+    """Instances narrower than a 16-byte transfer beside ragged and whole ones;
+    every run and every replay starts from a cleared tile counter."""
+    import torch
+
+    sizes = [(33, 3, 70), (5, 2, 9), (64, 1, 31), (130, 67, 129), (257, 300, 40), (128, 128, 64), (3, 4, 1)]
+    ops = [inputs.sgemm_operands(m, n, k, seed=i, dist="int") for i, (m, n, k) in enumerate(sizes)]
+    refs = [oracle.sgemm(A, B, C, 1.0, -2.0) for A, B, C in ops]
+    As, Bs, Cs = ([to_dev(o[j], 3, True) for o in ops] for j in range(3))
+    plan = gpu.GroupedPlan(As, Bs, Cs, [1.0] * len(sizes), [-2.0] * len(sizes))
+    graph = plan.capture()
+    for run in (plan.run, graph.launch, graph.launch, plan.run, graph.launch):
+        for c, o in zip(Cs, ops):
+            c.copy_(torch.from_numpy(o[2]))
+        print(f"case: grouped narrow {run.__qualname__}", flush=True)
+        run()
+        torch.cuda.synchronize()
+        for c, ref, size in zip(Cs, refs, sizes):
+            assert np.array_equal(to_host(c), ref), size
