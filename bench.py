@@ -54,7 +54,8 @@ def log(msg):
 # HBM traffic of the FP32 kernel, from rocprofv3 FETCH_SIZE / WRITE_SIZE runs  #
 # --------------------------------------------------------------------------- #
 TRAFFIC_TABLE = os.path.join(ROOT, "profiles", "fp32_sgemm_tiles_traffic.txt")
-KERNEL_SOURCES = ("device_common.hpp", "mfma_f32.hpp", "lds_dma.hpp", "mfma_f32_dma.hpp", "sgemm_mfma.hip")
+KERNEL_SOURCES = ("device_common.hpp", "mfma_f32.hpp", "lds_dma.hpp", "mfma_f32_dma.hpp", "mfma_f32_any.hpp",
+                  "sgemm_mfma.hip")
 COPY_BYTES = 1 << 30  # the calibration copy: 1 GiB read, 1 GiB written
 SWEEP_REPS = 2  # launches per (tile, workload entry) in a counter run
 
@@ -71,7 +72,7 @@ def kernel_source_sha():
 
 
 def is_fp32_gemm(kernel_name):
-    return "sgemm_f32_dma<" in kernel_name or "sgemm_mfma_f32<" in kernel_name
+    return any(k in kernel_name for k in ("sgemm_f32_dma<", "sgemm_f32_any<", "sgemm_mfma_f32<"))
 
 
 def fp32_kernel_name(tile, m, n, k):
@@ -136,7 +137,7 @@ def build_traffic_table(fetch_csv, write_csv, fetch_log, write_log, command):
         for r, (tile, m, n, k, beta) in zip(gemm, seq):
             key = _tile_key(tile, m, n, k, beta)
             result.setdefault(key, {}).setdefault(counter, []).append(float(r["Counter_Value"]) * 1024 * factor)
-    lines = ["# HBM traffic per launch (bytes) of the FP32 sgemm kernels (sgemm_f32_dma, sgemm_mfma_f32),",
+    lines = ["# HBM traffic per launch (bytes) of the FP32 sgemm kernels (sgemm_f32_dma, sgemm_f32_any),",
              "# every FP32 menu tile on the FP32 workload, from rocprofv3 counters",
              "# counter runs (GPU, repository root), once with FETCH_SIZE and once with WRITE_SIZE:",
              "#   rocprofv3 --pmc <COUNTER> --output-format csv -d <dir> -o pmc -- python3 bench.py --traffic-sweep",
