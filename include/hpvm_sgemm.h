@@ -234,11 +234,11 @@ int hpvm_sgemm(int64_t m, int64_t n, int64_t k, float alpha, const float* A,
  * menu order on a tie) when the workspace holds the partial sums; other
  * FP32 products, and BF16 and bf16x3 ones of less than 2^31 multiply-adds
  * (m n k), the tile with the least estimated time, splits included; larger
- * BF16 products take the first staged tile, or, when that would give fewer
- * than 256 tiles, 128 x 128 x 64 with 64 x 32 leaves or a 128 x 256 tile of
- * FP32 operands, whichever is estimated faster (bf16x3 only when the
- * DMA-fed 256 x 256 tile would not cover the CUs or does not suit k and n),
- * and others hpvm_sgemm's choice.  Every other argument and rule is
+ * ones, where estimated faster: the first staged tile (bf16x3 with k a
+ * multiple of 16 and n of 4: hpvm_sgemm's DMA-fed 256 x 256 tile) if it
+ * gives 256 tiles and k >= 256, or the staged 128 x 128 x 64 one with 64 x 32
+ * leaves, or, of those with k < 1024, any tile on the FP32 operands, of
+ * deeper ones the 128 x 256 one.  Every other argument and rule is
  * hpvm_sgemm's.                                                            */
 int hpvm_sgemm_ws(int64_t m, int64_t n, int64_t k, float alpha, const float* A, int64_t lda,
                   const float* B, int64_t ldb, float beta, float* C, int64_t ldc, int32_t prec,
@@ -364,7 +364,8 @@ int hpvm_tile_menu(int32_t prec, hpvm_tile* out, int32_t capacity,
  * in the fragment reads, with no conversion pass.  Passes that are not
  * whole, 16-byte aligned tiles take another entry (FP32: per pass; BF16:
  * the whole call takes the staged 128 x 128 x 64 entry).  The built-in
- * choice takes the DMA entry for FP32 only.
+ * choice takes the DMA entry for FP32 only.  The other fused entries run
+ * both products and the element-wise pass in one launch for any size.
  * The two scalars are reduced
  * in FP32 with fixed-order tree sums, so repeated calls give identical bits.
  * Any of dA, dB, dC_in, dalpha, dbeta may be NULL to skip that output.

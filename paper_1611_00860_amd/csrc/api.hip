@@ -176,11 +176,17 @@ struct TileTime {
   hpvm_tile tile;
   double start, alone, shared, more;
   bool aligned;  // only where its own loop runs (mfma_f32_dma.hpp, mfma_bf16_dma.hpp)
+  bool wide = false;  // too many registers or LDS to run beside an open streaming graph
 };
 static double tile_time(const TileTime& c, double tiles, double k) {
   const double rounds = std::ceil(tiles / 256.0);
   return c.start + std::max(c.alone, rounds * c.shared) * k / 32.0 + (rounds - 1.0) * c.more;
 }
+
+// Where tiles that cannot run beside an open streaming graph may be taken:
+// from a tile of this size per CU on, or of their own if that needs alignment.
+// Smaller products are those a program runs while it streams.
+constexpr hpvm_tile kWideFrom{128, 128, 32, 64, 64, 4};
 
 // The candidate with the least time, a contraction split that fits split_ws
 // (< 0: any) included: the partial sums' traffic at 4 TB/s and the summing
@@ -193,8 +199,7 @@ static bool least_time(const TileTime* c, int count, int32_t prec, int64_t m, in
     const hpvm_tile& t = c->tile;
     if (c->aligned && (m < t.tile_m || n < t.tile_n || n % 4 || k % t.tile_k)) continue;
     if (large_only && t.tile_m * t.tile_n < 128 * 256) continue;
-    // Alone too large to run beside an open streaming graph (128 KB of LDS).
-    if (c->aligned && (t.tile_m == 256 || prec != HPVM_PREC_FP32) && tiles_of(t, m, n) < 256) continue;
+    if (c->wide && tiles_of(c->aligned ? t : kWideFrom, m, n) < 256) continue;
     const MfmaEntry* e = find_menu_entry(prec, t);
     if (!e) continue;
     int64_t slices = 1;
@@ -246,7 +251,7 @@ static bool f32_groups_beat_split(const hpvm_tile& t, int64_t m, int64_t n, int6
 //   4096^3: 256 x 256 932
 bool f32_default_tile(int64_t m, int64_t n, int64_t k, int64_t split_ws, hpvm_tile* out) {
   static const TileTime kCandidates[] = {
-      {{256, 256, 32, 64, 128, 2}, 13.0, 6.31, 6.89, 32.0, true},
+      {{256, 256, 32, 64, 128, 2}, 13.0, 6.31, 6.89, 32.0, true, true},
       kF32Mid,
       {{64, 128, 32, 32, 64, 2}, 6.2, 1.09, 0.948, 2.3, false},
       {{64, 128, 16, 32, 64, 2}, 5.7, 1.18, 0.983, 2.3, false},
@@ -265,26 +270,24 @@ bool f32_default_tile(int64_t m, int64_t n, int64_t k, int64_t split_ws, hpvm_ti
 //   2048 x 2048 x 256: 64 x 128 11.8, 64 x 64 14.1; bf16x3 16.6, 18.5
 //   3000 x 3000 x 256: 256 x 256 24.0, 64 x 128 25.3; bf16x3 64 x 128 34.7
 //   100 x 3000 x 1500: 32 x 128, split 15.7, 64 x 64 18.0
-// Tiles that need most of a CU's LDS or registers cannot run beside an open
-// streaming graph: the aligned ones are taken only when they give a tile per
-// CU, the others when the smaller ones need more rounds.
+// bf16x3's 64 x 128 tile has 196 registers, and an open stream leaves 176.
 static bool bf16_default_tile(int32_t prec, int64_t m, int64_t n, int64_t k, int64_t split_ws, hpvm_tile* out,
                               double* estimate = nullptr, bool large_only = false) {
   const MfmaEntry* e0 = menu_entry_at(prec, 0);
   if (!e0) return false;
   const TileTime kBf16[] = {
-      {e0->tile, 28.0, 0.72, 1.15, 28.0, true},
-      {{128, 256, 32, 64, 64, 2}, 13.0, 0.9, 0.9, 20.0, false},
-      {{128, 128, 32, 64, 64, 4}, 10.7, 0.44, 0.44, 11.0, true},
+      {e0->tile, 28.0, 0.72, 1.15, 28.0, true, true},
+      {{128, 256, 32, 64, 64, 2}, 13.0, 0.9, 0.9, 20.0, false, true},
+      {{128, 128, 32, 64, 64, 4}, 10.7, 0.44, 0.44, 11.0, true, true},
       {{64, 128, 32, 32, 64, 2}, 6.0, 0.366, 0.265, 3.0, false},
       {{64, 64, 32, 32, 32, 2}, 4.5, 0.299, 0.182, 1.6, false},
       {{32, 128, 32, 32, 32, 2}, 4.6, 0.327, 0.219, 1.85, false},
   };
   const TileTime kX3[] = {
-      {e0->tile, 28.0, 2.4, 2.2, 48.0, true},
-      {{128, 256, 32, 64, 64, 2}, 14.0, 1.75, 1.75, 20.0, false},
-      {{128, 128, 32, 64, 64, 4}, 11.0, 0.85, 0.85, 9.6, true},
-      {{64, 128, 32, 32, 64, 2}, 6.4, 0.664, 0.498, 2.9, false},
+      {e0->tile, 28.0, 2.4, 2.2, 48.0, true, true},
+      {{128, 256, 32, 64, 64, 2}, 14.0, 1.75, 1.75, 20.0, false, true},
+      {{128, 128, 32, 64, 64, 4}, 11.0, 0.85, 0.85, 9.6, true, true},
+      {{64, 128, 32, 32, 64, 2}, 6.4, 0.664, 0.498, 2.9, false, true},
       {{64, 64, 32, 32, 32, 2}, 4.9, 0.471, 0.316, 1.55, false},
       {{32, 128, 32, 32, 32, 2}, 4.9, 0.509, 0.35, 1.85, false},
   };

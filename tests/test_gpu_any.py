@@ -135,3 +135,25 @@ def test_grouped_narrow_instances_replayed(gpu):
         torch.cuda.synchronize()
         for c, ref, size in zip(Cs, refs, sizes):
             assert np.array_equal(to_host(c), ref), size
+
+
+@pytest.mark.parametrize("prec", ["fp32", "bf16", "bf16x3"])
+def test_small_products_run_beside_an_open_stream(gpu, prec):
+    """An open streaming graph holds part of every CU until it idles out: the
+    default tiles of products that give fewer than 256 tiles of 128 x 128 fit
+    in the rest."""
+    import time
+
+    import torch
+
+    with gpu.SgemmStream(capacity=4, idle_ms=10000):
+        t0 = time.time()
+        for m, n, k in [(128, 128, 128), (200, 7000, 512), (1500, 1100, 300), (300, 300, 2048)]:
+            print(f"case: beside a stream {prec} {m}x{n}x{k}", flush=True)
+            A, B, C, G = (to_dev(x) for x in inputs.backward_operands(m, n, k, seed=3))
+            gpu.sgemm(A, B, C, 1.0, 0.5, prec=prec)
+            torch.cuda.current_stream().synchronize()
+            if m * n * k < 2 ** 28:
+                gpu.sgemm_backward(A, B, C, G, 1.0, 0.5, prec=prec)
+                torch.cuda.current_stream().synchronize()
+        assert time.time() - t0 < 8
