@@ -13,6 +13,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <iterator>
 #include <mutex>
 
 #include "device_common.hpp"
@@ -223,13 +224,14 @@ constexpr TileTime kF32Groups[] = {
     {{32, 32, 128, 8, 32, 2}, 5.4, 0.141, 0.129, 2.0, false},
 };
 
-// Whether a tile whose waves share k in groups (as short sums as two or four
-// slices give) is estimated faster than the whole-tile split `t` with `bytes`
-// of partial sums.  Not asked where that has four slices or more in a single
-// round, which it fills evenly.  1536^3, two slices in two rounds: 100 us
-// against 76 in 32 x 32 tiles; 2048 x 1024 x 512, two in one: 30 against 25.
+// Whether a tile whose waves share k in at least as many groups as the
+// whole-tile split `t` has slices (so that no sum is longer) is estimated
+// faster than that split, with `bytes` of partial sums.  Not asked where that
+// has four slices or more in a single round, which it fills evenly.  1536^3,
+// two slices in two rounds: 100 us against 76 in 32 x 32 tiles;
+// 2048 x 1024 x 512, two in one: 30 against 25 in 64 x 64.
 static bool f32_groups_beat_split(const hpvm_tile& t, int64_t m, int64_t n, int64_t k, int64_t bytes,
-                                  int64_t split_ws, hpvm_tile* out) {
+                                  hpvm_tile* out) {
   const int64_t slices = bytes / (m * n * (int64_t)sizeof(float)), tiles = tiles_of(t, m, n) * slices;
   if (slices >= 4 && tiles <= 256) return false;
   const double area = (double)t.tile_m * t.tile_n / (128.0 * 128.0);
@@ -237,8 +239,10 @@ static bool f32_groups_beat_split(const hpvm_tile& t, int64_t m, int64_t n, int6
   c.alone *= area;
   c.shared *= area;
   const double split = tile_time(c, (double)tiles, (double)k / slices) + 4.5 + (double)(bytes + m * n * 4) / 4.0e6;
+  const TileTime* from = kF32Groups + (slices > 2 ? 1 : 0);  // two groups, four
   double groups = 0.0;
-  return least_time(kF32Groups, 2, HPVM_PREC_FP32, m, n, k, split_ws, false, out, &groups) && groups < split;
+  return slices <= 4 && least_time(from, (int)(std::end(kF32Groups) - from), HPVM_PREC_FP32, m, n, k, 0, false, out, &groups) &&
+         groups < split;
 }
 
 // FP32.  Fitted to each tile's time over 72 products from 64 x 64 x 1000 to
@@ -338,7 +342,7 @@ const hpvm::MfmaEntry* fewest_slices(int32_t prec, int64_t m, int64_t n, int64_t
 //    estimated time, the staged 128 x 128 one included, where k < 1024
 //    (2500 x 2500 x 400 bf16x3: 36 us against 51 staged); for deeper ones
 //    the staged, unless 128 x 256 tiles on the FP32 operands are estimated
-//    faster.
+//    faster, then hpvm_sgemm's choice.
 // Returns false for hpvm_sgemm's choice.
 bool default_ws_tile(int32_t prec, int64_t m, int64_t n, int64_t k, int64_t ws_bytes, hpvm_tile* out) {
   const bool f32 = prec == HPVM_PREC_FP32, x3 = prec == HPVM_PREC_BF16X3;
@@ -348,7 +352,6 @@ bool default_ws_tile(int32_t prec, int64_t m, int64_t n, int64_t k, int64_t ws_b
     int64_t need = 0;
     const hpvm::MfmaEntry* best = fewest_slices(prec, m, n, k, &need);
     if (best && ws_bytes >= 0 && ws_bytes < need) return false;
-    if (best && f32 && hpvm::f32_groups_beat_split(best->tile, m, n, k, need, ws_bytes, out)) return true;
     if (best) {
       *out = best->tile;
       return true;
@@ -377,7 +380,7 @@ bool default_ws_tile(int32_t prec, int64_t m, int64_t n, int64_t k, int64_t ws_b
   if (ws_bytes >= 0 && ws_bytes < hpvm::staged_workspace_bytes(prec, m, n, k)) return false;
   if (!big) {
     double direct = 0.0;
-    if (hpvm::bf16_default_tile(prec, m, n, k, 0, out, &direct, k >= 1024) && direct < time_small) return true;
+    if (hpvm::bf16_default_tile(prec, m, n, k, 0, out, &direct, k >= 1024) && direct < time_small) return false;
   }
   *out = big ? staged[0].tile : small->tile;
   return true;
@@ -400,6 +403,12 @@ bool choose_tile(int32_t prec, int64_t m, int64_t n, int64_t k, bool ws_ok, int6
     const int64_t need = std::max(hpvm::entry_split_bytes(e, m, n, k), hpvm::entry_workspace_bytes(e, m, n, k));
     if (need == 0 || ws_bytes >= need) return true;
     return hpvm::tuned_tile(prec, m, n, k, false, out) != 0;
+  }
+  const hpvm::MfmaEntry* mid = prec == HPVM_PREC_FP32 ? f32_mid_entry() : nullptr;
+  if (mid && tiles_of(mid->tile, m, n) < 256) {  // with a workspace or without: the same tile
+    int64_t need = 0;
+    const hpvm::MfmaEntry* best = fewest_slices(prec, m, n, k, &need);
+    if (best && hpvm::f32_groups_beat_split(best->tile, m, n, k, need, out)) return true;
   }
   if (ws_ok && default_ws_tile(prec, m, n, k, ws_bytes, out)) return true;
   return prec == HPVM_PREC_FP32 ? hpvm::f32_default_tile(m, n, k, 0, out)

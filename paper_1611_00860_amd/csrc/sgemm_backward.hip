@@ -562,22 +562,28 @@ int64_t split_sum_blocks(int64_t rows, int64_t cols) {
 // `more` for each of those after the first.  The DMA entry (whole 256 x 256
 // tiles) adds the launch of its slice sums, about 6 us, and their traffic.
 // dalpha = <A, G B^T> cancels, so how the products are rounded shows in it:
-// the DMA entry's shorter sums are given up, and the k groups of the 32 x 32
-// tile taken for the others' plain order in k, only where that saves 30%
+// the DMA entry's shorter sums are given up only for tiles that share k among
+// as many groups as it has slices, so that no sum is longer, and only where
+// that saves 30%; elsewhere the k groups of the 32 x 32 tile replace the
+// others' plain order in k only where that saves as much
 // (`worth`).  Measured, us, this choice and the next: 1000 x 1200 x 800
 // 64 x 64 49, 64 x 128 58; 2048^3 64 x 128 264, 256 x 256 273;
-// 64 x 4096 x 1000 32 x 32 39, 64 x 64 99.
+// 64 x 4096 x 1000 32 x 32 39, 64 x 64 99; 1024^3 32 x 32 60,
+// 256 x 256 in four slices 82.
 const BwdEntry* f32_pick(int64_t m, int64_t n, int64_t k) {
   struct Candidate {
     hpvm_tile tile;
     double start, alone, shared, more, worth;
+    int groups;  // of k; the DMA entry: its slices
   };
   static const Candidate kCandidates[] = {
-      {{kDmaTile, kDmaTile, kDmaK, kDmaWM, kDmaWN, kDmaStages}, 16.0, 6.31, 6.89, 32.0, 0.7},
-      {{64, 128, 32, 32, 64, 2}, 9.2, 1.2, 1.0, 2.3, 1.0},
-      {{64, 64, 16, 32, 32, 2}, 7.5, 0.712, 0.541, 1.43, 1.0},
-      {{32, 32, 128, 8, 32, 2}, 8.4, 0.141, 0.129, 2.0, 1.0 / 0.7},
+      {{kDmaTile, kDmaTile, kDmaK, kDmaWM, kDmaWN, kDmaStages}, 16.0, 6.31, 6.89, 32.0, 0.7, 0},
+      {{64, 128, 32, 32, 64, 2}, 9.2, 1.2, 1.0, 2.3, 1.0, 1},
+      {{64, 64, 16, 32, 32, 2}, 7.5, 0.712, 0.541, 1.43, 1.0, 1},
+      {{64, 64, 32, 16, 32, 2}, 8.7, 0.597, 0.498, 2.3, 1.0 / 0.7, 2},
+      {{32, 32, 128, 8, 32, 2}, 8.4, 0.141, 0.129, 2.0, 1.0 / 0.7, 4},
   };
+  const int pair = pair_splits(m, n, k), cut = pair ? pair : dma_splits(m, k, n);
   const BwdEntry* pick = nullptr;
   double best = 0.0;
   for (const Candidate& c : kCandidates) {
@@ -586,14 +592,17 @@ const BwdEntry* f32_pick(int64_t m, int64_t n, int64_t k) {
     const double ta = (double)tiles_for(c.tile, m, k), tb = (double)tiles_for(c.tile, k, n);
     double slices = 1.0, extra = 0.0;
     if (e->dma) {
-      slices = pair_splits(m, n, k);
-      if (slices == 0.0) continue;
+      if (!cut) continue;
+      slices = cut;
       extra = 6.0 + (2.0 * slices + 1.0) * ((double)m * k + (double)k * n) * 4.0 / 4.0e6;
+    } else if (c.groups < cut) {
+      continue;
     }
+    const double worth = !e->dma && cut > 1 ? 1.0 : c.worth;
     const double deep = (double)std::max(m, n) / 32.0 / slices;
     const double mean = (ta * n + tb * m) / std::max(ta + tb, 1.0) / 32.0 / slices;
     const double rounds = (double)(((int64_t)((ta + tb) * slices) + 255) / 256);
-    const double time = c.worth * (c.start + std::max(rounds * mean * c.shared, deep * c.alone) +
+    const double time = worth * (c.start + std::max(rounds * mean * c.shared, deep * c.alone) +
                                    (rounds - 1.0) * c.more + extra);
     if (!pick || time < best) {
       best = time;

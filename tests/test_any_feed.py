@@ -85,7 +85,9 @@ def test_stages_hold_the_matrix_and_no_access_leaves_it(kc, R, TK, KW):
 
 
 @pytest.mark.parametrize("m,n,k", [(1, 4, 1), (128, 128, 128), (16, 4096, 4096), (33, 35, 2051), (1000, 1003, 777),
-                                   (512, 4096, 1024), (3001, 2999, 1001), (64, 64, 2047), (5, 3, 4096)])
+                                   (512, 4096, 1024), (3001, 2999, 1001), (64, 64, 2047), (5, 3, 4096),
+                                   (1536, 1536, 1536), (2048, 1024, 512), (1280, 1280, 1280), (1024, 1024, 1024),
+                                   (1024, 1536, 2048), (640, 640, 4096), (2048, 1024, 8192)])
 def test_fp32_choice_agrees_with_its_workspace(m, n, k):
     """With no tile: the workspace asked for is what the described slices fill, a
     shorter one gives a choice that fits it, and none gives hpvm_sgemm's."""
