@@ -436,12 +436,12 @@ static const FusedEntry kConsumerMenu[] = {
     HPVM_CONSUMER_ENTRY(64, 64, 16, 32, 32, 16, 6, 1),
     HPVM_CONSUMER_ENTRY(128, 64, 16, 64, 32, 16, 4, 1),
     HPVM_CONSUMER_ENTRY(64, 128, 16, 32, 64, 16, 4, 1),
-    HPVM_CONSUMER_DMA_ENTRY(256, 256, 16, 64, 4),
-    HPVM_CONSUMER_DMA_ENTRY(128, 256, 32, 32, 2),
-    HPVM_CONSUMER_DMA_ENTRY(128, 128, 32, 32, 2),
     HPVM_CONSUMER_ENTRY(64, 128, 32, 32, 64, 32, 2, 1),
     HPVM_CONSUMER_ENTRY(64, 64, 32, 32, 32, 16, 3, 2),
     HPVM_CONSUMER_ENTRY(32, 32, 128, 32, 32, 32, 2, 4),
+    HPVM_CONSUMER_DMA_ENTRY(256, 256, 16, 64, 4),
+    HPVM_CONSUMER_DMA_ENTRY(128, 256, 32, 32, 2),
+    HPVM_CONSUMER_DMA_ENTRY(128, 128, 32, 32, 2),
 };
 // Pair tiles: tile_m x tile_n of each output; 8, 8, 4 and 8 waves.  The
 // first DMA-fed entry's two stages of one A slab and two B slabs take all

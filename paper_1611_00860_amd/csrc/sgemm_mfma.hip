@@ -329,7 +329,10 @@ struct F32DmaConfig {
 // Entry 0 is the default for large problems.  The stages of the entries on
 // the loop for any size: 24 to 64 KB of slabs, alike in time however they
 // are cut (64 x 64 tiles at 1000 x 1003 x 777: two 32-deep slabs 21.9 us,
-// four 16-deep 22.4, six 22.4; in two k groups 20.9 and 19.7).
+// four 16-deep 22.4, six 22.4; in two k groups 20.9 and 19.7).  The autotuner
+// times in this order, twice: the large tiles end it, so that a slow tile's
+// rest does not come before entry 0 (with the 32 x 32 tile last, 3 of 6 tunings
+// of 4096^3 and 8192 x 4096 x 2048 took a 128-wide tile, 2% slower).
 static const MfmaEntry kF32Menu[] = {
     HPVM_F32_DMA_ENTRY(256, 256, 32, 64, 2),
     HPVM_F32_ENTRY(128, 128, 16, 64, 64, 16, 4, 1),
@@ -338,12 +341,12 @@ static const MfmaEntry kF32Menu[] = {
     HPVM_F32_ENTRY(64, 64, 16, 32, 32, 16, 6, 1),
     HPVM_F32_ENTRY(128, 64, 16, 64, 32, 16, 4, 1),
     HPVM_F32_ENTRY(64, 128, 16, 32, 64, 16, 4, 1),
-    HPVM_F32_DMA_ENTRY(256, 256, 16, 64, 4),
-    HPVM_F32_DMA_ENTRY(128, 256, 32, 32, 2),
-    HPVM_F32_DMA_ENTRY(128, 128, 32, 32, 2),
     HPVM_F32_ENTRY(64, 128, 32, 32, 64, 32, 2, 1),
     HPVM_F32_ENTRY(64, 64, 32, 32, 32, 16, 3, 2),
     HPVM_F32_SPLIT_ENTRY(32, 32, 128, 32, 32, 32, 2, 4),
+    HPVM_F32_DMA_ENTRY(256, 256, 16, 64, 4),
+    HPVM_F32_DMA_ENTRY(128, 256, 32, 32, 2),
+    HPVM_F32_DMA_ENTRY(128, 128, 32, 32, 2),
 };
 
 // BF16 and bf16x3 entries on the loop for any size.
