@@ -372,6 +372,14 @@ int hpvm_tile_menu(int32_t prec, hpvm_tile* out, int32_t capacity,
  * dalpha and dbeta are single device floats.  A, B, C_in and G are device
  * matrices with the row-major layouts of hpvm_sgemm (G and dC_in like C,
  * dA like A, dB like B); C_in is only read when dbeta is requested.
+ * Outputs may lie over inputs where the passes can be ordered so that none
+ * overwrites what itself or a later one reads: dC_in on G or C_in and one of
+ * dA on A and dB on B (same pointer and leading dimension), dC_in over A or
+ * B.  Such a call makes a launch per pass.  Where no order serves (dA on A
+ * and dB on B at once), the tiles whose products read copies of the inputs
+ * (stages == 3, and the first FP32 entry on whole tiles) still give the
+ * gradients; the others do not.  With tile == NULL such a call takes one of
+ * those tiles if its products have tiles enough to fill the device.
  * tile: an entry of hpvm_sgemm_backward_menu(prec), or NULL for the
  * hpvm_autotune_backward choice for these sizes (else a built-in rule).
  * `workspace` (device, 16-byte aligned, >= hpvm_sgemm_backward_workspace_bytes

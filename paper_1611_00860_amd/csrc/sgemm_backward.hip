@@ -5,9 +5,10 @@
 // read once more, tile by tile, where dA is written).  dB = alpha A^T G runs
 // the main loop with A read in transposed form.  One element-wise pass
 // writes dC_in = beta G and the partial sums of dbeta = <G, C_in>; a single
-// workgroup then reduces the partials.  In FP32 the tiles of both products
-// and the element-wise pass are one launch (sgemm_grad_any).  Every
-// reduction is FP32 with a fixed order, so results repeat bit for bit.
+// workgroup then reduces the partials.  The tiles of both products and the
+// element-wise pass are one launch (sgemm_grad_any) unless an output lies
+// over an input of another of the three (bwd_order).  Every reduction is
+// FP32 with a fixed order, so results repeat bit for bit.
 //
 // FP32 whole-tile problems can instead run both GEMMs on the DMA-fed loop
 // (mfma_f32_dma.hpp) with the contraction split into slices: dA and dB have
@@ -45,7 +46,7 @@ namespace hpvm {
 // p: A = G (m x n_g), B = B (read transposed), m = m, n = k, k = n.
 template <int TM, int TN, int TK, int WM, int WN, int PREC>
 __global__ void __launch_bounds__((TM / WM) * (TN / WN) * kWave)
-    sgemm_grad_a(GemmArgs p, const float* __restrict__ Aorig, int64_t lda, float* __restrict__ partial) {
+    sgemm_grad_a(GemmArgs p, const float* Aorig, int64_t lda, float* __restrict__ partial) {
   extern __shared__ __align__(16) char smem[];
   int tm, tn;
   tile_coords(p.tiles_m, p.tiles_n, blockIdx.x, tm, tn);
@@ -151,9 +152,10 @@ __device__ __forceinline__ void grad_c_block(const GradCJob& jb, int64_t block, 
     }
     for (; q < n4; q += blockDim.x) {
       const f32x4 gv = reinterpret_cast<const f32x4*>(g)[q];
+      f32x4 cv;  // read before d is written, which may be c
+      if (c) cv = reinterpret_cast<const f32x4*>(c)[q];
       if (d) reinterpret_cast<f32x4*>(d)[q] = (beta == 0.0f) ? f32x4{0.0f, 0.0f, 0.0f, 0.0f} : beta * gv;
       if (c) {
-        const f32x4 cv = reinterpret_cast<const f32x4*>(c)[q];
         part = fmaf(gv[0], cv[0], part);
         part = fmaf(gv[1], cv[1], part);
         part = fmaf(gv[2], cv[2], part);
@@ -162,8 +164,8 @@ __device__ __forceinline__ void grad_c_block(const GradCJob& jb, int64_t block, 
     }
     for (int64_t j = 4 * n4 + threadIdx.x; j < n; j += blockDim.x) {
       const float gv = g[j];
-      if (d) d[j] = (beta == 0.0f) ? 0.0f : beta * gv;
       if (c) part = fmaf(gv, c[j], part);
+      if (d) d[j] = (beta == 0.0f) ? 0.0f : beta * gv;
     }
   }
   if (!partial) return;
@@ -225,8 +227,8 @@ struct SumJob {
 
 __device__ __forceinline__ void split_sum_block(const SumJob& jb, int64_t block, float* red) {
   const float* __restrict__ part = jb.part;
-  float* __restrict__ out = jb.out;
-  const float* __restrict__ aorig = jb.aorig;
+  float* out = jb.out;
+  const float* aorig = jb.aorig;
   const int64_t cols = jb.cols, c4 = cols / 4, units = jb.rows * c4, plane = jb.rows * cols;
   const int64_t stride = jb.blocks * blockDim.x;
   float sum = 0.0f;
@@ -234,9 +236,10 @@ __device__ __forceinline__ void split_sum_block(const SumJob& jb, int64_t block,
     const int64_t i = u / c4, j = (u - i * c4) * 4;
     f32x4 v = *reinterpret_cast<const f32x4*>(part + i * cols + j);
     for (int z = 1; z < jb.splits; ++z) v += *reinterpret_cast<const f32x4*>(part + z * plane + i * cols + j);
+    f32x4 a;  // read first: out may be aorig
+    if (jb.dpart) a = *reinterpret_cast<const f32x4*>(aorig + i * jb.ldao + j);
     if (out) *reinterpret_cast<f32x4*>(out + i * jb.ldo + j) = jb.alpha * v;
     if (jb.dpart) {
-      const f32x4 a = *reinterpret_cast<const f32x4*>(aorig + i * jb.ldao + j);
       sum = fmaf(a[0], v[0], sum);
       sum = fmaf(a[1], v[1], sum);
       sum = fmaf(a[2], v[2], sum);
@@ -272,7 +275,7 @@ __global__ void __launch_bounds__(kElemThreads) sgemm_grad_tail(SumJob a, SumJob
 // this lane's share of <aorig, acc> over the row quads [q0, q1).  Each block
 // loads its elements of A before its stores.
 template <typename OA, typename OB, int NA, int NB>
-__device__ __forceinline__ float any_grad_a_epilogue(const GemmArgs& q, const float* __restrict__ aorig, int64_t ldao,
+__device__ __forceinline__ float any_grad_a_epilogue(const GemmArgs& q, const float* aorig, int64_t ldao,
                                                      const f32x16 (&acc)[NA][NB], int m0, int n0, int wm0, int wn0,
                                                      int lane, int q0, int q1) {
   float part = 0.0f;
@@ -321,7 +324,7 @@ constexpr int kAnyMinWaves =
 template <int PREC, int TM, int TN, int TK, int WM, int WN, int NST, int KW>
 __global__ void __launch_bounds__((AnyShape<TM, TN, TK, WM, WN, false, true, NST, KW>::kThreads)) __attribute__((
     amdgpu_waves_per_eu((kAnyMinWaves<PREC, AnyShape<TM, TN, TK, WM, WN, false, true, NST, KW>>))))
-    sgemm_grad_any(GemmArgs a, const float* __restrict__ aorig, int64_t ldao, float* __restrict__ partial, GemmArgs b,
+    sgemm_grad_any(GemmArgs a, const float* aorig, int64_t ldao, float* __restrict__ partial, GemmArgs b,
                    GradCJob c, int32_t tiles_a, int32_t tiles_b) {
   extern __shared__ __align__(16) char smem[];
   using SA = AnyShape<TM, TN, TK, WM, WN, false, true, NST, KW>;
@@ -628,10 +631,8 @@ int64_t launch_tiles(const BwdEntry& e, int64_t m, int64_t n, int64_t k) {
   return tiles;
 }
 
-const BwdEntry* bf16_pick(int32_t prec, int64_t m, int64_t n, int64_t k) {
-  const bool x3 = prec == HPVM_PREC_BF16X3;
-  const BwdEntry* fused = find_bwd(prec, odd_tile(prec));
-  if (!staged_k_ok(n) || !staged_k_ok(m)) return fused;  // the dA and dB contractions
+const BwdEntry* staged_pick(int32_t prec, int64_t m, int64_t n, int64_t k) {
+  if (!staged_k_ok(n) || !staged_k_ok(m)) return nullptr;  // the dA and dB contractions
   const BwdEntry* staged = nullptr;
   for (int i = 0; i < kNumBwd; ++i) {
     // The BF16 DMA entry reads FP32 slabs where the staged products read
@@ -645,6 +646,13 @@ const BwdEntry* bf16_pick(int32_t prec, int64_t m, int64_t n, int64_t k) {
       break;
     }
   }
+  return staged;
+}
+
+const BwdEntry* bf16_pick(int32_t prec, int64_t m, int64_t n, int64_t k) {
+  const bool x3 = prec == HPVM_PREC_BF16X3;
+  const BwdEntry* fused = find_bwd(prec, odd_tile(prec));
+  const BwdEntry* staged = staged_pick(prec, m, n, k);
   if (!staged || !fused) return staged ? staged : fused;
   // Slabs of the most tiles one of 256 CUs gets, and of one of the deeper.
   const double deep = (double)std::max(m, n) / 32.0;
@@ -667,6 +675,64 @@ const BwdEntry* pick(int32_t prec, int64_t m, int64_t n, int64_t k) {
     if (e) return e;
   }
   return prec == HPVM_PREC_FP32 ? f32_pick(m, n, k) : bf16_pick(prec, m, n, k);
+}
+
+// The entry that has read every input when it writes the first gradient
+// (through slice sums or bfloat16 planes), for a call without a tile whose
+// outputs lie over its inputs as no order of the fused launches allows.
+// Null where its tiles are neither one per CU nor more than dA's in 64 x 64
+// (FP32: not whole).
+const BwdEntry* inputs_first_pick(int32_t prec, int64_t m, int64_t n, int64_t k) {
+  if (prec == HPVM_PREC_FP32) return dma_splits(m, k, n) ? &kBwd[0] : nullptr;
+  const BwdEntry* e = staged_pick(prec, m, n, k);
+  if (!e) return nullptr;
+  const int64_t tiles = launch_tiles(*e, m, n, k);
+  return tiles >= kTargetTiles || tiles > tiles_for(odd_tile(prec), m, k) ? e : nullptr;
+}
+
+// A matrix of a call; p null: absent.
+struct Mat {
+  const float* p;
+  int64_t rows, cols, ld;
+};
+bool meet(const Mat& x, const Mat& y) {
+  if (!x.p || !y.p || x.rows <= 0 || x.cols <= 0 || y.rows <= 0 || y.cols <= 0) return false;
+  uintptr_t x0, x1, y0, y1;
+  matrix_extent(x.p, x.rows, x.cols, x.ld, &x0, &x1);
+  matrix_extent(y.p, y.rows, y.cols, y.ld, &y0, &y1);
+  return x0 < y1 && y0 < x1;
+}
+// One of a call's jobs (dA and dalpha; dB; dC_in and dbeta): what it writes,
+// and what it reads as a whole or only where it writes (each element by the
+// lane that then writes that one).
+struct BwdJob {
+  Mat out, whole[2], each[2];
+};
+
+// An order of the jobs in which none overwrites what itself or a later one
+// reads.
+struct BwdOrder {
+  int job[3] = {0, 1, 2};
+  bool apart = true;  // none overwrites what another reads: all may run at once
+  bool found = true;  // false: there is no such order (job is 0, 1, 2)
+};
+BwdOrder bwd_order(const BwdJob (&jobs)[3]) {
+  bool hits[3][3] = {};  // [x][y]: x overwrites what y reads
+  BwdOrder o;
+  for (int x = 0; x < 3; ++x)
+    for (int y = 0; y < 3; ++y) {
+      const Mat& w = jobs[x].out;
+      for (const Mat& r : jobs[y].whole) hits[x][y] = hits[x][y] || meet(w, r);
+      for (const Mat& r : jobs[y].each)
+        hits[x][y] = hits[x][y] || (meet(w, r) && !(x == y && w.p == r.p && w.ld == r.ld));
+      if (x != y && hits[x][y]) o.apart = false;
+    }
+  do {
+    const int a = o.job[0], b = o.job[1], c = o.job[2];
+    if (!(hits[a][a] || hits[b][b] || hits[c][c] || hits[a][b] || hits[a][c] || hits[b][c])) return o;
+  } while (std::next_permutation(o.job, o.job + 3));
+  o.found = false;
+  return o;  // the last step left job at 0, 1, 2
 }
 
 int64_t elem_blocks(int64_t m, int64_t n) {
@@ -741,6 +807,12 @@ BwdLayout bwd_layout(const BwdEntry* e, int64_t m, int64_t n, int64_t k) {
   // the same workspace.
   if (e->dma && e->prec != HPVM_PREC_FP32) L.total = std::max(L.total, bwd_layout(&kBwd[e->fallback], m, n, k).total);
   return L;
+}
+
+// Workspace of a call on entry e: without a tile, of inputs_first_pick too.
+int64_t call_bytes(const BwdEntry* e, const hpvm_tile* tile, int32_t prec, int64_t m, int64_t n, int64_t k) {
+  const BwdEntry* other = !tile && e->any ? inputs_first_pick(prec, m, n, k) : nullptr;
+  return std::max(bwd_layout(e, m, n, k).total, other ? bwd_layout(other, m, n, k).total : 0);
 }
 
 // One gradient on the DMA-fed loop: `splits` contraction slices write their
@@ -926,7 +998,7 @@ int hpvm_sgemm_backward_workspace_bytes(int64_t m, int64_t n, int64_t k, int32_t
   int rc = resolve_bwd(prec, tile, m, n, k, &e, 5);
   if (rc != HPVM_OK) return rc;
   if (!bytes) return set_error(HPVM_INVALID_ARG, "argument 6: bytes is NULL");
-  *bytes = bwd_layout(e, m, n, k).total;
+  *bytes = call_bytes(e, tile, prec, m, n, k);
   return clear_error();
 }
 
@@ -958,10 +1030,22 @@ int hpvm_sgemm_backward(int64_t m, int64_t n, int64_t k, float alpha, float beta
   const BwdEntry* cfg;
   int rc = resolve_bwd(prec, tile, m, n, k, &cfg, 23);
   if (rc != HPVM_OK) return rc;
+  // Outputs may lie over inputs that nothing after them reads.
+  const Mat in_a{A, m, k, lda}, in_b{B, k, n, ldb}, in_g{G, m, n, ldg}, none{};
+  const bool grad_c = mn && (dC_in || dbeta);  // the element-wise pass over G (and C_in)
+  const BwdJob jobs[3] = {
+      {{want_a ? dA : nullptr, m, k, ldda}, {run_a ? in_g : none, run_a ? in_b : none}, {run_a && dalpha ? in_a : none, none}},
+      {{dB, k, n, lddb}, {run_b ? in_a : none, run_b ? in_g : none}, {none, none}},
+      {{dC_in, m, n, lddci}, {none, none}, {grad_c ? in_g : none, dbeta ? Mat{C_in, m, n, ldci} : none}}};
+  const BwdOrder order = bwd_order(jobs);
+  const int64_t total = call_bytes(cfg, tile, prec, m, n, k);
+  if (!order.found && !tile && cfg->any && workspace && workspace_bytes >= total) {
+    const BwdEntry* other = inputs_first_pick(prec, m, n, k);
+    if (other) cfg = other;
+  }
   // The BF16 DMA entry runs a call only when every pass it makes is whole,
   // aligned tiles; otherwise the whole call takes its staged fallback (the
   // workspace it asks for covers that entry too).
-  const BwdLayout L0 = bwd_layout(cfg, m, n, k);
   if (cfg->dma && prec != HPVM_PREC_FP32) {
     const DmaPlan d = dma_plan(cfg, m, n, k);
     const bool ok_a = !run_a || (d.sa && vec16(G, ldg) && vec16(B, ldb) && (!dA || vec16(dA, ldda)) &&
@@ -970,7 +1054,7 @@ int hpvm_sgemm_backward(int64_t m, int64_t n, int64_t k, float alpha, float beta
     if (!ok_a || !ok_b) cfg = &kBwd[cfg->fallback];
   }
   BwdLayout L = bwd_layout(cfg, m, n, k);
-  L.total = L0.total;
+  L.total = total;
   const bool staged = cfg->grad_a == nullptr && !cfg->dma;
   const DmaPlan plan = dma_plan(cfg, m, n, k);
   const bool need_ws = dalpha || dbeta || (staged && (run_a || run_b)) || (cfg->dma && (run_a || run_b));
@@ -997,9 +1081,8 @@ int hpvm_sgemm_backward(int64_t m, int64_t n, int64_t k, float alpha, float beta
   hipError_t e = hipSuccess;
   int64_t na = L.na;
 
-  // dC_in and dbeta's partials: an element-wise pass over G (and C_in),
-  // launched on its own below unless a launch already carries it.
-  const bool grad_c = mn && (dC_in || dbeta);
+  // dC_in and dbeta's partials: launched on their own below unless a launch
+  // already carries them.
   GradCJob gc{G, ldg, C_in, ldci, dC_in, lddci, m, n, beta, dbeta ? pb : nullptr,
               vec16(G, ldg) && (!dC_in || vec16(dC_in, lddci)) && (!dbeta || vec16(C_in, ldci)), 0};
   if (grad_c) gc.blocks = L.nb;
@@ -1016,8 +1099,10 @@ int hpvm_sgemm_backward(int64_t m, int64_t n, int64_t k, float alpha, float beta
   // Likewise the DMA entry's slices of both gradients, when both are whole
   // tiles and aligned.
   const bool dma_pair = cfg->dma && run_a && run_b && dma_a && dma_b && plan.sp > 0;
-  GemmArgs a_pair{};
-  bool any_a = false;  // dA waits for the launch it shares with dB and grad_c (fb->any)
+  GemmArgs a_pair{}, b_any{};
+  // Products that wait for the launch they share with each other and grad_c
+  // (fb->any): where no output lies over another job's inputs.
+  bool any_a = false, any_b = false;
   if (staged && (run_a || run_b)) {
     if (!me || !me->launch_staged_planes) return hip_error(hipErrorInvalidValue, "backward staged entry");
     P = bwd_planes(prec, stage, m, n, k);
@@ -1026,14 +1111,16 @@ int hpvm_sgemm_backward(int64_t m, int64_t n, int64_t k, float alpha, float beta
     st.ldg = ldg;
     st.Cin = dbeta ? C_in : nullptr;
     st.ldci = ldci;
-    st.dCin = dC_in;
+    // dC_in over A or B waits until they are converted and dalpha has read A.
+    const bool c_waits = meet(jobs[2].out, in_a) || meet(jobs[2].out, in_b);
+    st.dCin = c_waits ? nullptr : dC_in;
     st.lddci = lddci;
     st.m = m;
     st.n = n;
     st.k = k;
     st.beta = beta;
     st.partial = dbeta ? pb : nullptr;
-    st.vec_g = vec16(G, ldg) && (!dC_in || vec16(dC_in, lddci)) && (!dbeta || vec16(C_in, ldci));
+    st.vec_g = vec16(G, ldg) && (!st.dCin || vec16(dC_in, lddci)) && (!dbeta || vec16(C_in, ldci));
     if (run_a) {
       st.gh = P.gh;
       st.gl = P.gl;
@@ -1054,14 +1141,22 @@ int hpvm_sgemm_backward(int64_t m, int64_t n, int64_t k, float alpha, float beta
     }
     e = stage_backward(prec, st, s);
     if (e != hipSuccess) return hip_error(e, "backward staging launch");
-    g_pass = gc_done = true;
+    g_pass = true;
+    gc_done = !c_waits;
+    gc.partial = nullptr;  // dbeta's are the pass over G's
   }
 
   // dA (and dalpha's partials): contraction over n.
-  if (want_a && mk && n == 0) {
-    if (dA) e = launch_scale(dA, ldda, m, k, 0.0f, s);
-    na = 0;
-  } else if (run_a) {
+  auto pass_a = [&]() {
+    if (want_a && mk && n == 0) {
+      na = 0;
+      return dA ? launch_scale(dA, ldda, m, k, 0.0f, s) : hipSuccess;
+    }
+    if (!run_a) {
+      na = 0;
+      return hipSuccess;
+    }
+    hipError_t r = hipSuccess;
     GemmArgs a{};
     a.A = G;
     a.lda = ldg;
@@ -1085,7 +1180,7 @@ int hpvm_sgemm_backward(int64_t m, int64_t n, int64_t k, float alpha, float beta
       if (dma_pair)
         a_pair = a;  // launched with dB below
       else
-        e = prec == HPVM_PREC_FP32
+        r = prec == HPVM_PREC_FP32
                 ? launch_split<HPVM_PREC_FP32, false, true>(a, plan.sa, reinterpret_cast<float*>(stage), dA, ldda,
                                                             dalpha ? A : nullptr, lda, dalpha ? pa : nullptr, s)
                 : launch_split<HPVM_PREC_BF16, false, true>(a, plan.sa, reinterpret_cast<float*>(stage), dA, ldda,
@@ -1095,39 +1190,37 @@ int hpvm_sgemm_backward(int64_t m, int64_t n, int64_t k, float alpha, float beta
       if (pair)
         a_pair = a;  // launched with dB below
       else
-        e = me->launch_staged_planes(a, StagedPlanes{P.gh, P.gl, P.bh, P.bl}, A, lda, dalpha ? pa : nullptr, s);
+        r = me->launch_staged_planes(a, StagedPlanes{P.gh, P.gl, P.bh, P.bl}, A, lda, dalpha ? pa : nullptr, s);
     } else if (fb->any && f32_any_fits(a, false, true) && lda < kAnyPitch) {
-      any_a = true;
-      a_pair = a;
       na = dalpha ? tiles_for(fb->tile, m, k) : 0;
+      a_pair = a;
+      if (order.apart) any_a = true;
+      else r = fb->any(&a, A, lda, dalpha ? pa : nullptr, nullptr, nullptr, s);
     } else if (dalpha) {
       // Fused pass: dA (when requested) and the per-tile partials of dalpha.
       if (fb->lds > 65536)
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(fb->grad_a),
+        r = hipFuncSetAttribute(reinterpret_cast<const void*>(fb->grad_a),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)fb->lds);
-      if (e == hipSuccess) {
+      if (r == hipSuccess) {
         const float* Ao = A;
         int64_t ldao = lda;
         float* part = pa;
         void* kargs[] = {&a, &Ao, &ldao, &part};
-        e = hipLaunchKernel(reinterpret_cast<const void*>(fb->grad_a), dim3((unsigned)(a.tiles_m * a.tiles_n)),
+        r = hipLaunchKernel(reinterpret_cast<const void*>(fb->grad_a), dim3((unsigned)(a.tiles_m * a.tiles_n)),
                             dim3(fb->threads), kargs, (size_t)fb->lds, s);
       }
       na = a.tiles_m * a.tiles_n;
     } else {
-      e = me ? me->launch(a, false, true, s) : hipErrorInvalidValue;
+      r = me ? me->launch(a, false, true, s) : hipErrorInvalidValue;
     }
-  } else {
-    na = 0;
-  }
-  if (e != hipSuccess) return hip_error(e, "backward dA launch");
+    return r;
+  };
 
   // dB: contraction over m.
-  GemmArgs b_any{};
-  bool any_b = false;
-  if (dB && kn && m == 0) {
-    e = launch_scale(dB, lddb, k, n, 0.0f, s);
-  } else if (run_b) {
+  auto pass_b = [&]() {
+    if (dB && kn && m == 0) return launch_scale(dB, lddb, k, n, 0.0f, s);
+    if (!run_b) return hipSuccess;
+    hipError_t r = hipSuccess;
     GemmArgs b{};
     b.A = A;
     b.lda = lda;
@@ -1145,45 +1238,59 @@ int hpvm_sgemm_backward(int64_t m, int64_t n, int64_t k, float alpha, float beta
     b.vec_a = vec16(A, lda);
     b.vec_b = vec16(G, ldg);
     if (dma_pair) {
-      e = launch_split_pair(prec, a_pair, b, plan.sp, reinterpret_cast<float*>(stage),
+      r = launch_split_pair(prec, a_pair, b, plan.sp, reinterpret_cast<float*>(stage),
                             reinterpret_cast<float*>(stage) + plan.sp * m * k, dA, ldda, dB, lddb,
                             dalpha ? A : nullptr, lda, dalpha ? pa : nullptr, gc, s);
       gc_done = true;
-    }
-    else if (dma_b)
-      e = prec == HPVM_PREC_FP32
+    } else if (dma_b) {
+      r = prec == HPVM_PREC_FP32
               ? launch_split<HPVM_PREC_FP32, true, false>(b, plan.sb, reinterpret_cast<float*>(stage), dB, lddb,
                                                           nullptr, 0, nullptr, s)
               : launch_split<HPVM_PREC_BF16, true, false>(b, plan.sb, reinterpret_cast<float*>(stage), dB, lddb,
                                                           nullptr, 0, nullptr, s);
-    else if (fb->any && f32_any_fits(b, true, false)) {
-      any_b = true;
+    } else if (fb->any && f32_any_fits(b, true, false)) {
       b_any = b;
-    }
-    else if (!me) e = hipErrorInvalidValue;
-    else if (staged && pair)
-      e = me->launch_staged_pair(a_pair, StagedPlanes{P.gh, P.gl, P.bh, P.bl}, A, lda, dalpha ? pa : nullptr, b,
+      if (order.apart) any_b = true;
+      else r = fb->any(nullptr, nullptr, 0, nullptr, &b, nullptr, s);
+    } else if (!me) {
+      r = hipErrorInvalidValue;
+    } else if (staged && pair) {
+      r = me->launch_staged_pair(a_pair, StagedPlanes{P.gh, P.gl, P.bh, P.bl}, A, lda, dalpha ? pa : nullptr, b,
                                  StagedPlanes{P.ah, P.al, P.th, P.tl}, s);
-    else if (staged)
-      e = me->launch_staged_planes(b, StagedPlanes{P.ah, P.al, P.th, P.tl}, nullptr, 0, nullptr, s);
-    else e = me->launch(b, true, false, s);
-  }
-  if (e != hipSuccess) return hip_error(e, "backward dB launch");
+    } else if (staged) {
+      r = me->launch_staged_planes(b, StagedPlanes{P.ah, P.al, P.th, P.tl}, nullptr, 0, nullptr, s);
+    } else {
+      r = me->launch(b, true, false, s);
+    }
+    return r;
+  };
 
-  if (any_a || any_b) {
-    const bool with_c = grad_c && !gc_done;
-    e = fb->any(any_a ? &a_pair : nullptr, A, lda, dalpha ? pa : nullptr, any_b ? &b_any : nullptr,
-                with_c ? &gc : nullptr, s);
-    gc_done = gc_done || with_c;
-  }
-  if (e != hipSuccess) return hip_error(e, "backward gradients launch");
-
-  if (grad_c && !gc_done) {
+  auto pass_c = [&]() {
+    if (!grad_c || gc_done) return hipSuccess;
     void* kargs[] = {&gc};
-    e = hipLaunchKernel(reinterpret_cast<const void*>(&sgemm_grad_c), dim3((unsigned)gc.blocks), dim3(kElemThreads),
-                        kargs, 0, s);
+    gc_done = true;
+    return hipLaunchKernel(reinterpret_cast<const void*>(&sgemm_grad_c), dim3((unsigned)gc.blocks), dim3(kElemThreads),
+                           kargs, 0, s);
+  };
+
+  // Planes and the pair's slices hold what the products read.  Otherwise an
+  // output that lies over another job's inputs is written after that job:
+  // separate launches, ordered by the stream.
+  const bool ordered = !order.apart && !staged && !dma_pair;
+  static const int kPlain[3] = {0, 1, 2};
+  const int* job = ordered ? order.job : kPlain;
+  for (int i = 0; i < 3; ++i) {
+    if (job[i] == 0 && (e = pass_a()) != hipSuccess) return hip_error(e, "backward dA launch");
+    if (job[i] == 1 && (e = pass_b()) != hipSuccess) return hip_error(e, "backward dB launch");
+    if (job[i] == 1 && (any_a || any_b)) {
+      const bool with_c = grad_c && !gc_done;
+      e = fb->any(any_a ? &a_pair : nullptr, A, lda, dalpha ? pa : nullptr, any_b ? &b_any : nullptr,
+                  with_c ? &gc : nullptr, s);
+      if (e != hipSuccess) return hip_error(e, "backward gradients launch");
+      gc_done = gc_done || with_c;
+    }
+    if (job[i] == 2 && (e = pass_c()) != hipSuccess) return hip_error(e, "backward dC_in launch");
   }
-  if (e != hipSuccess) return hip_error(e, "backward dC_in launch");
 
   if (dalpha || dbeta) {
     const float* pa_ = pa;

@@ -299,8 +299,8 @@ __device__ __forceinline__ void stage_gradient_block(const GradJob& j, int64_t b
       float g = 0.0f;
       if (gr < m && gc < n) {
         g = G[gr * ldg + gc];
+        if (partial) part = fmaf(g, Cin[gr * ldci + gc], part);  // first: dCin may be Cin
         if (dCin) dCin[gr * lddci + gc] = beta == 0.0f ? 0.0f : beta * g;
-        if (partial) part = fmaf(g, Cin[gr * ldci + gc], part);
       }
       t[r][c] = g;
     }
