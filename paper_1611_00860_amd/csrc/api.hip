@@ -184,23 +184,25 @@ static double tile_time(const TileTime& c, double tiles, double k) {
   return c.start + std::max(c.alone, rounds * c.shared) * k / 32.0 + (rounds - 1.0) * c.more;
 }
 
-// Where tiles that cannot run beside an open streaming graph may be taken:
-// from a tile of this size per CU on, or of their own if that needs alignment.
-// Smaller products are those a program runs while it streams.
-constexpr hpvm_tile kWideFrom{128, 128, 32, 64, 64, 4};
+// Where tiles that cannot run beside an open streaming graph may be taken.
+// Its two workgroups a CU leave 87 KB of LDS and, per SIMD, 176 registers; a
+// kernel that needs more waits until the stream has ended, which a program that
+// streams meanwhile cannot wait for.  They are taken where the product gives
+// 256 tiles of this size, or of their own if that needs alignment.
+constexpr hpvm_tile kWideFrom128{128, 128, 32, 64, 64, 4}, kWideFrom256{256, 256, 32, 64, 128, 2};
 
 // The candidate with the least time, a contraction split that fits split_ws
 // (< 0: any) included: the partial sums' traffic at 4 TB/s and the summing
 // launch.
 static bool least_time(const TileTime* c, int count, int32_t prec, int64_t m, int64_t n, int64_t k, int64_t split_ws,
-                       bool large_only, hpvm_tile* out, double* estimate) {
+                       bool large_only, const hpvm_tile& wide_from, hpvm_tile* out, double* estimate) {
   double best = 0.0;
   bool found = false;
   for (; count > 0; --count, ++c) {
     const hpvm_tile& t = c->tile;
     if (c->aligned && (m < t.tile_m || n < t.tile_n || n % 4 || k % t.tile_k)) continue;
     if (large_only && t.tile_m * t.tile_n < 128 * 256) continue;
-    if (c->wide && tiles_of(c->aligned ? t : kWideFrom, m, n) < 256) continue;
+    if (c->wide && tiles_of(c->aligned ? t : wide_from, m, n) < 256) continue;
     const MfmaEntry* e = find_menu_entry(prec, t);
     if (!e) continue;
     int64_t slices = 1;
@@ -241,7 +243,8 @@ static bool f32_groups_beat_split(const hpvm_tile& t, int64_t m, int64_t n, int6
   const double split = tile_time(c, (double)tiles, (double)k / slices) + 4.5 + (double)(bytes + m * n * 4) / 4.0e6;
   const TileTime* from = kF32Groups + (slices > 2 ? 1 : 0);  // two groups, four
   double groups = 0.0;
-  return slices <= 4 && least_time(from, (int)(std::end(kF32Groups) - from), HPVM_PREC_FP32, m, n, k, 0, false, out, &groups) &&
+  return slices <= 4 && least_time(from, (int)(std::end(kF32Groups) - from), HPVM_PREC_FP32, m, n, k, 0, false,
+                                   kWideFrom256, out, &groups) &&
          groups < split;
 }
 
@@ -264,7 +267,7 @@ bool f32_default_tile(int64_t m, int64_t n, int64_t k, int64_t split_ws, hpvm_ti
       kF32Groups[1],
   };
   return least_time(kCandidates, (int)(sizeof(kCandidates) / sizeof(kCandidates[0])), HPVM_PREC_FP32, m, n, k,
-                    split_ws, false, out, nullptr);
+                    split_ws, false, kWideFrom256, out, nullptr);
 }
 
 // BF16 and bf16x3, fitted the same way.  These loops move FP32 operands and
@@ -274,7 +277,8 @@ bool f32_default_tile(int64_t m, int64_t n, int64_t k, int64_t split_ws, hpvm_ti
 //   2048 x 2048 x 256: 64 x 128 11.8, 64 x 64 14.1; bf16x3 16.6, 18.5
 //   3000 x 3000 x 256: 256 x 256 24.0, 64 x 128 25.3; bf16x3 64 x 128 34.7
 //   100 x 3000 x 1500: 32 x 128, split 15.7, 64 x 64 18.0
-// bf16x3's 64 x 128 tile has 196 registers, and an open stream leaves 176.
+// bf16x3's 64 x 128 tile has 192 registers.  Products of 256 tiles of 256 x 256
+// (bf16x3: of 128 x 128) have never run beside an open stream.
 static bool bf16_default_tile(int32_t prec, int64_t m, int64_t n, int64_t k, int64_t split_ws, hpvm_tile* out,
                               double* estimate = nullptr, bool large_only = false) {
   const MfmaEntry* e0 = menu_entry_at(prec, 0);
@@ -296,7 +300,7 @@ static bool bf16_default_tile(int32_t prec, int64_t m, int64_t n, int64_t k, int
       {{32, 128, 32, 32, 32, 2}, 4.9, 0.509, 0.35, 1.85, false},
   };
   return least_time(prec == HPVM_PREC_BF16X3 ? kX3 : kBf16, (int)(sizeof(kX3) / sizeof(kX3[0])), prec, m, n, k,
-                    split_ws, large_only, out, estimate);
+                    split_ws, large_only, prec == HPVM_PREC_BF16X3 ? kWideFrom128 : kWideFrom256, out, estimate);
 }
 }  // namespace hpvm
 
@@ -342,7 +346,9 @@ const hpvm::MfmaEntry* fewest_slices(int32_t prec, int64_t m, int64_t n, int64_t
 //    estimated time, the staged 128 x 128 one included, where k < 1024
 //    (2500 x 2500 x 400 bf16x3: 36 us against 51 staged); for deeper ones
 //    the staged, unless 128 x 256 tiles on the FP32 operands are estimated
-//    faster, then hpvm_sgemm's choice.
+//    faster, then hpvm_sgemm's choice.  BF16 under 256 tiles of 256 x 256 keeps
+//    the staged 128 x 128 tile (64 KB, 88 registers: it runs beside an open
+//    stream) also where hpvm_sgemm's choice is faster but could not.
 // Returns false for hpvm_sgemm's choice.
 bool default_ws_tile(int32_t prec, int64_t m, int64_t n, int64_t k, int64_t ws_bytes, hpvm_tile* out) {
   const bool f32 = prec == HPVM_PREC_FP32, x3 = prec == HPVM_PREC_BF16X3;
@@ -380,7 +386,8 @@ bool default_ws_tile(int32_t prec, int64_t m, int64_t n, int64_t k, int64_t ws_b
   if (ws_bytes >= 0 && ws_bytes < hpvm::staged_workspace_bytes(prec, m, n, k)) return false;
   if (!big) {
     double direct = 0.0;
-    if (hpvm::bf16_default_tile(prec, m, n, k, 0, out, &direct, k >= 1024) && direct < time_small) return false;
+    const bool faster = hpvm::bf16_default_tile(prec, m, n, k, 0, out, &direct, k >= 1024) && direct < time_small;
+    if (faster && (x3 || big_tiles >= 256 || out->tile_m * out->tile_n < 128 * 128)) return false;
   }
   *out = big ? staged[0].tile : small->tile;
   return true;

@@ -44,7 +44,7 @@ constexpr int kGroupedThreads = 256;
 // slabs in as many stages as the Allocation holds: 48 KB for the grouped
 // launch, three workgroups a CU (128 x 128 tiles at 1024^3: 118 TFLOP/s
 // against 103 in 32 KB); 36 KB for the stream, whose two resident workgroups
-// leave 88 KB of a CU's LDS to the kernels that run beside it.
+// leave 87 KB of a CU's LDS to the kernels that run beside it.
 template <int TM, int TN, int WM, int WN, int NST>
 using GroupedAny = AnyShape<TM, TN, 16, WM, WN, false, false, NST, 1>;
 constexpr int64_t kGroupedLds = 49152, kStreamLds = 36864;

@@ -623,7 +623,11 @@ const BwdEntry* f32_pick(int64_t m, int64_t n, int64_t k) {
 // staged tile 0.27 (0.65), after its pass over the operands at 4.8 TB/s, and
 // 11 us of launches more than the fused.  Fused against staged, BF16 and
 // bf16x3: 1000 x 1200 x 800 30, 34 us against 42, 52; 300 x 3000 x 500 39, 54
-// against 57, 76; 2048^3 123, 190 against 73, 137.
+// against 57, 76; 2048^3 123, 190 against 73, 137.  A bf16x3 staged entry that
+// gives neither a tile per CU nor more than dA's in 64 x 64 is left out: it takes
+// 128 KB of LDS, an open streaming graph leaves 87 KB of a CU, and the fused
+// tiles that such calls had before do run beside one (1502 x 1675 x 1055: 84 us
+// against 62 staged).
 int64_t launch_tiles(const BwdEntry& e, int64_t m, int64_t n, int64_t k) {
   int64_t tiles = tiles_for(e.tile, m, k);
   const MfmaEntry* me = find_menu_entry(e.prec, e.tile);
@@ -631,7 +635,8 @@ int64_t launch_tiles(const BwdEntry& e, int64_t m, int64_t n, int64_t k) {
   return tiles;
 }
 
-const BwdEntry* staged_pick(int32_t prec, int64_t m, int64_t n, int64_t k) {
+// The staged entry of that rule, if its tiles are one per CU or more than `most`.
+const BwdEntry* staged_pick(int32_t prec, int64_t m, int64_t n, int64_t k, int64_t most) {
   if (!staged_k_ok(n) || !staged_k_ok(m)) return nullptr;  // the dA and dB contractions
   const BwdEntry* staged = nullptr;
   for (int i = 0; i < kNumBwd; ++i) {
@@ -640,10 +645,10 @@ const BwdEntry* staged_pick(int32_t prec, int64_t m, int64_t n, int64_t k) {
     // 0.131 for the staged 128 x 128 x 64 tile).
     if (kBwd[i].prec != prec || kBwd[i].dma || kBwd[i].grad_a) continue;
     const int64_t tiles = launch_tiles(kBwd[i], m, n, k);
-    if (!staged || tiles > launch_tiles(*staged, m, n, k)) staged = &kBwd[i];
-    if (tiles >= kTargetTiles) {
+    if (tiles >= kTargetTiles) return &kBwd[i];
+    if (tiles > most) {
       staged = &kBwd[i];
-      break;
+      most = tiles;
     }
   }
   return staged;
@@ -652,8 +657,8 @@ const BwdEntry* staged_pick(int32_t prec, int64_t m, int64_t n, int64_t k) {
 const BwdEntry* bf16_pick(int32_t prec, int64_t m, int64_t n, int64_t k) {
   const bool x3 = prec == HPVM_PREC_BF16X3;
   const BwdEntry* fused = find_bwd(prec, odd_tile(prec));
-  const BwdEntry* staged = staged_pick(prec, m, n, k);
-  if (!staged || !fused) return staged ? staged : fused;
+  const BwdEntry* staged = staged_pick(prec, m, n, k, x3 ? tiles_for(fused->tile, m, k) : 0);
+  if (!staged) return fused;
   // Slabs of the most tiles one of 256 CUs gets, and of one of the deeper.
   const double deep = (double)std::max(m, n) / 32.0;
   auto slabs = [&](const hpvm_tile& t) {
@@ -677,17 +682,13 @@ const BwdEntry* pick(int32_t prec, int64_t m, int64_t n, int64_t k) {
   return prec == HPVM_PREC_FP32 ? f32_pick(m, n, k) : bf16_pick(prec, m, n, k);
 }
 
-// The entry that has read every input when it writes the first gradient
-// (through slice sums or bfloat16 planes), for a call without a tile whose
-// outputs lie over its inputs as no order of the fused launches allows.
-// Null where its tiles are neither one per CU nor more than dA's in 64 x 64
-// (FP32: not whole).
+// For a call without a tile whose outputs lie over its inputs as no order of
+// the fused launches allows: an entry that has read every input when it writes
+// the first gradient (into slice sums or bfloat16 planes), where that gives
+// tiles enough (FP32: whole ones).  Null: none.
 const BwdEntry* inputs_first_pick(int32_t prec, int64_t m, int64_t n, int64_t k) {
   if (prec == HPVM_PREC_FP32) return dma_splits(m, k, n) ? &kBwd[0] : nullptr;
-  const BwdEntry* e = staged_pick(prec, m, n, k);
-  if (!e) return nullptr;
-  const int64_t tiles = launch_tiles(*e, m, n, k);
-  return tiles >= kTargetTiles || tiles > tiles_for(odd_tile(prec), m, k) ? e : nullptr;
+  return staged_pick(prec, m, n, k, tiles_for(odd_tile(prec), m, k));
 }
 
 // A matrix of a call; p null: absent.

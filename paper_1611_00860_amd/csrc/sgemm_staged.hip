@@ -392,7 +392,10 @@ struct StagedArgs {
 template <int BM, int BN>
 __device__ __forceinline__ void dalpha_epilogue(const StagedArgs& p, const f32x16 (&acc)[BM][BN], int row0,
                                                 int col0, int lane, int tile, char* smem) {
-  constexpr int kBatch = (BM * BN * 16 <= 64) ? BM : 1;  // row blocks loaded together
+  // Row blocks loaded together.  One of 64 x 32 waves' two: their pair of products
+  // keeps to 88 registers that way and runs beside an open streaming graph (with
+  // both, 91 and scalar registers spilled).
+  constexpr int kBatch = (BM * BN > 2 && BM * BN * 16 <= 64) ? BM : 1;
   const int64_t ldc = p.ldc, ldao = p.lda_orig;
   const int i0 = row0 + acc_row(0, lane), j0 = col0 + acc_col(lane);
   float* out = p.C ? p.C + (int64_t)i0 * ldc + j0 : nullptr;
@@ -689,6 +692,9 @@ __device__ __forceinline__ void bf16_dma_tile(const StagedArgs& p, int tile, cha
   }
   // No transfer may still be writing LDS when it is reused or released.
   dma_wait_barrier<0>();
+  // The epilogue's addresses are formed here, not kept through the loop.
+  int elane = lane;
+  asm volatile("" : "+v"(elane));
 
   if constexpr (EPI == 0) {
     GemmArgs e{};
@@ -700,9 +706,9 @@ __device__ __forceinline__ void bf16_dma_tile(const StagedArgs& p, int tile, cha
     e.n = p.n;
     e.alpha = p.alpha;
     e.beta = p.beta;
-    store_c<BM, BN>(e, acc, (int)m0 + wm0, (int)n0 + wn0, lane);
+    store_c<BM, BN>(e, acc, (int)m0 + wm0, (int)n0 + wn0, elane);
   } else {
-    dalpha_epilogue<BM, BN>(p, acc, (int)m0 + wm0, (int)n0 + wn0, lane, tile, smem);
+    dalpha_epilogue<BM, BN>(p, acc, (int)m0 + wm0, (int)n0 + wn0, elane, tile, smem);
   }
 }
 
