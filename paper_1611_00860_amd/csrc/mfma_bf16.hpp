@@ -275,7 +275,7 @@ __device__ __forceinline__ void bf16_mainloop_impl(const GemmArgs& p, int m0, in
   };
 
   zero_acc(acc);
-  const int slabs = (p.k + TK - 1) / TK;
+  const int slabs = slab_count(p.k, TK);
   fetch(0);
   stash(0);
   __syncthreads();

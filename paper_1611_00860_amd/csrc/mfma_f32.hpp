@@ -193,7 +193,7 @@ __device__ __forceinline__ void f32_mainloop_impl(
   };
 
   zero_acc(acc);
-  const int slabs = (p.k + TK - 1) / TK;
+  const int slabs = slab_count(p.k, TK);
   fetch(0);
   ga.template store_f32<OpA::kStride>(As0, tid);
   gb.template store_f32<OpB::kStride>(Bs0, tid);

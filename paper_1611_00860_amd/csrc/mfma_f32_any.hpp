@@ -348,7 +348,7 @@ __device__ __forceinline__ void any_tile(const GemmArgs& p, int splits, int tm, 
   // Whole slabs of k (moved by DMA), then at most one partial slab.
   const bool last_by_hand = (AT && p.m < TM && p.m % 4 != 0) || (!BT && p.n < TN && p.n % 4 != 0);
   const int dma_all = (last_by_hand ? p.k - 1 : p.k) / S::kSlab;
-  const int all = (p.k + S::kSlab - 1) / S::kSlab;
+  const int all = slab_count(p.k, S::kSlab);
   const int per = (all + splits - 1) / splits, sbeg = z * per;
   const int slabs = all - sbeg < per ? all - sbeg : per;  // <= 0: this slice is empty
   const int dma = (dma_all < sbeg + slabs ? dma_all : sbeg + slabs) - sbeg;

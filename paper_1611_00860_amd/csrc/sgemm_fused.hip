@@ -160,7 +160,7 @@ __device__ __forceinline__ void pair_mainloop_impl(const GemmArgs& p1, const Gem
   };
 
   zero_acc(acc);
-  const int slabs = (p1.k + TK - 1) / TK;
+  const int slabs = slab_count(p1.k, TK);
   fetch(0);
   stage(As0, Bs0);
   __syncthreads();
