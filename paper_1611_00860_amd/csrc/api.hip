@@ -58,10 +58,8 @@ void matrix_extent(const void* p, int64_t rows, int64_t cols, int64_t ld, uintpt
   *hi = (uintptr_t)p + (uintptr_t)(((rows - 1) * ld + cols) * (int64_t)sizeof(float));
 }
 
-int check_gemm_args(const char* what, int64_t m, int64_t n, int64_t k, float alpha, const float* A,
-                    int64_t lda, const float* B, int64_t ldb, float beta, const float* C,
-                    int64_t ldc, bool* reads_ab) {
-  (void)beta;
+int check_operands(const char* what, int64_t m, int64_t n, int64_t k, float alpha, const float* A, int64_t lda,
+                   const float* B, int64_t ldb, bool* reads_ab) {
   if (m < 0) return set_error(HPVM_INVALID_ARG, "%sargument 1: m = %lld < 0", what, (long long)m);
   if (n < 0) return set_error(HPVM_INVALID_ARG, "%sargument 2: n = %lld < 0", what, (long long)n);
   if (k < 0) return set_error(HPVM_INVALID_ARG, "%sargument 3: k = %lld < 0", what, (long long)k);
@@ -75,19 +73,34 @@ int check_gemm_args(const char* what, int64_t m, int64_t n, int64_t k, float alp
   if (*reads_ab && !B) return set_error(HPVM_INVALID_ARG, "%sargument 7: B is NULL", what);
   if (ldb < (n > 1 ? n : 1))
     return set_error(HPVM_INVALID_ARG, "%sargument 8: ldb = %lld < max(1, n)", what, (long long)ldb);
-  if (!empty && !C) return set_error(HPVM_INVALID_ARG, "%sargument 10: C is NULL", what);
+  return HPVM_OK;
+}
+
+int check_output(const char* what, int64_t m, int64_t n, int64_t k, const float* A, int64_t lda, const float* B,
+                 int64_t ldb, const float* C, int64_t ldc, bool reads_ab, int argno, char name) {
+  if (m > 0 && n > 0 && !C) return set_error(HPVM_INVALID_ARG, "%sargument %d: %c is NULL", what, argno, name);
   if (ldc < (n > 1 ? n : 1))
-    return set_error(HPVM_INVALID_ARG, "%sargument 11: ldc = %lld < max(1, n)", what, (long long)ldc);
-  if (*reads_ab) {
+    return set_error(HPVM_INVALID_ARG, "%sargument %d: ld%c = %lld < max(1, n)", what, argno + 1, name + ('a' - 'A'),
+                     (long long)ldc);
+  if (reads_ab) {
     uintptr_t c0, c1, x0, x1;
     matrix_extent(C, m, n, ldc, &c0, &c1);
     matrix_extent(A, m, k, lda, &x0, &x1);
     const bool oa = c0 < x1 && x0 < c1;
     matrix_extent(B, k, n, ldb, &x0, &x1);
     const bool ob = c0 < x1 && x0 < c1;
-    if (oa || ob) return set_error(HPVM_INVALID_ARG, "%sargument 10: C overlaps A or B", what);
+    if (oa || ob)
+      return set_error(HPVM_INVALID_ARG, "%sargument %d: %c overlaps A or B", what, argno, name);
   }
   return HPVM_OK;
+}
+
+int check_gemm_args(const char* what, int64_t m, int64_t n, int64_t k, float alpha, const float* A,
+                    int64_t lda, const float* B, int64_t ldb, float beta, const float* C,
+                    int64_t ldc, bool* reads_ab) {
+  (void)beta;
+  const int rc = check_operands(what, m, n, k, alpha, A, lda, B, ldb, reads_ab);
+  return rc != HPVM_OK ? rc : check_output(what, m, n, k, A, lda, B, ldb, C, ldc, *reads_ab, 10, 'C');
 }
 
 }  // namespace hpvm
@@ -562,33 +575,46 @@ int hpvm_dfg_edges(hpvm_edge* out, int32_t capacity, int32_t* count) {
 
 namespace {
 
+// Numbers, in the messages of an entry point's checks, of its output C (the
+// leading dimension is the next) and of its precision (the tile, workspace and
+// workspace's size are the next three).
+struct ArgNos {
+  int c, prec;
+  char c_name;
+};
+constexpr ArgNos kSgemmNos{10, 12, 'C'}, kIntoNos{12, 14, 'D'};
+
 // hpvm_sgemm and hpvm_sgemm_ws: `ws_ok` tells whether a workspace argument
-// exists (it is argument 14/15 of hpvm_sgemm_ws).  Cin, ldci: where beta * C
-// is read when that is not C (hpvm_sgemm_into, which checked them).
+// exists.  Cin, ldci: where beta * C is read when that is not C
+// (hpvm_sgemm_into, which checked them).
 int sgemm_impl(int64_t m, int64_t n, int64_t k, float alpha, const float* A, int64_t lda, const float* B,
                int64_t ldb, float beta, float* C, int64_t ldc, int32_t prec, const hpvm_tile* tile, bool ws_ok,
                void* workspace, int64_t workspace_bytes, void* stream, const float* Cin = nullptr,
-               int64_t ldci = 0) {
+               int64_t ldci = 0, const ArgNos& no = kSgemmNos) {
   // Checks in argument order; nothing below touches the device until all pass.
   bool reads_ab = false;
-  int rc = hpvm::check_gemm_args("", m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, &reads_ab);
+  int rc = hpvm::check_operands("", m, n, k, alpha, A, lda, B, ldb, &reads_ab);
+  if (rc == HPVM_OK) rc = hpvm::check_output("", m, n, k, A, lda, B, ldb, C, ldc, reads_ab, no.c, no.c_name);
   if (rc != HPVM_OK) return rc;
-  if (!valid_prec(prec)) return fail(HPVM_INVALID_ARG, "argument 12: unknown precision %d", prec);
+  if (!valid_prec(prec)) return fail(HPVM_INVALID_ARG, "argument %d: unknown precision %d", no.prec, prec);
   hpvm_tile tuned;
   if (!tile && choose_tile(prec, m, n, k, ws_ok, workspace ? workspace_bytes : 0, &tuned)) tile = &tuned;
   const hpvm::MfmaEntry* entry;
-  rc = resolve(prec, tile, &entry, 13);
+  rc = resolve(prec, tile, &entry, no.prec + 1);
   if (rc != HPVM_OK) return rc;
   const int64_t need = hpvm::entry_workspace_bytes(entry, m, n, k);
   if (need > 0 && reads_ab) {
     if (!hpvm::staged_k_ok(k))
-      return fail(HPVM_UNSUPPORTED, "argument 13: k = %lld is too deep for a tile with stages = 3", (long long)k);
+      return fail(HPVM_UNSUPPORTED, "argument %d: k = %lld is too deep for a tile with stages = 3", no.prec + 1,
+                  (long long)k);
     if (!ws_ok)
-      return fail(HPVM_UNSUPPORTED, "argument 13: tile with stages = 3 needs a workspace (use hpvm_sgemm_ws)");
-    if (!workspace) return fail(HPVM_INVALID_ARG, "argument 14: workspace is NULL");
-    if ((uintptr_t)workspace % 16) return fail(HPVM_INVALID_ARG, "argument 14: workspace is not 16-byte aligned");
+      return fail(HPVM_UNSUPPORTED, "argument %d: tile with stages = 3 needs a workspace (use hpvm_sgemm_ws)",
+                  no.prec + 1);
+    if (!workspace) return fail(HPVM_INVALID_ARG, "argument %d: workspace is NULL", no.prec + 2);
+    if ((uintptr_t)workspace % 16)
+      return fail(HPVM_INVALID_ARG, "argument %d: workspace is not 16-byte aligned", no.prec + 2);
     if (workspace_bytes < need)
-      return fail(HPVM_WORKSPACE_TOO_SMALL, "argument 15: workspace has %lld bytes, needs %lld",
+      return fail(HPVM_WORKSPACE_TOO_SMALL, "argument %d: workspace has %lld bytes, needs %lld", no.prec + 3,
                   (long long)workspace_bytes, (long long)need);
   }
   const bool empty = (m == 0 || n == 0);
@@ -651,15 +677,14 @@ int hpvm_sgemm_into(int64_t m, int64_t n, int64_t k, float alpha, const float* A
                     int64_t ldb, float beta, const float* C, int64_t ldc, float* D, int64_t ldd, int32_t prec,
                     const hpvm_tile* tile, void* workspace, int64_t workspace_bytes, void* stream) {
   bool reads_ab = false;
-  int rc = hpvm::check_gemm_args("", m, n, k, alpha, A, lda, B, ldb, beta, D, std::max(ldd, std::max<int64_t>(n, 1)),
-                                 &reads_ab);
+  int rc = hpvm::check_operands("", m, n, k, alpha, A, lda, B, ldb, &reads_ab);
   if (rc != HPVM_OK) return rc;
   const bool reads_c = m > 0 && n > 0 && beta != 0.0f;
   if (reads_c && !C) return fail(HPVM_INVALID_ARG, "argument 10: C is NULL (beta != 0)");
   if (ldc < std::max<int64_t>(n, 1))
     return fail(HPVM_INVALID_ARG, "argument 11: ldc = %lld < max(1, n)", (long long)ldc);
-  if (ldd < std::max<int64_t>(n, 1))
-    return fail(HPVM_INVALID_ARG, "argument 13: ldd = %lld < max(1, n)", (long long)ldd);
+  rc = hpvm::check_output("", m, n, k, A, lda, B, ldb, D, ldd, reads_ab, kIntoNos.c, kIntoNos.c_name);
+  if (rc != HPVM_OK) return rc;
   if (reads_c && !(C == D && ldc == ldd)) {
     uintptr_t c0, c1, d0, d1;
     hpvm::matrix_extent(C, m, n, ldc, &c0, &c1);
@@ -667,7 +692,7 @@ int hpvm_sgemm_into(int64_t m, int64_t n, int64_t k, float alpha, const float* A
     if (c0 < d1 && d0 < c1) return fail(HPVM_INVALID_ARG, "argument 12: D overlaps C without being C itself");
   }
   return sgemm_impl(m, n, k, alpha, A, lda, B, ldb, beta, D, ldd, prec, tile, true, workspace, workspace_bytes, stream,
-                    reads_c ? C : nullptr, ldc);
+                    reads_c ? C : nullptr, ldc, kIntoNos);
 }
 
 int hpvm_sgemm_workspace_bytes(int64_t m, int64_t n, int64_t k, int32_t prec, const hpvm_tile* tile,
@@ -687,9 +712,21 @@ int hpvm_sgemm_workspace_bytes(int64_t m, int64_t n, int64_t k, int32_t prec, co
 int64_t hpvm_sgemm_or_bytes(int64_t m, int64_t n, int64_t k, float alpha, const float* A, int64_t lda, const float* B,
                             int64_t ldb, float beta, float* C, int64_t ldc, int32_t prec, const hpvm_tile* tile,
                             void* stream) {
-  int64_t need = 0;
-  const int rc = hpvm_sgemm_workspace_bytes(m, n, k, prec, tile, &need);
-  if (rc != HPVM_OK || need > 0) return rc != HPVM_OK ? rc : need;
+  bool reads_ab = false;
+  int rc = hpvm::check_gemm_args("", m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, &reads_ab);
+  if (rc != HPVM_OK) return rc;
+  if (!valid_prec(prec)) return fail(HPVM_INVALID_ARG, "argument 12: unknown precision %d", prec);
+  hpvm_tile tuned;
+  const hpvm_tile* t = tile;
+  if (!t && choose_tile(prec, m, n, k, true, -1, &tuned)) t = &tuned;
+  const hpvm::MfmaEntry* entry;
+  rc = resolve(prec, t, &entry, 13);
+  if (rc != HPVM_OK) return rc;
+  const int64_t need = std::max(hpvm::entry_workspace_bytes(entry, m, n, k), hpvm::entry_split_bytes(entry, m, n, k));
+  if (need > 0) {
+    hpvm::clear_error();
+    return need;
+  }
   return hpvm_sgemm(m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, prec, tile, stream);
 }
 

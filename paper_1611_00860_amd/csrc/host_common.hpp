@@ -31,6 +31,14 @@ int check_gemm_args(const char* what, int64_t m, int64_t n, int64_t k, float alp
                     int64_t lda, const float* B, int64_t ldb, float beta, const float* C,
                     int64_t ldc, bool* reads_ab);
 
+// Its two halves: the sizes and operands (arguments 1 to 8), and the output,
+// which is argument argno, `name` in messages, and its leading dimension the
+// next one.
+int check_operands(const char* what, int64_t m, int64_t n, int64_t k, float alpha, const float* A, int64_t lda,
+                   const float* B, int64_t ldb, bool* reads_ab);
+int check_output(const char* what, int64_t m, int64_t n, int64_t k, const float* A, int64_t lda, const float* B,
+                 int64_t ldb, const float* C, int64_t ldc, bool reads_ab, int argno, char name);
+
 // Byte range [lo, hi) of a row-major rows x cols float matrix.
 void matrix_extent(const void* p, int64_t rows, int64_t cols, int64_t ld, uintptr_t* lo, uintptr_t* hi);
 
