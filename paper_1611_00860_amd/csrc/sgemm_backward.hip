@@ -1192,7 +1192,7 @@ int hpvm_sgemm_backward(int64_t m, int64_t n, int64_t k, float alpha, float beta
         a_pair = a;  // launched with dB below
       else
         r = me->launch_staged_planes(a, StagedPlanes{P.gh, P.gl, P.bh, P.bl}, A, lda, dalpha ? pa : nullptr, s);
-    } else if (fb->any && f32_any_fits(a, false, true) && lda < kAnyPitch) {
+    } else if (fb->any && f32_any_fits(a, false, true) && (!dalpha || lda < kAnyPitch)) {
       na = dalpha ? tiles_for(fb->tile, m, k) : 0;
       a_pair = a;
       if (order.apart) any_a = true;

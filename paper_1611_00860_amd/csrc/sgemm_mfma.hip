@@ -90,17 +90,23 @@ struct Bf16Config {
   static constexpr int kThreads = (TM / WM) * (TN / WN) * kWave;
   static constexpr int64_t lds(bool, bool) { return Bf16TileShape<TM, TN, TK, WM, WN, X3>::kLdsBytes; }
   static hipError_t launch(const GemmArgs& args, bool at, bool bt, hipStream_t s) {
-    GemmArgs a = args;
-    a.tiles_m = (a.m + TM - 1) / TM;
-    a.tiles_n = (a.n + TN - 1) / TN;
-    const dim3 grid((unsigned)(a.tiles_m * a.tiles_n));
-    void* kargs[] = {&a};
     void (*fn)(GemmArgs);
     if (!at && !bt) fn = &sgemm_mfma_bf16<TM, TN, TK, WM, WN, false, false, X3>;
     else if (at && !bt) fn = &sgemm_mfma_bf16<TM, TN, TK, WM, WN, true, false, X3>;
     else if (!at && bt) fn = &sgemm_mfma_bf16<TM, TN, TK, WM, WN, false, true, X3>;
     else return hipErrorInvalidValue;
-    const size_t bytes = (size_t)lds(at, bt);
+    return launch_fn(fn, args, s);
+  }
+  static hipError_t launch_plain(const GemmArgs& args, hipStream_t s) {
+    return launch_fn(&sgemm_mfma_bf16<TM, TN, TK, WM, WN, false, false, X3>, args, s);
+  }
+  static hipError_t launch_fn(void (*fn)(GemmArgs), const GemmArgs& args, hipStream_t s) {
+    GemmArgs a = args;
+    a.tiles_m = (a.m + TM - 1) / TM;
+    a.tiles_n = (a.n + TN - 1) / TN;
+    const dim3 grid((unsigned)(a.tiles_m * a.tiles_n));
+    void* kargs[] = {&a};
+    const size_t bytes = (size_t)lds(false, false);
     hipError_t e = allow_lds(fn, bytes);
     if (e != hipSuccess) return e;
     return hipLaunchKernel(reinterpret_cast<const void*>(fn), grid, dim3(kThreads), kargs, bytes, s);
@@ -119,11 +125,10 @@ struct Bf16Config {
 // 1500 x 1100 x 900, 64 x 128 tiles, 17.7 against 30.6.
 template <int PREC, int TM, int TN, int TK, int WM, int WN, int NST, int KW>
 struct AnyConfig {
-  template <bool AT, bool BT>
-  using Shape = AnyShape<TM, TN, TK, WM, WN, AT, BT, NST, KW>;
-  static constexpr int kThreads = Shape<false, false>::kThreads;
-  static constexpr int64_t kLdsBytes = Shape<false, false>::kLdsBytes;
-  template <bool AT, bool BT, int MODE>
+  using Shape = AnyShape<TM, TN, TK, WM, WN, false, false, NST, KW>;
+  static constexpr int kThreads = Shape::kThreads;
+  static constexpr int64_t kLdsBytes = Shape::kLdsBytes;
+  template <int MODE>
   static hipError_t run(const GemmArgs& args, int splits, hipStream_t s) {
     GemmArgs a = args;
     a.tiles_m = (a.m + TM - 1) / TM;
@@ -132,22 +137,19 @@ struct AnyConfig {
     o.splits = splits;
     void* kargs[] = {&a, &o};
     void (*fn)(GemmArgs, F32DmaOut);
-    if constexpr (PREC == HPVM_PREC_FP32) fn = &sgemm_f32_any<TM, TN, TK, WM, WN, AT, BT, NST, KW, MODE>;
-    else fn = &sgemm_bf16_any<TM, TN, TK, WM, WN, AT, BT, NST, KW, PREC == HPVM_PREC_BF16X3, MODE>;
+    if constexpr (PREC == HPVM_PREC_FP32) fn = &sgemm_f32_any<TM, TN, TK, WM, WN, false, false, NST, KW, MODE>;
+    else fn = &sgemm_bf16_any<TM, TN, TK, WM, WN, false, false, NST, KW, PREC == HPVM_PREC_BF16X3, MODE>;
     hipError_t e = allow_lds(fn, (size_t)kLdsBytes);
     if (e != hipSuccess) return e;
     return hipLaunchKernel(reinterpret_cast<const void*>(fn), dim3((unsigned)(a.tiles_m * a.tiles_n * splits)),
                            dim3(kThreads), kargs, (size_t)kLdsBytes, s);
   }
   static hipError_t launch(const GemmArgs& a, bool at, bool bt, hipStream_t s) {
-    if (at && bt) return hipErrorInvalidValue;
-    if (!f32_any_fits(a, at, bt)) {
-      if constexpr (PREC == HPVM_PREC_FP32) return F32Config<64, 64, 16, 32, 32>::launch(a, at, bt, s);
-      else return Bf16Config<64, 64, 32, 32, 32, PREC == HPVM_PREC_BF16X3>::launch(a, at, bt, s);
-    }
-    return at   ? run<true, false, kDmaUpdate>(a, 1, s)
-           : bt ? run<false, true, kDmaUpdate>(a, 1, s)
-                : run<false, false, kDmaUpdate>(a, 1, s);
+    // Transposed operands come from the backward only, which gives this entry what
+    // its own launch of both products leaves out.
+    if (!at && !bt && f32_any_fits(a, false, false)) return run<kDmaUpdate>(a, 1, s);
+    if constexpr (PREC == HPVM_PREC_FP32) return F32Config<64, 64, 16, 32, 32>::launch(a, at, bt, s);
+    else return Bf16Config<64, 64, 32, 32, 32, PREC == HPVM_PREC_BF16X3>::launch(a, at, bt, s);
   }
   // Contraction slices of a product whose tiles would leave CUs idle (any
   // sizes): doubled while they would, each at least 256 deep, at most 16.
@@ -177,7 +179,7 @@ struct AnyConfig {
     a.C = part;
     a.ldc = a.n;
     a.beta = 0.0f;
-    hipError_t e = run<false, false, kDmaSplit>(a, sp, s);
+    hipError_t e = run<kDmaSplit>(a, sp, s);
     if (e != hipSuccess) return e;
     return launch_split_finish(part, sp, args, s);
   }
@@ -360,8 +362,8 @@ static const MfmaEntry kF32Menu[] = {
 struct Bf16x3WideConfig {
   using Any = AnyConfig<HPVM_PREC_BF16X3, 256, 256, 16, 128, 64, 2, 1>;
   static hipError_t launch(const GemmArgs& a, bool at, bool bt, hipStream_t s) {
-    return a.vec_a && a.vec_b ? Bf16Config<256, 256, 32, 128, 64, true>::launch(a, at, bt, s)
-                              : Any::launch(a, at, bt, s);
+    return a.vec_a && a.vec_b && !at && !bt ? Bf16Config<256, 256, 32, 128, 64, true>::launch_plain(a, s)
+                                            : Any::launch(a, at, bt, s);
   }
 };
 #define HPVM_BF16_SPLIT_ENTRY(PREC, TM, TN, TK, WM, WN, SUB, NST)                                         \
