@@ -77,12 +77,19 @@ def is_fp32_gemm(kernel_name):
 
 def fp32_kernel_name(tile, m, n, k):
     """The kernel an FP32 menu tile launches for a row-major problem with aligned operands."""
+    import paper_1611_00860_amd as hp
+
+    if n < 4:
+        return "sgemm_mfma_f32<64, 64, 16, 32, 32, false, false>"
     tm, tn, tk, lm, ln, st = tile
-    if ln == 128 and m % tm == 0 and n % tn == 0 and k % tk == 0:
-        return f"sgemm_f32_dma<{tm}, {tn}, {tk}, {lm}, 128, false, false, {st}, 0, 0, false, false>"
-    if ln == 128:
-        tm, tn, tk, lm, ln = 128, 128, 16, 64, 64
-    return f"sgemm_mfma_f32<{tm}, {tn}, {tk}, {lm}, {ln}, false, false>"
+    if ln == 128 and m >= tm and n >= tn and n % 4 == 0 and k % tk == 0:
+        edges = "false" if m % tm == 0 and n % tn == 0 else "true"
+        return f"sgemm_f32_dma<{tm}, {tn}, {tk}, {lm}, 128, false, false, {st}, 0, 0, false, {edges}>"
+    if ln == 128:  # not aligned: what those entries run instead
+        tm, tn, tk, lm, ln, st = tile = (64, 128, 32, 32, 64, 2)
+    groups = max(1, 32 // lm)  # of k; a leaf owns its wave's share of the rows
+    stages = hp.describe(m, n, k, "fp32", tile)["alloc_bytes"] // (4 * tk * (tm + tn))
+    return f"sgemm_f32_any<{tm}, {tn}, {tk // groups}, {lm * groups}, {ln}, false, false, {stages}, {groups}, 0>"
 
 
 def _tile_key(tile, m, n, k, beta):
