@@ -617,17 +617,23 @@ const BwdEntry* f32_pick(int64_t m, int64_t n, int64_t k) {
 
 // Built-in choice for BF16 and bf16x3: the first staged entry giving at least
 // one tile per CU of a 256-CU part, else the one giving the most (dA's tiles,
-// plus dB's where one launch runs both), or the fused 64 x 64 tiles where
-// those are estimated faster.  Per 32-deep slab a round of 256 fused tiles
-// takes 0.25 us (bf16x3: 0.37), one tile alone 0.28 (0.44); a 128 x 128
-// staged tile 0.27 (0.65), after its pass over the operands at 4.8 TB/s, and
-// 11 us of launches more than the fused.  Fused against staged, BF16 and
-// bf16x3: 1000 x 1200 x 800 30, 34 us against 42, 52; 300 x 3000 x 500 39, 54
-// against 57, 76; 2048^3 123, 190 against 73, 137.  A bf16x3 staged entry that
-// gives neither a tile per CU nor more than dA's in 64 x 64 is left out: it takes
+// plus dB's where one launch runs both); for bf16x3, whose first is of 256 x 256,
+// also the 128 x 128 x 64 one of 64 x 32 waves; or the fused 64 x 64 tiles: the
+// least estimated time of these.  Per 32-deep slab a round of 256 fused tiles
+// takes 0.25 us (bf16x3: 0.37), one tile alone 0.28 (0.44); a 128 x 128 staged
+// tile 0.27 (0.65), bf16x3's 256 x 256 one 2.4, after the pass over the operands
+// at 4.8 TB/s, and 11 us of launches more than the fused.  Fused against staged,
+// BF16 and bf16x3: 1000 x 1200 x 800 30, 34 us against 42, 52; 300 x 3000 x 500
+// 39, 54 against 57, 76; 2048^3 123, 190 against 73, 137.  bf16x3 in 256 x 256,
+// 128 x 128 and fused tiles: 1024 x 4096 x 4096 295, 225, 337; 4096^3 752, 931,
+// 1324; 1024 x 8192 x 1024 471, 185, 177.  A bf16x3 staged entry that
+// gives neither a tile per CU nor as many as dA's in 64 x 64 is left out: it takes
 // 128 KB of LDS, an open streaming graph leaves 87 KB of a CU, and the fused
 // tiles that such calls had before do run beside one (1502 x 1675 x 1055: 84 us
-// against 62 staged).
+// against 62 staged).  With less than four columns of G or A the fused launch
+// leaves dB to the register-staged tile (f32_any_fits), which the estimate does
+// not hold for: fused only where the staged entry is left out (BF16
+// 4096 x 1 x 4096: 89 us staged, 223 fused).
 int64_t launch_tiles(const BwdEntry& e, int64_t m, int64_t n, int64_t k) {
   int64_t tiles = tiles_for(e.tile, m, k);
   const MfmaEntry* me = find_menu_entry(e.prec, e.tile);
@@ -635,8 +641,9 @@ int64_t launch_tiles(const BwdEntry& e, int64_t m, int64_t n, int64_t k) {
   return tiles;
 }
 
-// The staged entry of that rule, if its tiles are one per CU or more than `most`.
-const BwdEntry* staged_pick(int32_t prec, int64_t m, int64_t n, int64_t k, int64_t most) {
+// The first staged entry of that rule, if its tiles are one per CU or at least
+// `least`.
+const BwdEntry* staged_pick(int32_t prec, int64_t m, int64_t n, int64_t k, int64_t least) {
   if (!staged_k_ok(n) || !staged_k_ok(m)) return nullptr;  // the dA and dB contractions
   const BwdEntry* staged = nullptr;
   for (int i = 0; i < kNumBwd; ++i) {
@@ -646,9 +653,9 @@ const BwdEntry* staged_pick(int32_t prec, int64_t m, int64_t n, int64_t k, int64
     if (kBwd[i].prec != prec || kBwd[i].dma || kBwd[i].grad_a) continue;
     const int64_t tiles = launch_tiles(kBwd[i], m, n, k);
     if (tiles >= kTargetTiles) return &kBwd[i];
-    if (tiles > most) {
+    if (tiles >= least) {
       staged = &kBwd[i];
-      most = tiles;
+      least = tiles + 1;
     }
   }
   return staged;
@@ -657,9 +664,11 @@ const BwdEntry* staged_pick(int32_t prec, int64_t m, int64_t n, int64_t k, int64
 const BwdEntry* bf16_pick(int32_t prec, int64_t m, int64_t n, int64_t k) {
   const bool x3 = prec == HPVM_PREC_BF16X3;
   const BwdEntry* fused = find_bwd(prec, odd_tile(prec));
-  const BwdEntry* staged = staged_pick(prec, m, n, k, x3 ? tiles_for(fused->tile, m, k) : 0);
-  if (!staged) return fused;
+  const bool narrow = n < 4 || k < 4;
+  const BwdEntry* staged = staged_pick(prec, m, n, k, x3 || narrow ? tiles_for(fused->tile, m, k) : 0);
+  if (!staged || narrow) return staged ? staged : fused;
   // Slabs of the most tiles one of 256 CUs gets, and of one of the deeper.
+  constexpr hpvm_tile kSmallStaged{128, 128, 64, 64, 32, 3};
   const double deep = (double)std::max(m, n) / 32.0;
   auto slabs = [&](const hpvm_tile& t) {
     const double ta = (double)tiles_for(t, m, k), tb = (double)tiles_for(t, k, n);
@@ -668,8 +677,16 @@ const BwdEntry* bf16_pick(int32_t prec, int64_t m, int64_t n, int64_t k) {
   };
   const double tf = 10.0 + std::max(slabs(fused->tile) * (x3 ? 0.37 : 0.25), deep * (x3 ? 0.44 : 0.28));
   const double bytes = (double)m * n * (x3 ? 20.0 : 16.0) + ((double)m * k + (double)k * n) * (x3 ? 8.0 : 6.0);
-  const double slab = (x3 ? 0.65 : 0.27) * staged->tile.tile_m * staged->tile.tile_n / (128.0 * 128.0);
-  const double ts = 21.0 + bytes / 4.8e6 + std::max(slabs(staged->tile), deep) * slab;
+  auto time = [&](const hpvm_tile& t) {
+    const double area = (double)t.tile_m * t.tile_n / (128.0 * 128.0);
+    return 21.0 + bytes / 4.8e6 +
+           std::max(slabs(t), deep) * (!x3 ? 0.27 * area : area < 4.0 ? 0.65 * area : 2.4);
+  };
+  double ts = time(staged->tile);
+  if (x3 && time(kSmallStaged) < ts) {
+    staged = find_bwd(prec, kSmallStaged);
+    ts = time(kSmallStaged);
+  }
   return tf < ts ? fused : staged;
 }
 
