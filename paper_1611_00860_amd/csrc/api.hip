@@ -216,10 +216,9 @@ static bool least_time(const TileTime* c, int count, int32_t prec, int64_t m, in
     if (c->aligned && (m < t.tile_m || n < t.tile_n || n % 4 || k % t.tile_k)) continue;
     if (large_only && t.tile_m * t.tile_n < 128 * 256) continue;
     if (c->wide && tiles_of(c->aligned ? t : wide_from, m, n) < 256) continue;
-    const MfmaEntry* e = find_menu_entry(prec, t);
-    if (!e) continue;
-    int64_t slices = 1;
-    const int64_t bytes = c->aligned ? 0 : entry_split_bytes(e, m, n, k);
+    int64_t slices = 1, bytes = 0;
+    if (!c->aligned && k >= 1024)  // no entry splits less (AnyConfig::splits)
+      bytes = entry_split_bytes(find_menu_entry(prec, t), m, n, k);
     if (bytes > 0 && (split_ws < 0 || split_ws >= bytes)) slices = bytes / (m * n * (int64_t)sizeof(float));
     double time = tile_time(*c, (double)(tiles_of(t, m, n) * slices), (double)k / slices);
     if (slices > 1) time += 4.5 + (double)(bytes + m * n * 4) / 4.0e6;
@@ -712,22 +711,22 @@ int hpvm_sgemm_workspace_bytes(int64_t m, int64_t n, int64_t k, int32_t prec, co
 int64_t hpvm_sgemm_or_bytes(int64_t m, int64_t n, int64_t k, float alpha, const float* A, int64_t lda, const float* B,
                             int64_t ldb, float beta, float* C, int64_t ldc, int32_t prec, const hpvm_tile* tile,
                             void* stream) {
-  bool reads_ab = false;
-  int rc = hpvm::check_gemm_args("", m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, &reads_ab);
-  if (rc != HPVM_OK) return rc;
-  if (!valid_prec(prec)) return fail(HPVM_INVALID_ARG, "argument 12: unknown precision %d", prec);
-  hpvm_tile tuned;
-  const hpvm_tile* t = tile;
-  if (!t && choose_tile(prec, m, n, k, true, -1, &tuned)) t = &tuned;
-  const hpvm::MfmaEntry* entry;
-  rc = resolve(prec, t, &entry, 13);
-  if (rc != HPVM_OK) return rc;
-  const int64_t need = std::max(hpvm::entry_workspace_bytes(entry, m, n, k), hpvm::entry_split_bytes(entry, m, n, k));
-  if (need > 0) {
-    hpvm::clear_error();
-    return need;
+  int64_t need = 0;
+  if (m >= 0 && n >= 0 && k >= 0 && valid_prec(prec)) {
+    hpvm_tile tuned;
+    const hpvm_tile* t = tile;
+    if (!t && choose_tile(prec, m, n, k, true, -1, &tuned)) t = &tuned;
+    const hpvm::MfmaEntry* entry;
+    if (resolve(prec, t, &entry, 13) == HPVM_OK)
+      need = std::max(hpvm::entry_workspace_bytes(entry, m, n, k), hpvm::entry_split_bytes(entry, m, n, k));
   }
-  return hpvm_sgemm(m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, prec, tile, stream);
+  // hpvm_sgemm checks every argument; where it is not to be called, so does this.
+  if (need == 0) return hpvm_sgemm(m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, prec, tile, stream);
+  bool reads_ab = false;
+  const int rc = hpvm::check_gemm_args("", m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, &reads_ab);
+  if (rc != HPVM_OK) return rc;
+  hpvm::clear_error();
+  return need;
 }
 
 int hpvm_launch_root(const hpvm_root_in* r, void* stream) {
