@@ -53,8 +53,8 @@ __device__ __forceinline__ void read_early(const GemmArgs& p) {
   read_early(p.C, p.ldc, p.alpha, p.beta, p.Cin, p.ldci);
 }
 
-// Slabs of depth `slab` that a contraction of k takes.  k (a backward's m or n
-// at that) may be 2^31 - 1, so that k + slab - 1 is no int.
+// Slabs of depth `slab` that a contraction of k takes, where k (a backward's m
+// or n at that) may be 2^31 - 1, so that k + slab - 1 is no int.
 __host__ __device__ constexpr int slab_count(int k, int slab) { return k / slab + (k % slab != 0); }
 
 // True when the TM x TN tile at (m0, n0) and every K-slab of depth TK lie
