@@ -573,23 +573,31 @@ int64_t split_sum_blocks(int64_t rows, int64_t cols) {
 // 64 x 64 49, 64 x 128 58; 2048^3 64 x 128 264, 256 x 256 273;
 // 64 x 4096 x 1000 32 x 32 39, 64 x 64 99; 1024^3 32 x 32 60,
 // 256 x 256 in four slices 82.
+struct F32Candidate {
+  hpvm_tile tile;
+  double start, alone, shared, more, worth;
+  int groups;  // of k; the DMA entry: its slices
+};
+constexpr F32Candidate kF32Candidates[] = {
+    {{kDmaTile, kDmaTile, kDmaK, kDmaWM, kDmaWN, kDmaStages}, 16.0, 6.31, 6.89, 32.0, 0.7, 0},
+    {{64, 128, 32, 32, 64, 2}, 9.2, 1.2, 1.0, 2.3, 1.0, 1},
+    {{64, 64, 16, 32, 32, 2}, 7.5, 0.712, 0.541, 1.43, 1.0, 1},
+    {{64, 64, 32, 16, 32, 2}, 8.7, 0.597, 0.498, 2.3, 1.0 / 0.7, 2},
+    {{32, 32, 128, 8, 32, 2}, 8.4, 0.141, 0.129, 2.0, 1.0 / 0.7, 4},
+};
+// ta tiles of dA (contracting over n) and tb of dB (over m), in `slices`.
+double f32_time(const F32Candidate& c, double ta, double tb, int64_t m, int64_t n, double slices) {
+  const double deep = (double)std::max(ta > 0.0 ? n : 0, tb > 0.0 ? m : 0) / 32.0 / slices;
+  const double mean = (ta * n + tb * m) / std::max(ta + tb, 1.0) / 32.0 / slices;
+  const double rounds = (double)(((int64_t)((ta + tb) * slices) + 255) / 256);
+  return c.start + std::max(rounds * mean * c.shared, deep * c.alone) + (rounds - 1.0) * c.more;
+}
+
 const BwdEntry* f32_pick(int64_t m, int64_t n, int64_t k) {
-  struct Candidate {
-    hpvm_tile tile;
-    double start, alone, shared, more, worth;
-    int groups;  // of k; the DMA entry: its slices
-  };
-  static const Candidate kCandidates[] = {
-      {{kDmaTile, kDmaTile, kDmaK, kDmaWM, kDmaWN, kDmaStages}, 16.0, 6.31, 6.89, 32.0, 0.7, 0},
-      {{64, 128, 32, 32, 64, 2}, 9.2, 1.2, 1.0, 2.3, 1.0, 1},
-      {{64, 64, 16, 32, 32, 2}, 7.5, 0.712, 0.541, 1.43, 1.0, 1},
-      {{64, 64, 32, 16, 32, 2}, 8.7, 0.597, 0.498, 2.3, 1.0 / 0.7, 2},
-      {{32, 32, 128, 8, 32, 2}, 8.4, 0.141, 0.129, 2.0, 1.0 / 0.7, 4},
-  };
   const int pair = pair_splits(m, n, k), cut = pair ? pair : dma_splits(m, k, n);
   const BwdEntry* pick = nullptr;
   double best = 0.0;
-  for (const Candidate& c : kCandidates) {
+  for (const F32Candidate& c : kF32Candidates) {
     const BwdEntry* e = find_bwd(HPVM_PREC_FP32, c.tile);
     if (!e) continue;
     const double ta = (double)tiles_for(c.tile, m, k), tb = (double)tiles_for(c.tile, k, n);
@@ -602,11 +610,7 @@ const BwdEntry* f32_pick(int64_t m, int64_t n, int64_t k) {
       continue;
     }
     const double worth = !e->dma && cut > 1 ? 1.0 : c.worth;
-    const double deep = (double)std::max(m, n) / 32.0 / slices;
-    const double mean = (ta * n + tb * m) / std::max(ta + tb, 1.0) / 32.0 / slices;
-    const double rounds = (double)(((int64_t)((ta + tb) * slices) + 255) / 256);
-    const double time = worth * (c.start + std::max(rounds * mean * c.shared, deep * c.alone) +
-                                   (rounds - 1.0) * c.more + extra);
+    const double time = worth * (f32_time(c, ta, tb, m, n, slices) + extra);
     if (!pick || time < best) {
       best = time;
       pick = e;
@@ -751,6 +755,29 @@ BwdOrder bwd_order(const BwdJob (&jobs)[3]) {
   } while (std::next_permutation(o.job, o.job + 3));
   o.found = false;
   return o;  // the last step left job at 0, 1, 2
+}
+
+// The tile of a call for one FP32 gradient alone, without the scalars (their
+// sums' order is their tile's): the choice for both, `both`, unless a tile
+// without k groups takes that gradient less by a quarter.  Where one of m and n
+// is small, `both` goes by the gradient that contracts over the other, and the
+// other gradient alone had become slower on it than before it was chosen so
+// (7296 x 28 x 768: dA alone 49 us in 32 x 32 tiles, 14 in 64 x 128).
+const BwdEntry* f32_single(int64_t m, int64_t n, int64_t k, bool is_a, const BwdEntry* both) {
+  const BwdEntry* best = both;
+  double limit = 0.0, least = 0.0;
+  auto time = [&](const F32Candidate& c) {
+    return is_a ? f32_time(c, (double)tiles_for(c.tile, m, k), 0.0, m, n, 1.0)
+                : f32_time(c, 0.0, (double)tiles_for(c.tile, k, n), m, n, 1.0);
+  };
+  for (const F32Candidate& c : kF32Candidates)
+    if (same_tile(c.tile, both->tile)) limit = 0.75 * time(c);
+  for (const F32Candidate& c : kF32Candidates) {
+    if (c.groups != 1 || time(c) >= (best == both ? limit : least)) continue;
+    best = find_bwd(HPVM_PREC_FP32, c.tile);
+    least = time(c);
+  }
+  return best;
 }
 
 int64_t elem_blocks(int64_t m, int64_t n) {
@@ -1057,6 +1084,10 @@ int hpvm_sgemm_backward(int64_t m, int64_t n, int64_t k, float alpha, float beta
       {{dC_in, m, n, lddci}, {none, none}, {grad_c ? in_g : none, dbeta ? Mat{C_in, m, n, ldci} : none}}};
   const BwdOrder order = bwd_order(jobs);
   const int64_t total = call_bytes(cfg, tile, prec, m, n, k);
+  hpvm_tile tuned;
+  if (!tile && prec == HPVM_PREC_FP32 && cfg->any && run_a != run_b && !dalpha && !dbeta &&
+      !tuned_backward_tile(prec, m, n, k, &tuned))
+    cfg = f32_single(m, n, k, run_a, cfg);  // needs no workspace
   if (!order.found && !tile && cfg->any && workspace && workspace_bytes >= total) {
     const BwdEntry* other = inputs_first_pick(prec, m, n, k);
     if (other) cfg = other;
