@@ -90,7 +90,7 @@ typedef enum hpvm_precision {
  *                   C reading A and B from global memory, tile_m x tile_n
  *                   lanes per launch group; 1 = one buffer
  *                   (literal lowering); 2 = tiles with leaves less than
- *                   128 wide: a ring of two to four LDS stages filled
+ *                   128 wide: a ring of two to six LDS stages filled
  *                   straight from HBM, for any sizes and alignment (but for
  *                   products with n < 4 or rows 2^22 floats or more apart,
  *                   which run a 64 x 64 tile filled through registers), and
@@ -238,8 +238,10 @@ int hpvm_sgemm(int64_t m, int64_t n, int64_t k, float alpha, const float* A,
  * multiple of 16 and n of 4: hpvm_sgemm's DMA-fed 256 x 256 tile) if it
  * gives 256 tiles and k >= 256, or the staged 128 x 128 x 64 one with 64 x 32
  * leaves, or, of those with k < 1024, any tile on the FP32 operands, of
- * deeper ones the 128 x 256 one.  Every other argument and rule is
- * hpvm_sgemm's.                                                            */
+ * deeper ones the 128 x 256 one.  BF16 products of less than 256 tiles of
+ * 256 x 256 keep the staged tile also where one on the FP32 operands that
+ * cannot run beside an open stream (see hpvm_stream_open) is faster.  Every
+ * other argument and rule is hpvm_sgemm's.                                 */
 int hpvm_sgemm_ws(int64_t m, int64_t n, int64_t k, float alpha, const float* A, int64_t lda,
                   const float* B, int64_t ldb, float beta, float* C, int64_t ldc, int32_t prec,
                   const hpvm_tile* tile, void* workspace, int64_t workspace_bytes, void* stream);
@@ -680,7 +682,14 @@ int hpvm_sgemm_pair_workspace_bytes(int64_t m, int64_t n, int64_t k, const hpvm_
  * While a stream is open its kernel is resident: a device-wide wait
  * (hipDeviceSynchronize, and calls that imply it such as hipFree) waits for
  * that kernel too, i.e. until the stream is closed or reaches its idle
- * limit.  Wait on streams or events instead.                                */
+ * limit.  Wait on streams or events instead.  Another kernel starts beside it
+ * only in what two resident workgroups leave of a compute unit: 87 KB of LDS
+ * and, per SIMD, 176 registers a lane.  A larger one waits until the stream
+ * has ended.  With no tile, FP32 products need more from 256 tiles of
+ * 256 x 256 on.  So do BF16 ones, and whole-tile ones that split their
+ * contraction or, below 2^31 multiply-adds, give 256 tiles of 128 x 128.
+ * bf16x3 ones need more from 256 tiles of 128 x 128 or 2^31 multiply-adds on,
+ * and whole-tile ones that split their contraction.                         */
 
 typedef struct hpvm_stream_config {
   int32_t capacity;  /* ring slots = most items pushed and not yet popped,

@@ -20,8 +20,8 @@ namespace hpvm {
 
 // FP32 kernel: v_mfma_f32_32x32x2f32, FP32 operands and accumulation.  The
 // register-staged loop remains for the products the DMA-fed one does not
-// take (f32_any_fits): an operand of 1 to 3 columns, or rows 2^22 floats or
-// more apart.
+// take (f32_any_fits): an operand of 1 to 3 columns, rows 2^22 floats or
+// more apart, or a contraction deeper than kAnyDepth.
 template <int TM, int TN, int TK, int WM, int WN, bool AT, bool BT>
 __global__ void __launch_bounds__((TM / WM) * (TN / WN) * kWave) sgemm_mfma_f32(GemmArgs p) {
   extern __shared__ __align__(16) float lds[];
@@ -113,11 +113,10 @@ struct Bf16Config {
   }
 };
 
-// Tiles of KW k groups (TK = KW sub-slabs of SUB): a wave computes a WM x WN
-// block of its group and, after the groups' sum, owns WM / KW of its rows.
-
 // The DMA-fed loops for any size and alignment (mfma_f32_any.hpp,
-// mfma_bf16_any.hpp): TK deep sub-slabs, KW of them per slab, NST stages.  It replaced register-staged
+// mfma_bf16_any.hpp): TK deep sub-slabs, KW of them per slab, NST stages.  In
+// tiles of KW k groups a wave computes a WM x WN block of its group and, after
+// the groups' sum, owns WM / KW of its rows.  They replaced register-staged
 // loops of the same tiles, which loaded one slab ahead (and element by
 // element where an operand was not 16-byte aligned) and waited a memory
 // round trip for nearly every slab: 1000 x 1003 x 777, 64 x 64 tiles, 21.6 us
